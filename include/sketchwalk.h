@@ -351,14 +351,13 @@ int sw_sparse_attn_decode_noalloc(int dtype, const void* q, const void* Kc, cons
 /*
  * sw_decode_step - one decode step of every layer in one call: Alg. 2 steps
  * 1-7 for layer 0, 1, ..., layers-1 in order (the walk row of layer l starts
- * from that of layer l-1; layer 0 is the first walked layer). Per layer it
- * enqueues the same arithmetic as sw_kv_append + sw_sketch_scores_decode +
+ * from that of layer l-1; layer 0 is the first walked layer). It enqueues the
+ * same arithmetic as sw_kv_append + sw_sketch_scores_decode +
  * sw_walk_update_decode_variant + sw_select_topk_blocks_decode +
- * sw_sparse_attn_decode, with the KV append, the score updates and the walk
- * over the score entries the step leaves unchanged in one launch, and the
- * open block's walk terms and the normalisation in the selection's launch
- * (4 kernel launches per layer instead of 7); results are bit-identical to
- * those calls.
+ * sw_sparse_attn_decode for every layer, with the KV append and the score
+ * updates of all layers in one launch, one launch per layer for its walk row
+ * beside the selection of the layer before it, and the attention of several
+ * layers in one launch; results are bit-identical to those calls.
  *
  * Layer-stacked, contiguous buffers (device):
  *   q_new [layers][batch][h_q][d], k_new, v_new [layers][batch][h_kv][d]
@@ -369,9 +368,10 @@ int sw_sparse_attn_decode_noalloc(int dtype, const void* q, const void* Kc, cons
  *   [layers][batch][h_q][d] attention outputs (out, input dtype).
  * T_max <= b_max * B; walk_variant SW_WALK_POWER or SW_WALK_RELU; other
  * arguments as in the per-layer calls. workspace: >=
- * sw_decode_step_workspace_bytes(...) bytes, 256-byte aligned, reused by
- * every layer in stream order. The call only enqueues work on `stream`; it
- * may be captured into a HIP graph.
+ * sw_decode_attn_workspace_bytes(...) bytes, 256-byte aligned; it holds the
+ * attention's partials, and the layers whose partials fit share a launch
+ * (sw_decode_step_workspace_bytes(...) is the size to ask for). The call only
+ * enqueues work on `stream`; it may be captured into a HIP graph.
  */
 int64_t sw_decode_step_workspace_bytes(int batch, int h_q, int h_kv, int d);
 int sw_decode_step(int dtype, int layers, int batch, int h_q, int h_kv, int d, int r, int T_max,

@@ -484,10 +484,9 @@ def decode_step(q_new: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, K
     o.setdefault("idx", torch.empty((L, batch, kmax), dtype=torch.int32, device=dev))
     o.setdefault("cnt", torch.empty((L, batch), dtype=torch.int32, device=dev))
     o.setdefault("O", torch.empty_like(q_new))
-    wsb = int(load().sw_decode_step_workspace_bytes(batch, h_q, h_kv, d))
-    if wsb < 0:
-        _check(1, "sw_decode_step_workspace_bytes")
-    if workspace is None or workspace.numel() < wsb:
+    least = decode_attn_workspace_bytes(batch, h_q, h_kv, d)
+    if workspace is None or workspace.numel() < least:
+        wsb = int(load().sw_decode_step_workspace_bytes(batch, h_q, h_kv, d))
         workspace = torch.empty((max(wsb, 256),), dtype=torch.uint8, device=dev)
     for name, t in (("k_new", k_new), ("v_new", v_new), ("Kc", Kc), ("Vc", Vc)):
         if t.dtype != q_new.dtype:

@@ -469,7 +469,7 @@ int sw_sparse_attn_decode(int dtype, const void* q, const void* Kc, const void* 
     return fail(SW_ERR_INVALID_ARG, "workspace_bytes=%lld < required %lld",
                 (long long)workspace_bytes, (long long)need);
   if (!(scale > 0.0f)) scale = 1.0f / sqrtf((float)d);
-  hipError_t e = sw::launch_attn_decode(dtype, q, Kc, Vc, batch, h_q, h_kv, d, T_max, B, pos, idx,
+  hipError_t e = sw::launch_attn_decode(dtype, 1, q, Kc, Vc, batch, h_q, h_kv, d, T_max, B, pos, idx,
                                         cnt, kmax, scale, O, reinterpret_cast<float*>(workspace),
                                         reinterpret_cast<hipStream_t>(stream));
   return hip_status(e, "sw_sparse_attn_decode launch");
@@ -493,8 +493,15 @@ int sw_sparse_attn_decode_noalloc(int dtype, const void* q, const void* Kc, cons
                                scale, O, ws, need, stream);
 }
 
+// The attention of as many layers as the workspace holds shares a launch. Eight
+// layers are asked for where they stay within 64 MiB: at batch 1 one layer's
+// attention is 256 workgroups of a few microseconds.
 int64_t sw_decode_step_workspace_bytes(int batch, int h_q, int h_kv, int d) {
-  return sw_decode_attn_workspace_bytes(batch, h_q, h_kv, d);
+  const int64_t one = sw_decode_attn_workspace_bytes(batch, h_q, h_kv, d);
+  if (one < 0) return one;
+  int64_t n = ((int64_t)64 << 20) / one;
+  n = n < 1 ? 1 : n > 8 ? 8 : n;
+  return n * one;
 }
 
 int sw_decode_step(int dtype, int layers, int batch, int h_q, int h_kv, int d, int r, int T_max,
@@ -541,35 +548,26 @@ int sw_decode_step(int dtype, int layers, int batch, int h_q, int h_kv, int d, i
     return fail(SW_ERR_INVALID_ARG, "workspace_bytes=%lld < required %lld",
                 (long long)workspace_bytes, (long long)need);
   if (!(scale > 0.0f)) scale = 1.0f / sqrtf((float)d);
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  hipError_t e = sw::launch_decode_layers(dtype, layers, q_new, k_new, v_new, Kc, Vc, T_max, batch, h_q,
+                                          h_kv, d, B, pos, signs, cols, r, b_max,
+                                          static_cast<char*>(state), s, walk_variant == SW_WALK_RELU,
+                                          rows, k, density_pct, flags, idx, cnt, kmax, st);
+  if (e != hipSuccess) return hip_status(e, "sw_decode_step launch");
   const size_t esz = dtype == SW_BF16 ? 2 : 4;
   const int64_t q_step = (int64_t)batch * h_q * d * esz;
-  const int64_t kv_step = (int64_t)batch * h_kv * d * esz;
   const int64_t cache_step = (int64_t)batch * h_kv * T_max * d * esz;
-  const int64_t state_step = sw::decode_layout(batch, d, r, b_max).total;
-  const int64_t row_step = (int64_t)batch * b_max;
-  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const char* qb = static_cast<const char*>(q_new);
-  const char* kb = static_cast<const char*>(k_new);
-  const char* vb = static_cast<const char*>(v_new);
-  char* Kb = static_cast<char*>(Kc);
-  char* Vb = static_cast<char*>(Vc);
-  char* Sb = static_cast<char*>(state);
-  char* Ob = static_cast<char*>(O);
-  for (int l = 0; l < layers; ++l) {
-    char* stl = Sb + l * state_step;
-    void* Kl = Kb + l * cache_step;
-    void* Vl = Vb + l * cache_step;
-    double* rl = rows + l * row_step;
-    int32_t* il = idx + (int64_t)l * batch * kmax;
-    int32_t* cl = cnt + (int64_t)l * batch;
-    hipError_t e = sw::launch_decode_layer(
-        dtype, qb + l * q_step, kb + l * kv_step, vb + l * kv_step, Kl, Vl, T_max, batch, h_q,
-        h_kv, d, B, pos, signs, cols, r, b_max, stl, s, walk_variant == SW_WALK_RELU,
-        l == 0 ? nullptr : rl - row_step, rl, k, density_pct, flags, il, cl, kmax, st);
-    if (e == hipSuccess)
-      e = sw::launch_attn_decode(dtype, qb + l * q_step, Kl, Vl, batch, h_q, h_kv, d, T_max, B, pos,
-                                 il, cl, kmax, scale, Ob + l * q_step,
-                                 reinterpret_cast<float*>(workspace), st);
+  // layers whose partials fit the workspace share a launch (grid limit 65535)
+  int64_t per = workspace_bytes / need;
+  per = per > 65535 ? 65535 : per;
+  for (int64_t l = 0; l < layers; l += per) {
+    const int n = (int)(layers - l < per ? layers - l : per);
+    e = sw::launch_attn_decode(dtype, n, static_cast<const char*>(q_new) + l * q_step,
+                               static_cast<const char*>(Kc) + l * cache_step,
+                               static_cast<const char*>(Vc) + l * cache_step, batch, h_q, h_kv, d, T_max,
+                               B, pos, idx + l * batch * kmax, cnt + l * batch, kmax, scale,
+                               static_cast<char*>(O) + l * q_step,
+                               reinterpret_cast<float*>(workspace), st);
     if (e != hipSuccess) return hip_status(e, "sw_decode_step launch");
   }
   return ok();

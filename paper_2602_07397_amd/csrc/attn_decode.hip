@@ -10,7 +10,10 @@
 //                           selected tokens of one (sequence, KV head) for all
 //                           G query heads of the group with 16-byte loads and
 //                           keeps an online softmax per (key lane group, head)
-//  attn_merge_kernel        log-sum-exp merge of the splits
+//  attn_merge_kernel        log-sum-exp merge of the splits, one workgroup per
+//                           (sequence, query head)
+// The layers of a one-call decode step share a launch (blockIdx.y is the
+// layer; buffers are stacked over the layers).
 #include <mutex>
 
 #include "sw_common.h"
@@ -39,6 +42,11 @@ __device__ __forceinline__ float sum_xor32(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// Elements from one layer to the next of the stacked buffers.
+struct DecodeAttnSteps {
+  long long q, cache, idx, cnt, ws;
+};
+
 constexpr int kDecodeSelCache = 512;   // selected-block entries cached per workgroup
 
 // Tuning constants (overridable at build time).
@@ -63,7 +71,14 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const T* __restrict__ 
                                                           const int32_t* __restrict__ idx,
                                                           const int32_t* __restrict__ cnt,
                                                           int kmax, float sl2, int S,
-                                                          float* __restrict__ ws) {
+                                                          float* __restrict__ ws,
+                                                          DecodeAttnSteps ls) {
+  q += blockIdx.y * ls.q;
+  Kc += blockIdx.y * ls.cache;
+  Vc += blockIdx.y * ls.cache;
+  idx += blockIdx.y * ls.idx;
+  cnt += blockIdx.y * ls.cnt;
+  ws += blockIdx.y * ls.ws;
   constexpr int EPL = 16 / sizeof(T);            // elements per lane per row
   constexpr int LPK = D / EPL;                   // lanes per key row
   constexpr int KPW = 64 / LPK;                  // key rows per wave per step
@@ -272,7 +287,13 @@ __global__ __launch_bounds__(256) void attn_decode_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ Kc, const uint16_t* __restrict__ Vc,
     int h_kv, int G, int T_max, int B, const int32_t* __restrict__ pos,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int kmax, float sl2, int S,
-    float* __restrict__ ws) {
+    float* __restrict__ ws, DecodeAttnSteps ls) {
+  q += blockIdx.y * ls.q;
+  Kc += blockIdx.y * ls.cache;
+  Vc += blockIdx.y * ls.cache;
+  idx += blockIdx.y * ls.idx;
+  cnt += blockIdx.y * ls.cnt;
+  ws += blockIdx.y * ls.ws;
   constexpr int VTS = 16 + 4;                      // V^T row stride (keys + pad)
   constexpr int GPS = SW_DEC_GPS;                  // 16-token groups per wave step
   // LDS: per-wave V^T slices during the loop; the epilogue's partials reuse it
@@ -493,29 +514,56 @@ __global__ __launch_bounds__(256) void attn_decode_mfma_kernel(
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(128) void attn_merge_kernel(const float* __restrict__ ws, int S, int D,
-                                                         long long n_hu, T* __restrict__ O) {
+// Four wavefronts per (sequence, query head): every wavefront holds the splits'
+// maxima and sums (lane s holds split s) and adds the outputs of splits w,
+// w + 4, ..., all loaded before the first is used; the four sums are added in
+// order. The splits' outputs come from another launch, so the kernel is two
+// dependent loads and one barrier long: 32 splits took 10.5 us as a loop over
+// the splits (batch 1, 32 heads).
+template <typename T, int D, int NLOAD>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ ws, int S,
+                                                         long long n_hu, T* __restrict__ O,
+                                                         long long ws_step) {
+  static_assert(kDecodeMaxSplits <= 64, "one split per lane");   // and S <= 4 * NLOAD
+  constexpr int V = D / 64;                        // output dims per lane
+  typedef float vec __attribute__((ext_vector_type(V)));
+  __shared__ float part[4][D];
   const long long hu = blockIdx.x;
-  const float* ws_ml = ws;
-  const float* ws_o = ws + n_hu * S * 2;
-  float M = -INFINITY;
-  for (int s = 0; s < S; ++s) M = fmaxf(M, ws_ml[(hu * S + s) * 2]);
-  for (int dim = threadIdx.x; dim < D; dim += 128) {
-    float Lsum = 0.0f, Osum = 0.0f;
-    if (M != -INFINITY) {
-      for (int s = 0; s < S; ++s) {
-        const float sc = exp2f(ws_ml[(hu * S + s) * 2] - M);
-        Lsum += ws_ml[(hu * S + s) * 2 + 1] * sc;
-        Osum += ws_o[(hu * S + s) * D + dim] * sc;
-      }
-    }
-    const float v = Lsum > 0.0f ? Osum / Lsum : 0.0f;
-    if constexpr (sizeof(T) == 2)
-      reinterpret_cast<uint16_t*>(O)[hu * D + dim] = f32_to_bf16(v);
-    else
-      O[hu * D + dim] = v;
+  ws += blockIdx.y * ws_step;
+  const float* ws_ml = ws + hu * S * 2;
+  const float* ws_o = ws + n_hu * S * 2 + hu * S * D;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  float m = ws_ml[2 * min(l, S - 1)];
+  const float ls = ws_ml[2 * min(l, S - 1) + 1];
+  vec o[NLOAD];
+#pragma unroll
+  for (int i = 0; i < NLOAD; ++i)
+    o[i] = *reinterpret_cast<const vec*>(ws_o + (long long)min(w + 4 * i, S - 1) * D + l * V);
+  m = l < S ? m : -INFINITY;
+  float M = m;
+  for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
+  // a split without keys (m = -inf) has weight 0; without any key all have
+  const float sc = (M != -INFINITY && l < S) ? exp2f(m - M) : 0.0f;
+  float Lsum = ls * sc;
+  for (int off = 32; off > 0; off >>= 1) Lsum += __shfl_xor(Lsum, off);
+  vec acc = {};
+#pragma unroll
+  for (int i = 0; i < NLOAD; ++i) {
+    const int s = w + 4 * i;
+    if (s < S) acc += o[i] * __shfl(sc, s);
   }
+#pragma unroll
+  for (int e = 0; e < V; ++e) part[w][l * V + e] = acc[e];
+  __syncthreads();
+  if (threadIdx.x >= D) return;
+  const int dim = threadIdx.x;
+  const float sum = ((part[0][dim] + part[1][dim]) + part[2][dim]) + part[3][dim];
+  const float v = Lsum > 0.0f ? sum / Lsum : 0.0f;
+  const long long at = (blockIdx.y * n_hu + hu) * D + dim;
+  if constexpr (sizeof(T) == 2)
+    reinterpret_cast<uint16_t*>(O)[at] = f32_to_bf16(v);
+  else
+    O[at] = v;
 }
 
 // Splits per (sequence, KV head): about SW_DEC_WGS workgroups; 512 fills
@@ -532,12 +580,12 @@ template <typename T, int D>
 static void launch_attn_decode_t(int G, dim3 grid, hipStream_t st, const T* q, const T* Kc,
                                  const T* Vc, int h_kv, int T_max, int B, const int32_t* pos,
                                  const int32_t* idx, const int32_t* cnt, int kmax, float sl2,
-                                 int S, float* ws) {
+                                 int S, float* ws, const DecodeAttnSteps& ls) {
   switch (G) {
-    case 1: hipLaunchKernelGGL((attn_decode_kernel<T, D, 1>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws); break;
-    case 2: hipLaunchKernelGGL((attn_decode_kernel<T, D, 2>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws); break;
-    case 4: hipLaunchKernelGGL((attn_decode_kernel<T, D, 4>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws); break;
-    default: hipLaunchKernelGGL((attn_decode_kernel<T, D, 8>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws); break;
+    case 1: hipLaunchKernelGGL((attn_decode_kernel<T, D, 1>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
+    case 2: hipLaunchKernelGGL((attn_decode_kernel<T, D, 2>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
+    case 4: hipLaunchKernelGGL((attn_decode_kernel<T, D, 4>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
+    default: hipLaunchKernelGGL((attn_decode_kernel<T, D, 8>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
   }
 }
 
@@ -573,36 +621,58 @@ hipError_t noalloc_scratch(void** out) {
   return hipSuccess;
 }
 
-hipError_t launch_attn_decode(int dtype, const void* q, const void* Kc, const void* Vc, int batch,
-                              int h_q, int h_kv, int d, int T_max, int B, const int32_t* pos,
-                              const int32_t* idx, const int32_t* cnt, int kmax, float scale,
-                              void* O, float* ws, hipStream_t st) {
+hipError_t launch_attn_decode(int dtype, int layers, const void* q, const void* Kc, const void* Vc,
+                              int batch, int h_q, int h_kv, int d, int T_max, int B,
+                              const int32_t* pos, const int32_t* idx, const int32_t* cnt, int kmax,
+                              float scale, void* O, float* ws, hipStream_t st) {
   const int G = h_q / h_kv;
   const int S = decode_attn_splits(batch, h_kv);
-  const dim3 grid((unsigned)(batch * h_kv * S));
+  const dim3 grid((unsigned)(batch * h_kv * S), (unsigned)layers);
   const float sl2 = scale * kLog2eD;
   const long long n_hu = (long long)batch * h_q;
+  const dim3 mgrid((unsigned)n_hu, (unsigned)layers);
+  DecodeAttnSteps ls;
+  ls.q = n_hu * d;
+  ls.cache = (long long)batch * h_kv * T_max * d;
+  ls.idx = (long long)batch * kmax;
+  ls.cnt = batch;
+  ls.ws = n_hu * S * (d + 2);
+#define SW_MERGE_N(T, D, N)                                                                    \
+  hipLaunchKernelGGL((attn_merge_kernel<T, D, N>), mgrid, dim3(256), 0, st, ws, S, n_hu,       \
+                     reinterpret_cast<T*>(O), ls.ws)
+#define SW_MERGE(T, D)                                      \
+  do {                                                      \
+    if (S <= 4) SW_MERGE_N(T, D, 1);                        \
+    else if (S <= 16) SW_MERGE_N(T, D, 4);                  \
+    else SW_MERGE_N(T, D, kDecodeMaxSplits / 4);            \
+  } while (0)
   if (dtype == SW_BF16) {
     auto qq = reinterpret_cast<const uint16_t*>(q);
     auto kk = reinterpret_cast<const uint16_t*>(Kc);
     auto vv = reinterpret_cast<const uint16_t*>(Vc);
-    if (d == 128)
+    if (d == 128) {
       hipLaunchKernelGGL(attn_decode_mfma_kernel<128>, grid, dim3(256), 0, st, qq, kk, vv, h_kv, G,
-                         T_max, B, pos, idx, cnt, kmax, sl2, S, ws);
-    else
+                         T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
+      SW_MERGE(uint16_t, 128);
+    } else {
       hipLaunchKernelGGL(attn_decode_mfma_kernel<64>, grid, dim3(256), 0, st, qq, kk, vv, h_kv, G,
-                         T_max, B, pos, idx, cnt, kmax, sl2, S, ws);
-    hipLaunchKernelGGL(attn_merge_kernel<uint16_t>, dim3((unsigned)n_hu), dim3(128), 0, st, ws, S, d,
-                       n_hu, reinterpret_cast<uint16_t*>(O));
+                         T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
+      SW_MERGE(uint16_t, 64);
+    }
   } else {
     auto qq = reinterpret_cast<const float*>(q);
     auto kk = reinterpret_cast<const float*>(Kc);
     auto vv = reinterpret_cast<const float*>(Vc);
-    if (d == 128) launch_attn_decode_t<float, 128>(G, grid, st, qq, kk, vv, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws);
-    else launch_attn_decode_t<float, 64>(G, grid, st, qq, kk, vv, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws);
-    hipLaunchKernelGGL(attn_merge_kernel<float>, dim3((unsigned)n_hu), dim3(128), 0, st, ws, S, d, n_hu,
-                       reinterpret_cast<float*>(O));
+    if (d == 128) {
+      launch_attn_decode_t<float, 128>(G, grid, st, qq, kk, vv, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
+      SW_MERGE(float, 128);
+    } else {
+      launch_attn_decode_t<float, 64>(G, grid, st, qq, kk, vv, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
+      SW_MERGE(float, 64);
+    }
   }
+#undef SW_MERGE
+#undef SW_MERGE_N
   return hipGetLastError();
 }
 

@@ -12,6 +12,9 @@
 //                         workgroup writes its rows' entries of (i) the new
 //                         score row and (ii) the new last column, 4 lanes per
 //                         sketch row
+//  decode_sketch_layers_kernel  the one-call step's launch of the same work for
+//                         every layer at once (the layers' sketches do not
+//                         depend on each other)
 //  walk_strip_kernel      step 5 on the query row only, for the score entries
 //                         the step leaves unchanged (rows and columns before
 //                         the open block): r_prev W with W = (A/c)^s (or the
@@ -23,13 +26,13 @@
 //                         wavefront, then the wavefronts); the rows above a
 //                         strip, which hold only its decode-filled columns,
 //                         are shared by every thread of the workgroup
-//  decode_sketch_walk_kernel  the one-call step's launch of both: the walk
-//                         workgroups and the sketch workgroups of a layer
-//                         side by side (they touch disjoint state)
 //  walk_row_norm_kernel   adds the open block's row and column terms to the
 //                         walk row and divides it by its largest magnitude
-//                         (the one-call step does this in
-//                         select_decode_norm_kernel before selecting, step 6)
+//  decode_chain_kernel    the one-call step's launch per layer: the whole walk
+//                         row of one layer (before its division), beside the
+//                         selection of the layer before it
+#include <type_traits>
+
 #include "select_row.h"
 #include "sw_common.h"
 #include "sw_internal.h"
@@ -337,7 +340,7 @@ __device__ __forceinline__ void decode_sketch_body(const T* __restrict__ q_new,
   }
 }
 
-template <typename T, bool APPEND>
+template <typename T>
 __global__ __launch_bounds__(256) void decode_sketch_kernel(const T* __restrict__ q_new,
                                                             const T* __restrict__ k_new, int h_q,
                                                             int h_kv, int d, int B,
@@ -345,13 +348,37 @@ __global__ __launch_bounds__(256) void decode_sketch_kernel(const T* __restrict_
                                                             const int8_t* __restrict__ signs,
                                                             const int32_t* __restrict__ cols, int r,
                                                             int batch, int b_max,
-                                                            char* __restrict__ state,
-                                                            const T* __restrict__ v_new,
-                                                            T* __restrict__ Kc, T* __restrict__ Vc,
-                                                            int T_max) {
+                                                            char* __restrict__ state) {
   __shared__ double lds[sketch_lds_doubles<T>()];
-  decode_sketch_body<T, APPEND>(q_new, k_new, h_q, h_kv, d, B, pos, signs, cols, r, batch, b_max,
-                                state, v_new, Kc, Vc, T_max, blockIdx.x, blockIdx.y, lds);
+  decode_sketch_body<T, false>(q_new, k_new, h_q, h_kv, d, B, pos, signs, cols, r, batch, b_max,
+                               state, nullptr, nullptr, nullptr, 0, blockIdx.x, blockIdx.y, lds);
+}
+
+// Byte strides from one layer to the next of the one-call step's stacked
+// buffers.
+struct LayerStrides {
+  long long q, kv, cache, state;
+};
+
+// The one-call step: steps 1-4 of every layer in one launch (blockIdx.z is
+// the layer). A launch per layer is latency: about 8 us each at batch 1,
+// where a layer has 9 workgroups; together the layers fill the chip.
+template <typename T>
+__global__ __launch_bounds__(256) void decode_sketch_layers_kernel(
+    const T* __restrict__ q_new, const T* __restrict__ k_new, int h_q, int h_kv, int d, int B,
+    const int32_t* __restrict__ pos, const int8_t* __restrict__ signs,
+    const int32_t* __restrict__ cols, int r, int batch, int b_max, char* __restrict__ state,
+    const T* __restrict__ v_new, T* __restrict__ Kc, T* __restrict__ Vc, int T_max,
+    LayerStrides ls) {
+  __shared__ double lds[sketch_lds_doubles<T>()];
+  const long long l = blockIdx.z;
+  auto at = [l](auto* p, long long step) {
+    using C = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(p)>>, const char, char>;
+    return reinterpret_cast<decltype(p)>(reinterpret_cast<C*>(p) + l * step);
+  };
+  decode_sketch_body<T, true>(at(q_new, ls.q), at(k_new, ls.kv), h_q, h_kv, d, B, pos, signs, cols, r,
+                              batch, b_max, state + l * ls.state, at(v_new, ls.kv), at(Kc, ls.cache),
+                              at(Vc, ls.cache), T_max, blockIdx.x, blockIdx.y, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -363,7 +390,7 @@ constexpr int kStripQuads = kStripCols / 4;
 constexpr int kStripGroups = 32;         // row groups per workgroup, 8 per wavefront
 constexpr int kStripThreads = kStripQuads * kStripGroups;
 #ifndef SW_STRIP_ROWS
-#define SW_STRIP_ROWS 4                  // rows each thread loads before adding
+#define SW_STRIP_ROWS 8                  // rows each thread loads before adding
 #endif
 constexpr int kStripBufWord3 = 0x00020000;   // raw buffer descriptor word 3 (gfx9 family)
 
@@ -383,16 +410,66 @@ __device__ __forceinline__ uint4 load_quad(__amdgpu_buffer_rsrc_t ra, int off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0));
 }
 
+// The previous layer's walk row as a workgroup of 256 threads takes it up,
+// thread t the entries t, t + 256, ... The per-layer calls hold it divided by
+// its largest magnitude already; the one-call step keeps it undivided until
+// the launches that read it are done, and each of their workgroups divides its
+// own copy (a maximum does not depend on the order it is taken in, so all get
+// the same bits). The first walked layer's row is W[b_cur][:] itself and is
+// taken from the open block's score row.
+struct PrevRow {
+  const double* row;       // [batch][b_max]; unused when rowc is set
+  const float* rowc;       // [batch][b_max] score row of the first layer, or NULL
+  const double* scale;     // [batch] score scale of the first layer
+
+  // the loads carry no condition (clamped indices)
+  template <bool S8, bool RELU, int MAXE>
+  __device__ __forceinline__ void load(int bi, int b_max, int s_exp, double (&v)[MAXE]) const {
+    const int t = threadIdx.x;
+    if (rowc == nullptr) {
+#pragma unroll
+      for (int i = 0; i < MAXE; ++i)
+        v[i] = row[(long long)bi * b_max + min(t + i * 256, b_max - 1)];
+    } else {
+      const double c0 = scale[bi];
+      const double inv_c = 1.0 / (c0 > 0.0 ? c0 : 1.0);
+      float a[MAXE];
+#pragma unroll
+      for (int i = 0; i < MAXE; ++i)
+        a[i] = rowc[(long long)bi * b_max + min(t + i * 256, b_max - 1)];
+#pragma unroll
+      for (int i = 0; i < MAXE; ++i) v[i] = walk_weight<S8, RELU>(a[i], inv_c, s_exp);
+    }
+  }
+
+  // 1 / (largest magnitude over blocks 0..b_cur), or 1 for a row of zeros;
+  // one barrier, tmp holds 4 doubles
+  template <int MAXE>
+  __device__ __forceinline__ double inverse_max(const double (&v)[MAXE], int bc, double* tmp) const {
+    const int t = threadIdx.x;
+    double mx = 0.0;
+#pragma unroll
+    for (int i = 0; i < MAXE; ++i)
+      if (t + i * 256 <= bc) mx = fmax(mx, fabs(v[i]));
+    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
+    if ((t & 63) == 0) tmp[t >> 6] = mx;
+    __syncthreads();
+    mx = fmax(fmax(tmp[0], tmp[1]), fmax(tmp[2], tmp[3]));
+    return mx > 0.0 ? 1.0 / mx : 1.0;
+  }
+};
+
 // The walk row splits into the part the step's sketch does not change and the
 // open block's row and column, which it rewrites (Alg. 2 step 4):
 //   r[j] = sum_{m != b_cur} r_prev[m] W[m][j]                 (j < b_cur)
 //          + r_prev[b_cur] W[b_cur][j]
 //   r[b_cur] = sum_{m <= b_cur} r_prev[m] W[m][b_cur]
-// walk_old_body computes the first sum from the score cache as the previous
-// steps left it (it reads no entry of row or column b_cur, so it may run
-// while the sketch of the same step writes them); walk_finish adds the rest.
+// walk_strips computes the first sum from the score cache (it reads no entry
+// of row or column b_cur); the per-layer calls add the rest in walk_finish,
+// the one-call step in walk_strips itself and in walk_column, with the same
+// sums in the same order.
 //
-// walk_old_body: one workgroup per (sequence, strip pair): strips k and
+// walk_strips: one workgroup per (sequence, strip pair): strips k and
 // S-1-k of 32 columns (S = lda / 32; the cache stores a strip's rows
 // contiguously, 128 bytes each, so a strip is read as one contiguous range).
 // Strip x's rows m = 32 x .. b_cur - 1 hold its causal entries, so a pair
@@ -417,13 +494,11 @@ constexpr int kWalkSmem = SW_MAX_BLOCKS;
 constexpr int kWalkLdsDoubles = kWalkSmem + 2 * (kStripThreads / 64) * 2 * kStripCols;
 static_assert(kStripThreads == 256 && kStripQuads == 8, "8 row groups x 8 quads per wavefront");
 
-template <bool S8, bool RELU>
-__device__ __forceinline__ void walk_old_body(const char* __restrict__ state, int batch, int d,
-                                              int r, int b_max, int B,
-                                              const int32_t* __restrict__ pos, int s_exp,
-                                              const double* __restrict__ r_prev,
-                                              double* __restrict__ r_out, int bi, int k,
-                                              double* lds) {
+template <bool S8, bool RELU, int MAXE, bool WHOLE>
+__device__ __forceinline__ void walk_strips(const char* __restrict__ state, int batch, int d, int r,
+                                            int b_max, int B, const int32_t* __restrict__ pos,
+                                            int s_exp, const PrevRow& prev,
+                                            double* __restrict__ r_out, int bi, int k, double* lds) {
   double* smem = lds;
   // wsum[w][strip][c]: wavefront w's strip-row sums; xw[w][strip][c]: its
   // rows-above sums (zero outside the decode-filled quads)
@@ -438,18 +513,16 @@ __device__ __forceinline__ void walk_old_body(const char* __restrict__ state, in
   const int p = pos[bi];
   const double c0 = reinterpret_cast<const double*>(state + L.scale)[bi];
   const int col0 = reinterpret_cast<const int32_t*>(state + L.col0)[bi];
-  constexpr int kStage = (SW_MAX_BLOCKS + kStripThreads - 1) / kStripThreads;
-  {
-    double rs[kStage];
+  double rs[MAXE];
+  prev.load<S8, RELU, MAXE>(bi, b_max, s_exp, rs);
+  if constexpr (!WHOLE) {
 #pragma unroll
-    for (int i = 0; i < kStage; ++i)
-      rs[i] = r_prev[(long long)bi * b_max + min(t + i * kStripThreads, b_max - 1)];
-#pragma unroll
-    for (int i = 0; i < kStage; ++i)
+    for (int i = 0; i < MAXE; ++i)
       if (t + i * kStripThreads < b_max) smem[t + i * kStripThreads] = rs[i];
   }
   const int bc = p / B;
   if (p < 0 || bc >= b_max) return;
+  const float* rowc = reinterpret_cast<const float*>(state + L.rowc) + (long long)bi * b_max;
   const int S = lda / kStripCols;
   const int sa = k, sb = S - 1 - k;                 // sb == sa: a single strip
   const double inv_c = 1.0 / (c0 > 0.0 ? c0 : 1.0);
@@ -489,30 +562,45 @@ __device__ __forceinline__ void walk_old_body(const char* __restrict__ state, in
     const int m = t + v * kStripThreads;
     pa[v] = load_quad(ra, (pre_b && m < xjb) ? cache_at(b_max, m, jd_b) * 4 : bytes);
   }
+  // The strip's rows, NR per pass and thread: every load of a pass is issued
+  // before any is used, those of the first pass before the previous row is
+  // staged.
+  constexpr int NR = S8 ? SW_STRIP_ROWS : SW_STRIP_ROWS / 2;   // the general power needs more registers
+  uint4 a[NR];
+  auto load_rows = [&](int i0) {
+#pragma unroll
+    for (int v = 0; v < NR; ++v) {
+      const int i = i0 + v * ng;
+      const bool ok = i < nrows && okj;
+      a[v] = load_quad(ra, ok ? cache_at(b_max, m0 + i, j) * 4 : bytes);
+    }
+  };
+  load_rows(gi);
+  // the open block's score row entry of the column this thread writes last
+  float wrow = 0.0f;
+  if constexpr (WHOLE) {
+    const int c = (t < kStripCols ? sa : sb) * kStripCols + t % kStripCols;
+    wrow = rowc[min(c, bc)];
+    const double inv = prev.inverse_max<MAXE>(rs, bc, smem + kWalkSmem);
+#pragma unroll
+    for (int i = 0; i < MAXE; ++i)
+      if (t + i * kStripThreads < b_max) smem[t + i * kStripThreads] = rs[i] * inv;
+  }
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   __syncthreads();                       // the staged row is visible
   const double* rp = smem;
-  {
-    constexpr int NR = S8 ? SW_STRIP_ROWS : SW_STRIP_ROWS / 2;   // the general power needs more registers
-    for (int i0 = gi; i0 < nrows; i0 += NR * ng) {
-      // every load of the pass is issued before any is used
-      uint4 a[NR];
+  for (int i0 = gi; i0 < nrows;) {
 #pragma unroll
-      for (int v = 0; v < NR; ++v) {
-        const int i = i0 + v * ng;
-        const bool ok = i < nrows && okj;
-        a[v] = load_quad(ra, ok ? cache_at(b_max, m0 + i, j) * 4 : bytes);
-      }
+    for (int v = 0; v < NR; ++v) {
+      const double rv = rp[m0 + min(i0 + v * ng, nrows - 1)];
+      const float av[4] = {__uint_as_float(a[v].x), __uint_as_float(a[v].y),
+                           __uint_as_float(a[v].z), __uint_as_float(a[v].w)};
 #pragma unroll
-      for (int v = 0; v < NR; ++v) {
-        const double rv = rp[m0 + min(i0 + v * ng, nrows - 1)];
-        const float av[4] = {__uint_as_float(a[v].x), __uint_as_float(a[v].y),
-                             __uint_as_float(a[v].z), __uint_as_float(a[v].w)};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (e != ebc) acc[e] += rv * walk_weight<S8, RELU>(av[e], inv_c, s_exp);
-      }
+      for (int e = 0; e < 4; ++e)
+        if (e != ebc) acc[e] += rv * walk_weight<S8, RELU>(av[e], inv_c, s_exp);
     }
+    i0 += NR * ng;
+    if (i0 < nrows) load_rows(i0);
   }
   // Both sums are reduced in a fixed order behind one barrier: per wavefront
   // by lane exchanges (a butterfly), then over the four wavefronts in order.
@@ -592,6 +680,7 @@ __device__ __forceinline__ void walk_old_body(const char* __restrict__ state, in
       const int jj = xs * kStripCols + c;
       if (jj >= col0 && xs * kStripCols > 0)
         v += ((xw[0][which][c] + xw[1][which][c]) + xw[2][which][c]) + xw[3][which][c];
+      if constexpr (WHOLE) v = v + rp[bc] * walk_weight<S8, RELU>(wrow, inv_c, s_exp);
       if (jj < bc) r_out[(long long)bi * b_max + jj] = v;
     }
   }
@@ -599,7 +688,7 @@ __device__ __forceinline__ void walk_old_body(const char* __restrict__ state, in
 
 // Per-layer form: the unchanged part of the walk row into r_out[j], j < b_cur
 // (walk_row_norm_kernel completes it).
-template <bool S8, bool RELU>
+template <bool S8, bool RELU, int MAXE>
 __global__ __launch_bounds__(kStripThreads) void walk_strip_kernel(const char* __restrict__ state,
                                                                    int batch, int d, int r,
                                                                    int b_max, int B,
@@ -608,31 +697,9 @@ __global__ __launch_bounds__(kStripThreads) void walk_strip_kernel(const char* _
                                                                    const double* __restrict__ r_prev,
                                                                    double* __restrict__ r_out) {
   __shared__ double lds[kWalkLdsDoubles];
-  walk_old_body<S8, RELU>(state, batch, d, r, b_max, B, pos, s_exp, r_prev, r_out, blockIdx.x,
-                          blockIdx.y, lds);
-}
-
-// The one-call step: the workgroups with blockIdx.y < pairs compute the
-// unchanged part of this layer's walk row (none at the first walked layer),
-// the others run the incremental sketch (with the KV append). The two read
-// and write disjoint parts of the state, so they run side by side.
-template <typename T, bool S8, bool RELU>
-__global__ __launch_bounds__(256) void decode_sketch_walk_kernel(
-    const T* __restrict__ q_new, const T* __restrict__ k_new, int h_q, int h_kv, int d, int B,
-    const int32_t* __restrict__ pos, const int8_t* __restrict__ signs,
-    const int32_t* __restrict__ cols, int r, int batch, int b_max, char* __restrict__ state,
-    const T* __restrict__ v_new, T* __restrict__ Kc, T* __restrict__ Vc, int T_max, int pairs,
-    int s_exp, const double* __restrict__ r_prev, double* __restrict__ rows) {
-  static_assert(kStripThreads == 256, "both roles run 256 threads");
-  constexpr int kLds = sketch_lds_doubles<T>() > kWalkLdsDoubles ? sketch_lds_doubles<T>()
-                                                                 : kWalkLdsDoubles;
-  __shared__ double lds[kLds];
-  if ((int)blockIdx.y < pairs)
-    walk_old_body<S8, RELU>(state, batch, d, r, b_max, B, pos, s_exp, r_prev, rows, blockIdx.x,
-                            blockIdx.y, lds);
-  else
-    decode_sketch_body<T, true>(q_new, k_new, h_q, h_kv, d, B, pos, signs, cols, r, batch, b_max,
-                                state, v_new, Kc, Vc, T_max, blockIdx.x, blockIdx.y - pairs, lds);
+  walk_strips<S8, RELU, MAXE, false>(state, batch, d, r, b_max, B, pos, s_exp,
+                                     PrevRow{r_prev, nullptr, nullptr}, r_out, blockIdx.x,
+                                     blockIdx.y, lds);
 }
 
 // walk_finish: thread t's values v[e] of the finished (unnormalised) walk row
@@ -732,49 +799,135 @@ __global__ __launch_bounds__(256) void walk_row_norm_kernel(const char* __restri
   for (int j = avail + t; j < b_max; j += 256) out[j] = 0.0;
 }
 
-// The one-call step: the walk row of each sequence finished from its
-// unchanged part in rows, divided in place by its largest magnitude over
-// blocks 0..b_cur (entries past b_cur zeroed), then its selection (Alg. 2
-// step 6, forced set {0, b_cur}) from the rescaled values the threads still
-// hold in registers.
+// The open block's own entry of the one-call step's walk row,
+// r[b_cur] = sum over m <= b_cur of r_prev[m] W[m][b_cur]: one workgroup per
+// sequence, the same sum as in walk_finish.
 template <bool S8, bool RELU, int MAXE>
-__global__ __launch_bounds__(256) void select_decode_norm_kernel(
-    const char* __restrict__ state, int batch, int d, int r, int b_max, int B,
-    const int32_t* __restrict__ pos, int s_exp, const double* __restrict__ r_prev,
-    double* __restrict__ rows, int k, int pct, uint32_t flags, int32_t* __restrict__ idx,
-    int32_t* __restrict__ cnt, int kmax) {
-  __shared__ double tmp[4];
-  const int bi = blockIdx.x;
+__device__ __forceinline__ void walk_column(const char* __restrict__ state, int batch, int d, int r,
+                                            int b_max, int B, const int32_t* __restrict__ pos,
+                                            int s_exp, const PrevRow& prev,
+                                            double* __restrict__ r_out, int bi, double* tmp) {
+  const DecodeLayout L = decode_layout(batch, d, r, b_max);
+  const int t = threadIdx.x;
   const int p = pos[bi];
+  double rs[MAXE];
+  prev.load<S8, RELU, MAXE>(bi, b_max, s_exp, rs);
+  const double c0 = reinterpret_cast<const double*>(state + L.scale)[bi];
+  const double inv_c = 1.0 / (c0 > 0.0 ? c0 : 1.0);
+  const float* colc = reinterpret_cast<const float*>(state + L.colc) + (long long)bi * b_max;
+  float wcol[MAXE];
+#pragma unroll
+  for (int e = 0; e < MAXE; ++e) wcol[e] = colc[min(t + 256 * e, b_max - 1)];
   const int bc = p / B;
   if (p < 0 || bc >= b_max) return;
-  double* row = rows + (long long)bi * b_max;
+  const double inv = prev.inverse_max<MAXE>(rs, bc, tmp);
+  double cs = 0.0;
+#pragma unroll
+  for (int e = 0; e < MAXE; ++e)
+    if (t + 256 * e <= bc) {
+      const double rv = rs[e] * inv;
+      cs += rv * walk_weight<S8, RELU>(wcol[e], inv_c, s_exp);
+    }
+  for (int off = 1; off < 64; off <<= 1) cs += __shfl_xor(cs, off);
+  __syncthreads();                       // tmp is read
+  if ((t & 63) == 0) tmp[t >> 6] = cs;
+  __syncthreads();
+  if (t == 0) r_out[(long long)bi * b_max + bc] = ((tmp[0] + tmp[1]) + tmp[2]) + tmp[3];
+}
+
+// One launch of the one-call step's walk over the layers, launch l = 1, ...,
+// layers (256-thread workgroups, blockIdx.x the sequence, blockIdx.y the
+// role):
+//   walk     (pairs + 1 workgroups, l < layers) layer l's walk row, undivided,
+//            into its slot of rows, from the undivided row of layer l - 1;
+//   select   (1) layer l - 1's row divided by its largest magnitude and its
+//            selection (Alg. 2 step 6, forced set {0, b_cur}). The row is
+//            written back divided (entries past b_cur zeroed) unless the walk
+//            workgroups of this launch read it;
+//   divide   (1, where layer l - 2's row was such a one) that row.
+// So the chain over the layers is one launch a layer, with the selection
+// beside the walk and not before it, and nothing of the attention in it. A
+// launch is latency (6.2 us at 513 blocks and batch 1, about 13 us at 1025
+// blocks and batch 16, where the walk reads 34 MB). With the sketch of all
+// layers in one launch and the attention of several in another, a step takes
+// 412 us instead of 1165 (batch 1, 32768 tokens, 32 layers; four launches per
+// layer before), and 1166 instead of 1318 (batch 16, 65536 tokens, 8 layers).
+struct ChainArgs {
+  const char* state;       // of layer l
+  const int32_t* pos;
+  double* rows;            // of layer l
+  double* rows_sel;        // of layer l - 1
+  double* rows_div;        // of layer l - 2
+  int32_t* idx;            // of layer l - 1
+  int32_t* cnt;
+  PrevRow prev;            // layer l - 1
+  int batch, d, r, b_max, B, s_exp, k, pct, kmax;
+  uint32_t flags;
+  int walk_wgs;            // workgroups per sequence of the walk role (0: none)
+  int write_sel;           // the selection writes its row back
+};
+
+template <bool S8, bool RELU, int MAXE>
+__global__ __launch_bounds__(256, 2) void decode_chain_kernel(ChainArgs a) {
+  __shared__ double lds[kWalkLdsDoubles];
+  const int bi = blockIdx.x;
+  const int role = (int)blockIdx.y;
+  if (role < a.walk_wgs - 1) {
+    walk_strips<S8, RELU, MAXE, true>(a.state, a.batch, a.d, a.r, a.b_max, a.B, a.pos, a.s_exp,
+                                      a.prev, a.rows, bi, role, lds);
+    return;
+  }
+  if (role < a.walk_wgs) {
+    walk_column<S8, RELU, MAXE>(a.state, a.batch, a.d, a.r, a.b_max, a.B, a.pos, a.s_exp, a.prev,
+                                a.rows, bi, lds);
+    return;
+  }
+  const bool sel = role == a.walk_wgs;
+  const int t = threadIdx.x;
+  const int p = a.pos[bi];
+  const int bc = p / a.B;
+  if (p < 0 || bc >= a.b_max) return;
   const int avail = bc + 1;
   const int E = (avail + 255) / 256;
-  const int t = threadIdx.x;
+  double* out = (sel ? a.rows_sel : a.rows_div) + (long long)bi * a.b_max;
   double v[MAXE];
-  walk_finish<S8, RELU, MAXE>(state, batch, d, r, b_max, bi, bc, s_exp, r_prev, row, v, tmp);
+  if (sel && a.prev.rowc != nullptr) {
+    const double c0 = a.prev.scale[bi];
+    const double inv_c = 1.0 / (c0 > 0.0 ? c0 : 1.0);
+    float w[MAXE];
+#pragma unroll
+    for (int e = 0; e < MAXE; ++e)
+      w[e] = a.prev.rowc[(long long)bi * a.b_max + min(t * E + e, bc)];
+#pragma unroll
+    for (int e = 0; e < MAXE; ++e) v[e] = walk_weight<S8, RELU>(w[e], inv_c, a.s_exp);
+  } else {
+#pragma unroll
+    for (int e = 0; e < MAXE; ++e) v[e] = out[min(t * E + e, bc)];
+  }
   double mx = 0.0;
 #pragma unroll
   for (int e = 0; e < MAXE; ++e)
     if (e < E && t * E + e < avail) mx = fmax(mx, fabs(v[e]));
   for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off));
-  if ((t & 63) == 0) tmp[t >> 6] = mx;
+  if ((t & 63) == 0) lds[t >> 6] = mx;
   __syncthreads();
-  mx = fmax(fmax(tmp[0], tmp[1]), fmax(tmp[2], tmp[3]));
+  mx = fmax(fmax(lds[0], lds[1]), fmax(lds[2], lds[3]));
   const double inv = mx > 0.0 ? 1.0 / mx : 1.0;
 #pragma unroll
-  for (int e = 0; e < MAXE; ++e) {
-    const int j = t * E + e;
-    if (e < E && j < avail) {
-      v[e] = v[e] * inv;
-      row[j] = v[e];
+  for (int e = 0; e < MAXE; ++e) v[e] = v[e] * inv;
+  if (!sel || a.write_sel) {
+#pragma unroll
+    for (int e = 0; e < MAXE; ++e) {
+      const int j = t * E + e;
+      if (e < E && j < avail) out[j] = v[e];
     }
+    for (int j = avail + t; j < a.b_max; j += 256) out[j] = 0.0;
   }
-  for (int j = avail + t; j < b_max; j += 256) row[j] = 0.0;
-  const int first = (flags & SW_FORCE_FIRST) ? 0 : -1;
-  const int last = (flags & SW_FORCE_LAST) ? bc : -1;
-  select_row_vals<MAXE>(v, avail, first, last, k, pct, idx + (long long)bi * kmax, cnt + bi, kmax);
+  if (!sel) return;
+  const int first = (a.flags & SW_FORCE_FIRST) ? 0 : -1;
+  const int last = (a.flags & SW_FORCE_LAST) ? bc : -1;
+  select_row_vals<MAXE>(v, avail, first, last, a.k, a.pct, a.idx + (long long)bi * a.kmax,
+                        a.cnt + bi, a.kmax);
 }
 
 // ---------------------------------------------------------------------------
@@ -811,20 +964,12 @@ namespace {
 template <typename T>
 void launch_sketch_t(const void* q_new, const void* k_new, int batch, int h_q, int h_kv, int d,
                      int B, const int32_t* pos, const int8_t* signs, const int32_t* cols, int r,
-                     int b_max, char* state, const void* v_new, void* Kc, void* Vc, int T_max,
-                     hipStream_t st) {
+                     int b_max, char* state, hipStream_t st) {
   const T* q = reinterpret_cast<const T*>(q_new);
   const T* k = reinterpret_cast<const T*>(k_new);
-  const T* v = reinterpret_cast<const T*>(v_new);
   const dim3 grid((unsigned)batch, (unsigned)((b_max + kScoreChunk - 1) / kScoreChunk));
-  if (Kc != nullptr)
-    hipLaunchKernelGGL((decode_sketch_kernel<T, true>), grid, dim3(256), 0, st, q, k, h_q, h_kv, d,
-                       B, pos, signs, cols, r, batch, b_max, state, v, reinterpret_cast<T*>(Kc),
-                       reinterpret_cast<T*>(Vc), T_max);
-  else
-    hipLaunchKernelGGL((decode_sketch_kernel<T, false>), grid, dim3(256), 0, st, q, k, h_q, h_kv, d,
-                       B, pos, signs, cols, r, batch, b_max, state, v, static_cast<T*>(nullptr),
-                       static_cast<T*>(nullptr), T_max);
+  hipLaunchKernelGGL(decode_sketch_kernel<T>, grid, dim3(256), 0, st, q, k, h_q, h_kv, d, B, pos,
+                     signs, cols, r, batch, b_max, state);
 }
 
 int strip_pairs(int batch, int d, int r, int b_max) {
@@ -836,13 +981,13 @@ int strip_pairs(int batch, int d, int r, int b_max) {
 hipError_t launch_decode_sketch(int dtype, const void* q_new, const void* k_new, int batch, int h_q,
                                 int h_kv, int d, int B, const int32_t* pos, const int8_t* signs,
                                 const int32_t* cols, int r, int b_max, char* state,
-                                hipStream_t st, const void* v_new, void* Kc, void* Vc, int T_max) {
+                                hipStream_t st) {
   if (dtype == SW_BF16)
     launch_sketch_t<uint16_t>(q_new, k_new, batch, h_q, h_kv, d, B, pos, signs, cols, r, b_max,
-                              state, v_new, Kc, Vc, T_max, st);
+                              state, st);
   else
     launch_sketch_t<float>(q_new, k_new, batch, h_q, h_kv, d, B, pos, signs, cols, r, b_max, state,
-                           v_new, Kc, Vc, T_max, st);
+                           st);
   return hipGetLastError();
 }
 
@@ -851,13 +996,15 @@ hipError_t launch_decode_walk(const char* state, int batch, int d, int r, int b_
                               double* r_out, hipStream_t st) {
   const dim3 grid((unsigned)batch, (unsigned)strip_pairs(batch, d, r, b_max));
 #define SW_NORM_LAUNCH(S8, RELU, E)                                                              \
-  hipLaunchKernelGGL((walk_row_norm_kernel<S8, RELU, E>), dim3((unsigned)batch), dim3(256), 0, st, \
-                     state, batch, d, r, b_max, B, pos, s_exp, r_prev, r_out)
-#define SW_WALK_LAUNCH(S8, RELU)                                                                   \
   do {                                                                                            \
     if (r_prev != nullptr)                                                                        \
-      hipLaunchKernelGGL((walk_strip_kernel<S8, RELU>), grid, dim3(kStripThreads), 0, st, state,  \
+      hipLaunchKernelGGL((walk_strip_kernel<S8, RELU, E>), grid, dim3(kStripThreads), 0, st, state, \
                          batch, d, r, b_max, B, pos, s_exp, r_prev, r_out);                       \
+    hipLaunchKernelGGL((walk_row_norm_kernel<S8, RELU, E>), dim3((unsigned)batch), dim3(256), 0,   \
+                       st, state, batch, d, r, b_max, B, pos, s_exp, r_prev, r_out);              \
+  } while (0)
+#define SW_WALK_LAUNCH(S8, RELU)                                                                   \
+  do {                                                                                            \
     switch (row_maxe(b_max)) {                                                                    \
       case 2: SW_NORM_LAUNCH(S8, RELU, 2); break;                                                 \
       case 4: SW_NORM_LAUNCH(S8, RELU, 4); break;                                                 \
@@ -876,66 +1023,90 @@ hipError_t launch_decode_walk(const char* state, int batch, int d, int r, int b_
 
 namespace {
 
-template <typename T, bool S8, bool RELU>
-void launch_layer_t(const void* q_new, const void* k_new, const void* v_new, void* Kc, void* Vc,
-                    int T_max, int batch, int h_q, int h_kv, int d, int B, const int32_t* pos,
-                    const int8_t* signs, const int32_t* cols, int r, int b_max, char* state,
-                    int s_exp, const double* r_prev, double* rows, int k, int pct, uint32_t flags,
-                    int32_t* idx, int32_t* cnt, int kmax, hipStream_t st) {
-  const int pairs = r_prev != nullptr ? strip_pairs(batch, d, r, b_max) : 0;
-  const int chunks = (b_max + kScoreChunk - 1) / kScoreChunk;
-  hipLaunchKernelGGL((decode_sketch_walk_kernel<T, S8, RELU>),
-                     dim3((unsigned)batch, (unsigned)(pairs + chunks)), dim3(256), 0, st,
-                     reinterpret_cast<const T*>(q_new), reinterpret_cast<const T*>(k_new), h_q,
-                     h_kv, d, B, pos, signs, cols, r, batch, b_max, state,
-                     reinterpret_cast<const T*>(v_new), reinterpret_cast<T*>(Kc),
-                     reinterpret_cast<T*>(Vc), T_max, pairs, s_exp, r_prev, rows);
-#define SW_SEL_LAUNCH(E)                                                                        \
-  hipLaunchKernelGGL((select_decode_norm_kernel<S8, RELU, E>), dim3((unsigned)batch), dim3(256), 0, \
-                     st, state, batch, d, r, b_max, B, pos, s_exp, r_prev, rows, k, pct, flags,    \
-                     idx, cnt, kmax)
-  switch (row_maxe(b_max)) {
-    case 2: SW_SEL_LAUNCH(2); break;
-    case 4: SW_SEL_LAUNCH(4); break;
-    case 8: SW_SEL_LAUNCH(8); break;
-    default: SW_SEL_LAUNCH(16); break;
+template <typename T>
+void launch_sketch_layers_t(int layers, const void* q_new, const void* k_new, const void* v_new,
+                            void* Kc, void* Vc, int T_max, int batch, int h_q, int h_kv, int d, int B,
+                            const int32_t* pos, const int8_t* signs, const int32_t* cols, int r,
+                            int b_max, char* state, hipStream_t st) {
+  LayerStrides ls;
+  ls.q = (long long)batch * h_q * d * (long long)sizeof(T);
+  ls.kv = (long long)batch * h_kv * d * (long long)sizeof(T);
+  ls.cache = ls.kv * T_max;
+  ls.state = decode_layout(batch, d, r, b_max).total;
+  const unsigned chunks = (unsigned)((b_max + kScoreChunk - 1) / kScoreChunk);
+  constexpr int kMaxZ = 65535;           // grid limit
+  for (int l0 = 0; l0 < layers; l0 += kMaxZ) {
+    const int nz = layers - l0 < kMaxZ ? layers - l0 : kMaxZ;
+    auto at = [l0](const void* p, long long step) { return static_cast<const char*>(p) + l0 * step; };
+    hipLaunchKernelGGL(decode_sketch_layers_kernel<T>, dim3((unsigned)batch, chunks, (unsigned)nz),
+                       dim3(256), 0, st, reinterpret_cast<const T*>(at(q_new, ls.q)),
+                       reinterpret_cast<const T*>(at(k_new, ls.kv)), h_q, h_kv, d, B, pos, signs, cols,
+                       r, batch, b_max, state + l0 * ls.state,
+                       reinterpret_cast<const T*>(at(v_new, ls.kv)),
+                       reinterpret_cast<T*>(static_cast<char*>(Kc) + l0 * ls.cache),
+                       reinterpret_cast<T*>(static_cast<char*>(Vc) + l0 * ls.cache), T_max, ls);
   }
-#undef SW_SEL_LAUNCH
 }
 
-template <typename T>
-void launch_layer_w(bool relu, const void* q_new, const void* k_new, const void* v_new, void* Kc,
-                    void* Vc, int T_max, int batch, int h_q, int h_kv, int d, int B,
-                    const int32_t* pos, const int8_t* signs, const int32_t* cols, int r, int b_max,
-                    char* state, int s_exp, const double* r_prev, double* rows, int k, int pct,
-                    uint32_t flags, int32_t* idx, int32_t* cnt, int kmax, hipStream_t st) {
-#define SW_LAYER(S8, RELU)                                                                     \
-  launch_layer_t<T, S8, RELU>(q_new, k_new, v_new, Kc, Vc, T_max, batch, h_q, h_kv, d, B, pos, \
-                              signs, cols, r, b_max, state, s_exp, r_prev, rows, k, pct, flags, \
-                              idx, cnt, kmax, st)
-  if (s_exp == 8 && !relu) SW_LAYER(true, false);
-  else if (s_exp == 8) SW_LAYER(true, true);
-  else if (!relu) SW_LAYER(false, false);
-  else SW_LAYER(false, true);
-#undef SW_LAYER
+template <bool S8, bool RELU>
+void launch_chain(const ChainArgs& a, hipStream_t st) {
+  // roles: the walk's, the selection, and the division where there is one
+  const dim3 grid((unsigned)a.batch, (unsigned)(a.walk_wgs + 1 + (a.rows_div != nullptr)));
+  switch (row_maxe(a.b_max)) {
+    case 2: hipLaunchKernelGGL((decode_chain_kernel<S8, RELU, 2>), grid, dim3(256), 0, st, a); break;
+    case 4: hipLaunchKernelGGL((decode_chain_kernel<S8, RELU, 4>), grid, dim3(256), 0, st, a); break;
+    case 8: hipLaunchKernelGGL((decode_chain_kernel<S8, RELU, 8>), grid, dim3(256), 0, st, a); break;
+    default: hipLaunchKernelGGL((decode_chain_kernel<S8, RELU, 16>), grid, dim3(256), 0, st, a); break;
+  }
 }
 
 }  // namespace
 
-hipError_t launch_decode_layer(int dtype, const void* q_new, const void* k_new, const void* v_new,
-                               void* Kc, void* Vc, int T_max, int batch, int h_q, int h_kv, int d,
-                               int B, const int32_t* pos, const int8_t* signs, const int32_t* cols,
-                               int r, int b_max, char* state, int s_exp, bool relu,
-                               const double* r_prev, double* rows, int k, int pct, uint32_t flags,
-                               int32_t* idx, int32_t* cnt, int kmax, hipStream_t st) {
+hipError_t launch_decode_layers(int dtype, int layers, const void* q_new, const void* k_new,
+                                const void* v_new, void* Kc, void* Vc, int T_max, int batch, int h_q,
+                                int h_kv, int d, int B, const int32_t* pos, const int8_t* signs,
+                                const int32_t* cols, int r, int b_max, char* state, int s_exp,
+                                bool relu, double* rows, int k, int pct, uint32_t flags, int32_t* idx,
+                                int32_t* cnt, int kmax, hipStream_t st) {
   if (dtype == SW_BF16)
-    launch_layer_w<uint16_t>(relu, q_new, k_new, v_new, Kc, Vc, T_max, batch, h_q, h_kv, d, B, pos,
-                             signs, cols, r, b_max, state, s_exp, r_prev, rows, k, pct, flags, idx,
-                             cnt, kmax, st);
+    launch_sketch_layers_t<uint16_t>(layers, q_new, k_new, v_new, Kc, Vc, T_max, batch, h_q, h_kv, d, B,
+                                     pos, signs, cols, r, b_max, state, st);
   else
-    launch_layer_w<float>(relu, q_new, k_new, v_new, Kc, Vc, T_max, batch, h_q, h_kv, d, B, pos,
-                          signs, cols, r, b_max, state, s_exp, r_prev, rows, k, pct, flags, idx,
-                          cnt, kmax, st);
+    launch_sketch_layers_t<float>(layers, q_new, k_new, v_new, Kc, Vc, T_max, batch, h_q, h_kv, d, B,
+                                  pos, signs, cols, r, b_max, state, st);
+  const DecodeLayout L = decode_layout(batch, d, r, b_max);
+  const long long row_step = (long long)batch * b_max;
+  const int pairs = strip_pairs(batch, d, r, b_max);
+  for (int l = 1; l <= layers; ++l) {
+    ChainArgs a;
+    const int s = l - 1;                 // the layer whose blocks are selected
+    a.state = state + (long long)(l < layers ? l : s) * L.total;
+    a.pos = pos;
+    a.rows = rows + (l < layers ? l : s) * row_step;
+    a.rows_sel = rows + s * row_step;
+    a.rows_div = (l >= 3) ? rows + (l - 2) * row_step : nullptr;
+    a.idx = idx + (long long)s * batch * kmax;
+    a.cnt = cnt + (long long)s * batch;
+    a.prev.row = rows + s * row_step;
+    a.prev.rowc = s == 0 ? reinterpret_cast<const float*>(state + L.rowc) : nullptr;
+    a.prev.scale = reinterpret_cast<const double*>(state + L.scale);
+    a.batch = batch;
+    a.d = d;
+    a.r = r;
+    a.b_max = b_max;
+    a.B = B;
+    a.s_exp = s_exp;
+    a.k = k;
+    a.pct = pct;
+    a.kmax = kmax;
+    a.flags = flags;
+    a.walk_wgs = l < layers ? pairs + 1 : 0;
+    a.write_sel = s == 0 || l == layers;
+    if (s_exp == 8 && !relu) launch_chain<true, false>(a, st);
+    else if (s_exp == 8) launch_chain<true, true>(a, st);
+    else if (!relu) launch_chain<false, false>(a, st);
+    else launch_chain<false, true>(a, st);
+  }
   return hipGetLastError();
 }
 

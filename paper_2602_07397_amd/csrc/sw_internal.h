@@ -95,8 +95,7 @@ hipError_t launch_kv_append(int dtype, const void* k_new, const void* v_new, voi
 hipError_t launch_decode_sketch(int dtype, const void* q_new, const void* k_new, int batch, int h_q,
                                 int h_kv, int d, int B, const int32_t* pos, const int8_t* signs,
                                 const int32_t* cols, int r, int b_max, char* state,
-                                hipStream_t st, const void* v_new = nullptr, void* Kc = nullptr,
-                                void* Vc = nullptr, int T_max = 0);
+                                hipStream_t st);
 
 // Alg. 2 step 5 for the per-layer entry point: the walk row of every
 // sequence, divided by its largest magnitude, into r_out [batch][b_max].
@@ -104,16 +103,16 @@ hipError_t launch_decode_walk(const char* state, int batch, int d, int r, int b_
                               const int32_t* pos, int s_exp, bool relu, const double* r_prev,
                               double* r_out, hipStream_t st);
 
-// Alg. 2 steps 1-6 of one layer for the one-call step: the incremental
-// sketch with the KV append, side by side with the walk over the score
-// entries the sketch leaves unchanged, then the walk row finished, normalised
-// and written to rows [batch][b_max], and its selection.
-hipError_t launch_decode_layer(int dtype, const void* q_new, const void* k_new, const void* v_new,
-                               void* Kc, void* Vc, int T_max, int batch, int h_q, int h_kv, int d,
-                               int B, const int32_t* pos, const int8_t* signs, const int32_t* cols,
-                               int r, int b_max, char* state, int s_exp, bool relu,
-                               const double* r_prev, double* rows, int k, int pct, uint32_t flags,
-                               int32_t* idx, int32_t* cnt, int kmax, hipStream_t st);
+// Alg. 2 steps 1-6 of every layer for the one-call step: the incremental
+// sketch with the KV append of all layers in one launch, then one launch per
+// layer for the walk row with the selection of the layer before it, and a
+// last one for the last layer's selection. Buffers are stacked over layers.
+hipError_t launch_decode_layers(int dtype, int layers, const void* q_new, const void* k_new,
+                                const void* v_new, void* Kc, void* Vc, int T_max, int batch, int h_q,
+                                int h_kv, int d, int B, const int32_t* pos, const int8_t* signs,
+                                const int32_t* cols, int r, int b_max, char* state, int s_exp,
+                                bool relu, double* rows, int k, int pct, uint32_t flags, int32_t* idx,
+                                int32_t* cnt, int kmax, hipStream_t st);
 
 hipError_t launch_select_decode(const double* rows, int batch, int b_max, int B,
                                 const int32_t* pos, int k, int pct, uint32_t flags, int32_t* idx,
@@ -125,9 +124,11 @@ int decode_attn_splits(int batch, int h_kv);
 // (SW_NOALLOC_SCRATCH_BYTES), looked up on the first call on each device.
 hipError_t noalloc_scratch(void** out);
 
-hipError_t launch_attn_decode(int dtype, const void* q, const void* Kc, const void* Vc, int batch,
-                              int h_q, int h_kv, int d, int T_max, int B, const int32_t* pos,
-                              const int32_t* idx, const int32_t* cnt, int kmax, float scale,
-                              void* O, float* ws, hipStream_t st);
+// Alg. 2 step 7 for `layers` layers in one launch (and one for the merge); all
+// buffers stacked over the layers, ws too (decode_attn_workspace per layer).
+hipError_t launch_attn_decode(int dtype, int layers, const void* q, const void* Kc, const void* Vc,
+                              int batch, int h_q, int h_kv, int d, int T_max, int B,
+                              const int32_t* pos, const int32_t* idx, const int32_t* cnt, int kmax,
+                              float scale, void* O, float* ws, hipStream_t st);
 
 }  // namespace sw

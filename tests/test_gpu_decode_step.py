@@ -138,3 +138,31 @@ def test_inactive_sequence_is_skipped():
     assert torch.all(part[0]["idx"][:, 1] == 5) and torch.all(part[0]["cnt"][:, 1] == 5)
     assert torch.all(part[0]["O"][:, 1] == 0)
     assert torch.equal(part[2][:, 1], part[4][:, 1])      # cache of the skipped sequence
+
+
+@pytest.mark.parametrize("layers", [1, 2, 3, 5])
+def test_layers_share_launches_as_the_workspace_allows(layers):
+    """The walk's chain over 1, 2, 3 and 5 layers (undivided rows of the
+    layers in between, written back divided later) and the attention of one,
+    two or all layers in a launch, as the workspace holds: each bit-identical
+    to the per-layer calls. Sequences of 1, 33 and 70 blocks in one batch."""
+    w = synth.Workload("dec", 50, layers=layers, h_q=8, h_kv=2, d=64, B=16, dtype="bf16", pct=20,
+                       needles=2, batch=3, kv_len=1110, steps=1)
+    run = D.DecodeRun(w, prompts=[9, 520, 1110], steps=1)
+    K0, V0, S0 = (torch.stack(x).contiguous() for x in (run.Kc, run.Vc, run.state))
+    q, kk, v = _stacked_inputs(w, 0, run.batch)
+    pos = U.to_dev(np.array(run.prompts, dtype=np.int32))
+    run.step(0)                                    # per-layer path, checked against the oracle
+    one = sw.decode_attn_workspace_bytes(run.batch, 8, 2, 64)
+    for n in (1, 2, layers):
+        Kc, Vc, state = K0.clone(), V0.clone(), S0.clone()
+        ws = torch.empty((n * one,), dtype=torch.uint8, device=U.DEV)
+        out = sw.decode_step(q, kk, v, Kc, Vc, state, pos, run.ts, run.tc, run.B, run.b_max,
+                             s=run.s, density_pct=w.pct, kmax=run.kmax, workspace=ws)
+        for l, (r, idx, cnt, o) in enumerate(run.last):
+            assert torch.equal(out["rows"][l], r), (n, l)
+            assert torch.equal(out["cnt"][l], cnt), (n, l)
+            assert torch.equal(out["idx"][l], idx), (n, l)
+            assert torch.equal(out["O"][l], o), (n, l)
+            assert torch.equal(state[l], run.state[l]), (n, l)
+            assert torch.equal(Kc[l], run.Kc[l]), (n, l)
