@@ -3,9 +3,11 @@
 // the tokens of the selected blocks that precede each query, renormalised
 // over those keys only.
 //
-// bf16 kernel. Work item = (query block, KV head g, slice of the group's query
-// heads). A 512-thread workgroup has 8 wavefronts, two per SIMD; each owns 32
-// query rows of one head (a B = 128 block takes four wavefronts per head, a
+// bf16 kernels: one of eight wavefronts per workgroup, described here, and one
+// of four for head dimension 64 and for head counts that leave the eight
+// without rows (further down). Work item = (query block, KV head g, slice of
+// the group's query heads). A 512-thread workgroup has 8 wavefronts, two per
+// SIMD; each owns 32 query rows of one head (a B = 128 block takes four wavefronts per head, a
 // B = 64 block two), so a workgroup serves two (B = 128) or four (B = 64)
 // query heads of the same KV group from one copy of each K/V tile in LDS.
 // The two wavefronts of a SIMD cover each other's LDS and barrier waits.
@@ -545,6 +547,436 @@ __global__ __launch_bounds__(kPfWaves * 64, 1) void attn_prefill_bf16_kernel(
     lse[(long long)u * N + qpos] = (ltot > 0.0f) ? (mref + log2f(ltot)) / kLog2e : -INFINITY;
 }
 
+// ---------------------------------------------------------------------------
+// bf16 kernel, four wavefronts
+// ---------------------------------------------------------------------------
+
+// The pipeline of the eight-wavefront kernel for workgroups of four
+// wavefronts, two or three to a CU: one workgroup's list, first tiles and
+// output run beside another's math. A step is 32 keys per wavefront: the
+// scores of step t + 1 and the P.V of step t, so K is staged one step ahead of
+// V and two slots of each suffice, with one barrier a step.
+// KH = 2 (one query head per KV head, blocks of 64): a block has 32-row groups
+// for two wavefronts, so wavefronts 2r and 2r + 1 take the two 32-key halves of
+// each 64-key step for row group r and join their sums at the end.
+// Bounded by the matrix cores and the softmax beside them as the other kernel;
+// each K/V tile serves 128 query rows (64 with KH = 2) and not 256, so its
+// staging weighs more. The steps at the end (a wavefront goes on, masks, ends
+// or skips) run one at a time with the state copied over: unrolled by two like
+// the main loop they took 282 VGPRs at D = 128 and spilled.
+template <int D, int KH>
+struct W4Lds {
+  static constexpr int KT4 = 32 * KH;      // keys per step, 32 per wavefront
+  static constexpr int KS = BfLds<D>::KS;
+  static constexpr int VS = BfLds<D>::VS;
+  static constexpr int K_ELEMS = KT4 * KS;
+  static constexpr int V_ELEMS = KT4 * VS;
+  static constexpr int SLOTS = 2 * (K_ELEMS + V_ELEMS);   // two K slots, two V slots
+  // selected blocks a row can hold: two workgroups share a CU's 160 KB
+  static constexpr int LIST = (80 * 1024 - 2 * SLOTS - 64) / 2 < SW_MAX_BLOCKS
+                                  ? (80 * 1024 - 2 * SLOTS - 64) / 2
+                                  : SW_MAX_BLOCKS;
+};
+
+template <int D, int BLK, int KH>
+__global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
+    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+    const uint16_t* __restrict__ V, int h_q, int h_kv, long long N, SeqMeta m,
+    const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int kmax, float sl2,
+    uint16_t* __restrict__ O, float* __restrict__ lse, int groups, int sg) {
+  using L = W4Lds<D, KH>;
+  constexpr int NT = 256;
+  constexpr int NW = 4;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[L::SLOTS];
+  __shared__ int16_t blist[L::LIST];
+  __shared__ int wtot[NW];
+
+  // ---- work item ----
+  const int x = blockIdx.x;
+  const int xcd = x & 7;
+  const int slot = x >> 3;
+  const int mu = slot % sg;
+  const int gamma = (slot / sg) * 8 + xcd;
+  if (gamma >= groups) return;
+  const int rho = gamma / h_kv;
+  const int g = gamma % h_kv;
+  int row, s, i;
+  lpt_row(m, rho, &row, &s, &i);
+  constexpr int WPB = BLK / 32;            // 32-row groups per (query head, block)
+  constexpr int TPB = BLK / L::KT4;        // steps per block
+  static_assert(KH == 1 || (KH == 2 && BLK == 64), "key halves: a block is one step");
+  const int G = h_q / h_kv;
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l = tid & 63;
+  const int hl = l >> 5;                   // half-wave
+  const int ln = l & 31;                   // lane within half
+  const int kh = (KH == 2) ? w & 1 : 0;    // this wavefront's 32 keys of a step
+  const int task = mu * (NW / KH) + w / KH;
+  const int u = g * G + task / WPB;        // query head (meaningful only when active)
+  const int seq0 = m.tok_start[s];
+  const int seq1 = m.tok_start[s + 1];
+  const int rgrp = task % WPB;
+  const int q0 = seq0 + i * BLK + rgrp * 32;   // first query row of this wavefront
+  const bool active = (task < G * WPB) && (q0 < seq1);
+  const int qpos = q0 + ln;                // this lane's query row
+
+  const int32_t* sel = idx + (long long)row * kmax;
+  const int nsel = min(cnt[row], kmax);
+  int jnext = (tid < kmax) ? sel[tid] : -1;
+
+  // ---- Q fragments: lane holds query qpos, dims kk*16 + hl*8 .. +7 ----
+  bf16x8 qf[D / 16];
+  {
+    const bool ok = active && qpos < seq1;
+    const uint16_t* qrow = Q + ((long long)(ok ? u : 0) * N + (ok ? qpos : 0)) * D;
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) {
+      uint4 v = ok ? *reinterpret_cast<const uint4*>(qrow + kk * 16 + hl * 8) : make_uint4(0, 0, 0, 0);
+      qf[kk] = __builtin_bit_cast(bf16x8, v);
+    }
+  }
+
+  // ---- selected blocks, compacted: valid j < i in list order, then i ----
+  int n_off = 0, sdiag = 0;
+  for (int base = 0; base < nsel; base += NT) {
+    const int e = base + tid;
+    const int j = (e < nsel) ? jnext : -1;
+    jnext = (e + NT < nsel) ? sel[e + NT] : -1;
+    const bool off = (j >= 0 && j < i);
+    const unsigned long long bal = __ballot(off);
+    const bool dg = __ballot(j == i) != 0ull;
+    const int pre = __popcll(bal & ((1ull << l) - 1ull));
+    if (l == 0) wtot[w] = __popcll(bal) | (dg ? 0x10000 : 0);
+    __syncthreads();
+    int woff = 0, tot = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const int c = wtot[q];
+      woff += (q < w) ? (c & 0xffff) : 0;
+      tot += c & 0xffff;
+      sdiag |= c >> 16;
+    }
+    if (off && n_off + woff + pre < L::LIST) blist[n_off + woff + pre] = (int16_t)j;
+    n_off = min(n_off + tot, L::LIST);
+    __syncthreads();
+  }
+  const int n_blk = n_off + sdiag;
+  const int nsteps = n_blk * TPB;
+  const int noffs = n_off * TPB;           // steps before the diagonal block
+
+  // ---- K/V staging: global -> registers -> LDS, 16-byte chunks ----
+  constexpr int KCH = D / 8;               // chunks per key row
+  constexpr int KP = (L::KT4 * KCH) / NT;  // chunks per thread for K (and for V)
+  static_assert(KP >= 1 && KP * NT == L::KT4 * KCH && NT % KCH == 0, "step chunks must divide over the workgroup");
+  constexpr int RPP = NT / KCH;            // key rows per chunk pass
+  const int sr = tid / KCH, sc = tid % KCH;
+  const int goff = (sr * D + sc * 8) * 2;
+  const int kloff = sr * L::KS + sc * 8;
+  const int vloff = sr * L::VS + sc * 8;
+  uint16_t* const kslots = lds;
+  uint16_t* const vslots = lds + 2 * L::K_ELEMS;
+  const uint16_t* Kg = K + (long long)g * N * D;
+  const uint16_t* Vg = V + (long long)g * N * D;
+  // first key of step t (wave-uniform)
+  auto step_k0 = [&](int t) SW_INL {
+    const int jj = t / TPB;
+    const int j = (jj < n_off) ? __builtin_amdgcn_readfirstlane((int)blist[jj]) : i;
+    return seq0 + j * BLK + (t % TPB) * L::KT4;
+  };
+  // keys past the end of the sequence read as zero (the mask removes them)
+  auto load = [&](const uint16_t* base, int k0, uint4 (&r)[KP]) SW_INL {
+    const int bytes = max(0, (seq1 - k0) * D * 2);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(base + (long long)k0 * D), (short)0, bytes, kBufWord3);
+#pragma unroll
+    for (int p = 0; p < KP; ++p)
+      r[p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, goff + p * RPP * D * 2, 0, 0));
+  };
+  auto store_k = [&](int sl, const uint4 (&r)[KP]) SW_INL {
+#pragma unroll
+    for (int p = 0; p < KP; ++p)
+      *reinterpret_cast<uint4*>(kslots + sl * L::K_ELEMS + kloff + p * RPP * L::KS) = r[p];
+  };
+  auto store_v = [&](int sl, const uint4 (&r)[KP]) SW_INL {
+#pragma unroll
+    for (int p = 0; p < KP; ++p)
+      *reinterpret_cast<uint4*>(vslots + sl * L::V_ELEMS + vloff + p * RPP * L::VS) = r[p];
+  };
+
+  // ---- running state ----
+  f32x16 oacc[D / 32];
+#pragma unroll
+  for (int td = 0; td < D / 32; ++td)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) oacc[td][j] = 0.0f;
+  float mref = kNoRef;
+  float lsum = 0.0f;
+  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+  constexpr int NKK = D / 16;              // score MFMAs per sub-tile
+  constexpr int NPV = 2 * (D / 32);        // P.V MFMAs per sub-tile: (chunk, dim block)
+  constexpr int QK_PER_PAIR = NKK / 4;     // score MFMAs per element pair (phase A)
+  constexpr int PV_PER_PAIR = NPV / 4;     // P.V MFMAs per element pair (phase B)
+  constexpr int kAhead = 3;                // K and V^T operands are read this many MFMAs ahead
+  // V^T operand lane offset (see the eight-wavefront kernel)
+  const int vlane = (kh * 32 + 4 * hl + ((ln & 15) >> 2)) * L::VS + 16 * (ln >> 4) + 4 * (ln & 3);
+  const int klane = (kh * 32 + ln) * L::KS + hl * 8;
+
+  // causal + sequence-end mask of the diagonal sub-tile (raw scores)
+  auto mask_sub = [&](int t, f32x16& S) SW_INL {
+    const int k0 = step_k0(t) + kh * 32;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int kp = k0 + (j >> 2) * 8 + hl * 4 + (j & 3);
+      if (kp > qpos || kp >= seq1) S[j] = -INFINITY;
+    }
+  };
+  auto row_max = [&](const f32x16& S) SW_INL {
+    float a = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) a = fmaxf(a, S[j]);
+    return max_other_half(a) * sl2;
+  };
+  auto rescale_to = [&](float nref) SW_INL {
+    const float alpha = __builtin_amdgcn_exp2f(mref - nref);
+    mref = nref;
+    lsum *= alpha;
+#pragma unroll
+    for (int td = 0; td < D / 32; ++td)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) oacc[td][j] *= alpha;
+  };
+  auto pair = [&](const f32x16& S, int e, uint32_t& word, float& ts) SW_INL {
+    const float nr = -mref;
+    const float p0 = __builtin_amdgcn_exp2f(fmaf(S[2 * e], sl2, nr));
+    const float p1 = __builtin_amdgcn_exp2f(fmaf(S[2 * e + 1], sl2, nr));
+    word = pack_bf16x2(p0, p1);
+    ts = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, word), ones, ts, false);
+  };
+  auto vread = [&](const uint16_t* vr, int n) SW_INL {
+    const uint16_t* pp = vr + (n / (D / 32)) * 16 * L::VS + (n % (D / 32)) * 32;
+    const i16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) i16x4*)(pp));
+    const i16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) i16x4*)(pp + 8 * L::VS));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  // rare path: exact row max of S, new reference, rescale, recompute P
+  auto check = [&](const f32x16& S, uint32_t (&w0)[4], uint32_t (&w1)[4], float& ts) SW_INL {
+    if (__any(ts > kSumLimit)) {
+      rescale_to(fmaxf(mref, row_max(S)));
+      ts = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pair(S, e, w0[e], ts);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pair(S, 4 + e, w1[e], ts);
+    }
+    lsum += ts;
+  };
+  auto phase_b = [&](const uint16_t* vr, const uint32_t (&w0)[4], const uint32_t (&w1)[4],
+                     bf16x8 (&vf)[NPV], const f32x16& nxt, uint32_t (&wn)[4], float& tn,
+                     auto has_next) SW_INL {
+    constexpr bool HAS_NEXT = decltype(has_next)::value;
+    const bf16x8 pb[2] = {__builtin_bit_cast(bf16x8, w0), __builtin_bit_cast(bf16x8, w1)};
+    tn = 0.0f;
+#pragma unroll
+    for (int n = 0; n < NPV; ++n) {
+      if (n + kAhead < NPV) vf[n + kAhead] = vread(vr, n + kAhead);
+      oacc[n % (D / 32)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[n], pb[n / (D / 32)],
+                                                                   oacc[n % (D / 32)], 0, 0, 0);
+      if (HAS_NEXT && (n % PV_PER_PAIR) == PV_PER_PAIR - 1) {
+        const int e = n / PV_PER_PAIR;               // 0..3
+        pair(nxt, e, wn[e], tn);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // one step: cur = S(t) with chunk-0 words wc and partial sum tc; produces
+  // nxt = S(t+1) (masked when tmask >= 0), its chunk-0 words and partial sum
+  auto sub = [&](f32x16& cur, uint32_t (&wc)[4], float& tc, f32x16& nxt, uint32_t (&wn)[4],
+                 float& tn, int ksl, int vsl, int tmask) SW_INL {
+    const uint16_t* kr = kslots + ksl * L::K_ELEMS + klane;
+    const uint16_t* vr = vslots + vsl * L::V_ELEMS + vlane;
+    uint32_t w1[4];
+    bf16x8 kf[NKK];
+    bf16x8 vf[NPV];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) kf[q] = *reinterpret_cast<const bf16x8*>(kr + q * 16);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) nxt[j] = 0.0f;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      if (kk + kAhead < NKK) kf[kk + kAhead] = *reinterpret_cast<const bf16x8*>(kr + (kk + kAhead) * 16);
+      if (kk >= NKK - kAhead) vf[kk - (NKK - kAhead)] = vread(vr, kk - (NKK - kAhead));
+      nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk], qf[kk], nxt, 0, 0, 0);
+      if ((kk % QK_PER_PAIR) == QK_PER_PAIR - 1) {
+        const int e = kk / QK_PER_PAIR;              // 0..3
+        pair(cur, 4 + e, w1[e], tc);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (tmask >= 0) mask_sub(tmask, nxt);
+    check(cur, wc, w1, tc);
+    phase_b(vr, wc, w1, vf, nxt, wn, tn, std::true_type{});
+  };
+  auto sub_last = [&](f32x16& cur, uint32_t (&wc)[4], float& tc, int vsl) SW_INL {
+    const uint16_t* vr = vslots + vsl * L::V_ELEMS + vlane;
+    uint32_t w1[4];
+    bf16x8 vf[NPV];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) vf[q] = vread(vr, q);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) pair(cur, 4 + e, w1[e], tc);
+    check(cur, wc, w1, tc);
+    uint32_t wdummy[4];
+    float tdummy;
+    phase_b(vr, wc, w1, vf, cur, wdummy, tdummy, std::false_type{});
+  };
+
+  // Last step of this wavefront's run: the steps of the off-diagonal blocks,
+  // then in the diagonal block those up to the sub-tile its rows cross, the
+  // masked one (later ones lie after all its rows).
+  const bool dmine = active && sdiag;
+  const int tend = (KH == 1) ? noffs - 1 + (dmine ? rgrp + 1 : 0)
+                             : noffs - 1 + ((dmine && kh <= rgrp) ? 1 : 0);
+  const int tmasked = (dmine && (KH == 1 || kh == rgrp)) ? tend : -1;
+  f32x16 sX, sY;
+  uint32_t wX[4], wY[4];
+  float tX = 0.0f, tY = 0.0f;
+  // Step t stores K(t+2) and V(t+1) into the slots whose tiles step t-1 read
+  // last (K runs a step ahead of V, as the scores do), then loads K(t+3) and
+  // V(t+2) into the same registers.
+  uint4 kr[KP], vr[KP];
+  int k0_2 = 0, k0_3 = 0;                  // first keys of steps t+2 and t+3
+  auto io = [&](int t) SW_INL {
+    if (t + 2 < nsteps) store_k(t & 1, kr);
+    if (t + 1 < nsteps) store_v((t + 1) & 1, vr);
+    if (t + 3 < nsteps) load(Kg, k0_3, kr);
+    if (t + 2 < nsteps) load(Vg, k0_2, vr);
+    k0_2 = k0_3;
+    if (t + 4 < nsteps) k0_3 = step_k0(t + 4);
+  };
+  if (nsteps > 0) {
+    {
+      uint4 k1r[KP], v0r[KP];
+      const int a0 = step_k0(0), a1 = nsteps > 1 ? step_k0(1) : 0;
+      if (nsteps > 2) k0_2 = step_k0(2);
+      if (nsteps > 3) k0_3 = step_k0(3);
+      load(Kg, a0, kr);
+      if (nsteps > 1) load(Kg, a1, k1r);
+      load(Vg, a0, v0r);
+      if (nsteps > 1) load(Vg, a1, vr);
+      store_k(0, kr);
+      if (nsteps > 2) load(Kg, k0_2, kr);
+      if (nsteps > 1) store_k(1, k1r);
+      store_v(0, v0r);
+    }
+    __syncthreads();
+    if (tend >= 0) {
+      // scores of the first sub-tile; its chunk-0 words are left to the first
+      // check (an infinite partial sum forces the exact reference)
+      const uint16_t* kr = kslots + klane;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) sX[j] = 0.0f;
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk)
+        sX = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(kr + kk * 16),
+                                                     qf[kk], sX, 0, 0, 0);
+      if (tmasked == 0) mask_sub(0, sX);
+      tX = INFINITY;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wX[e] = 0u;
+    }
+    __syncthreads();
+    // steps t, t+1 with every wavefront's run going past t+2: no masks, no ends
+    int t = 0;
+    for (; t + 2 < noffs; t += 2) {
+      io(t);
+      sub(sX, wX, tX, sY, wY, tY, 1, 0, -1);
+      __syncthreads();
+      io(t + 1);
+      sub(sY, wY, tY, sX, wX, tX, 0, 1, -1);
+      __syncthreads();
+    }
+    // the last steps: each wavefront goes on, ends or skips
+    for (; t < nsteps; ++t) {
+      io(t);
+      if (t < tend) {
+        sub(sX, wX, tX, sY, wY, tY, (t + 1) & 1, t & 1, (t + 1 == tmasked) ? t + 1 : -1);
+        sX = sY;
+        tX = tY;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wX[e] = wY[e];
+      } else if (t == tend) {
+        sub_last(sX, wX, tX, t & 1);
+      }
+      __syncthreads();
+    }
+  }
+
+  // ---- epilogue (the slots are free: every run ended before the last barrier) ----
+  float ltot = sum_other_half(lsum);
+  if constexpr (KH == 2) {
+    // the two key halves of a row group (wavefronts 2r and 2r + 1) are joined
+    // under their common reference, two 32-dim blocks at a time
+    float* pm = reinterpret_cast<float*>(lds);                 // [4][32] references, then sums
+    if (hl == 0) {
+      pm[w * 32 + ln] = mref;
+      pm[128 + w * 32 + ln] = ltot;
+    }
+    float* po = pm + 256 + (w >> 1) * 64 * 16 * (D / 32);      // [D/32][16][64]
+    static_assert((256 + 2 * 64 * 16 * (D / 32)) * 4 <= L::SLOTS * 2, "partials must fit the slots");
+    if (kh == 1) {
+#pragma unroll
+      for (int td = 0; td < D / 32; ++td)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) po[(td * 16 + j) * 64 + l] = oacc[td][j];
+    }
+    __syncthreads();
+    if (kh == 0) {
+      const float m1 = pm[(w + 1) * 32 + ln], l1 = pm[128 + (w + 1) * 32 + ln];
+      // a half without keys has a sum of 0 and the reference kNoRef
+      const float mm = fmaxf(mref, m1);
+      const float f0 = __builtin_amdgcn_exp2f(mref - mm), f1 = __builtin_amdgcn_exp2f(m1 - mm);
+      ltot = ltot * f0 + l1 * f1;
+      mref = mm;
+#pragma unroll
+      for (int td = 0; td < D / 32; ++td)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) oacc[td][j] = oacc[td][j] * f0 + po[(td * 16 + j) * 64 + l] * f1;
+    }
+    __syncthreads();
+  }
+  const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
+  constexpr int OS = D + 8;                // output row stride in LDS (elements)
+  static_assert(NW * 32 * OS <= L::SLOTS, "output staging must fit the slots");
+  if (KH == 2 && kh == 1) return;
+  uint16_t* ob = lds + w * 32 * OS;        // this wavefront's own rows: no barrier
+#pragma unroll
+  for (int td = 0; td < D / 32; ++td) {
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb) {
+      uint2 st;
+      st.x = pack_bf16x2(oacc[td][jb * 4 + 0] * inv, oacc[td][jb * 4 + 1] * inv);
+      st.y = pack_bf16x2(oacc[td][jb * 4 + 2] * inv, oacc[td][jb * 4 + 3] * inv);
+      *reinterpret_cast<uint2*>(ob + ln * OS + td * 32 + jb * 8 + hl * 4) = st;
+    }
+  }
+  if (!active) return;
+  constexpr int CPR = D / 8;               // 16-byte chunks per row
+  constexpr int RPI = 64 / CPR;            // rows per store instruction
+  const int rr = l / CPR, cc = l % CPR;
+  uint16_t* obase = O + ((long long)u * N + q0) * D;
+#pragma unroll
+  for (int it = 0; it < 32 / RPI; ++it) {
+    const int r = it * RPI + rr;
+    const uint4 v = *reinterpret_cast<const uint4*>(ob + r * OS + cc * 8);
+    if (q0 + r < seq1) *reinterpret_cast<uint4*>(obase + (long long)r * D + cc * 8) = v;
+  }
+  if (lse && hl == 0 && qpos < seq1)
+    lse[(long long)u * N + qpos] = (ltot > 0.0f) ? (mref + log2f(ltot)) / kLog2e : -INFINITY;
+}
+
 #undef SW_INL
 
 // ---------------------------------------------------------------------------
@@ -708,20 +1140,47 @@ hipError_t launch_attn_prefill(int dtype, const void* Q, const void* K, const vo
   const int groups = (int)(nb * h_kv);
   const float sl2 = scale * kLog2e;
   if (dtype == SW_BF16) {
-    // 32 query rows per wavefront, kPfWaves wavefronts per workgroup
-    const int sg = (G * (meta.B / 32) + kPfWaves - 1) / kPfWaves;
-    const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg);
+    // 32 query rows per wavefront
+    const int tasks = G * (meta.B / 32);
+    const int sg = (tasks + kPfWaves - 1) / kPfWaves;
     auto q = reinterpret_cast<const uint16_t*>(Q);
     auto k = reinterpret_cast<const uint16_t*>(K);
     auto v = reinterpret_cast<const uint16_t*>(V);
     auto o = reinterpret_cast<uint16_t*>(O);
-#define SW_LAUNCH_BF16(DD, BB)                                                                  \
-  hipLaunchKernelGGL((attn_prefill_bf16_kernel<DD, BB>), dim3(grid), dim3(kPfWaves * 64), 0, st, q, k, v, h_q, \
-                     h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg)
-    if (d == 128 && meta.B == 128) SW_LAUNCH_BF16(128, 128);
-    else if (d == 128) SW_LAUNCH_BF16(128, 64);
-    else if (meta.B == 128) SW_LAUNCH_BF16(64, 128);
-    else SW_LAUNCH_BF16(64, 64);
+    // Eight wavefronts share each K/V tile among twice the query rows, four
+    // start and finish beside another workgroup. Measured (8000 tokens, 20 %;
+    // eight / four): 32 query heads over 8, d = 128: B = 128 at 32768 tokens
+    // 1641 / 1829 us, B = 64 121 / 126; d = 64: 84 / 79 and 81 / 74. Where the
+    // eight have rows for seven at most, four are as fast (28 heads over 4,
+    // B = 128: 937 / 929); with one query head per KV head (16 over 16) they
+    // win by what the eight leave idle: B = 128 113 / 74, B = 64 194 / 90 and,
+    // d = 64, 146 / 51.
+    const bool four = d == 64 || tasks * 8 < sg * kPfWaves * 7;
+    if (four) {
+      // G = 1 and B = 64 have rows for two wavefronts only: the other two
+      // take the other half of the keys, if the row's blocks fit the list
+      const bool halves = meta.B == 64 && G == 1 && kmax <= W4Lds<128, 2>::LIST;
+      const int sg4 = halves ? 1 : (tasks + 3) / 4;
+      const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg4);
+#define SW_LAUNCH_W4(DD, BB, KK)                                                                  \
+  hipLaunchKernelGGL((attn_prefill_w4_kernel<DD, BB, KK>), dim3(grid), dim3(256), 0, st, q, k, v, \
+                     h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg4)
+      if (halves) {
+        if (d == 128) SW_LAUNCH_W4(128, 64, 2);
+        else SW_LAUNCH_W4(64, 64, 2);
+      } else if (d == 128 && meta.B == 128) SW_LAUNCH_W4(128, 128, 1);
+      else if (d == 128) SW_LAUNCH_W4(128, 64, 1);
+      else if (meta.B == 128) SW_LAUNCH_W4(64, 128, 1);
+      else SW_LAUNCH_W4(64, 64, 1);
+#undef SW_LAUNCH_W4
+      return hipGetLastError();
+    }
+    const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg);
+#define SW_LAUNCH_BF16(BB)                                                                        \
+  hipLaunchKernelGGL((attn_prefill_bf16_kernel<128, BB>), dim3(grid), dim3(kPfWaves * 64), 0, st, q, k, v, \
+                     h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg)
+    if (meta.B == 128) SW_LAUNCH_BF16(128);
+    else SW_LAUNCH_BF16(64);
 #undef SW_LAUNCH_BF16
   } else {
     const int hpw = (meta.B == 64) ? 2 : 1;

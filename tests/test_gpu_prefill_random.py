@@ -122,3 +122,59 @@ def test_rows_selecting_every_block_at_max_blocks():
         for u in range(h_q):
             ref = O.sparse_attention_block(Qh, Kh, Vh, B, sel[i], u, i)
             assert U.max_abs(got[u, i * B:(i + 1) * B], ref) <= U.ATOL_BF16, (i, u)
+
+
+@pytest.mark.parametrize("d,B,G", [(128, 64, 1), (64, 64, 1), (128, 128, 1), (128, 64, 2),
+                                   (128, 64, 3), (128, 128, 3), (64, 64, 2), (64, 128, 3),
+                                   (128, 128, 2), (128, 64, 4)])
+def test_head_counts_and_lengths_of_the_two_bf16_kernels(d, B, G):
+    """Both sides of the head-count rule, rows of 1 to 9 selected blocks (every
+    remainder of the unrolled steps), sequences ending on every 32-row group of
+    a block, and keys that grow along the sequence, so that the exponent
+    reference moves and the two key halves of a row end with different ones.
+    lse against the float64 log-sum-exp: the kernel sums the weights it applies,
+    each rounded to bf16 (8 significant bits, unit roundoff 2^-8), so the sum is
+    within 2^-8 of the exact one (relative; one large weight does not average
+    it out) and its logarithm within -log(1 - 2^-8) < 3.92e-3; the logits
+    (|x| <= 40, fp32 sums of d exact products) and the exponential add less
+    than 4e-5."""
+    rng = np.random.default_rng(700 + d + B + G)
+    seqlens = [B * 9, B * 3 + 1, B + 33, B * 2 + B // 2 + 7, 5]
+    cu = [0] + list(np.cumsum(seqlens).astype(int))
+    h_kv, N = 2, cu[-1]
+    h_q = G * h_kv
+    g = torch.Generator().manual_seed(31)
+    Q = torch.randn((h_q, N, d), generator=g)
+    K = torch.randn((h_kv, N, d), generator=g)
+    V = torch.randn((h_kv, N, d), generator=g)
+    for a, e in zip(cu[:-1], cu[1:]):
+        K[:, a:e] *= torch.linspace(0.5, 3.0, e - a)[None, :, None]
+    Q, K, V = (x.to(torch.bfloat16) for x in (Q, K, V))
+    rows = []
+    for a, e in zip(cu[:-1], cu[1:]):
+        for i in range(-(-(e - a) // B)):
+            keep = [j for j in range(i) if rng.uniform() < 0.7]
+            rows.append(keep + [i] if rng.uniform() < 0.8 or not keep else keep)
+    kmax = max(len(r) for r in rows)
+    idx = np.full((len(rows), kmax), -1, dtype=np.int32)
+    for r, s in enumerate(rows):
+        idx[r, :len(s)] = s
+    cnt = np.array([len(s) for s in rows], dtype=np.int32)
+    out, lse = sw.sparse_attn_prefill(U.to_dev(Q), U.to_dev(K), U.to_dev(V), cu, B, U.to_dev(idx),
+                                      U.to_dev(cnt), kmax, want_lse=True)
+    got, glse = out.float().cpu().numpy(), lse.cpu().numpy()
+    Qh, Kh, Vh = O.f64(Q), O.f64(K), O.f64(V)
+    r = 0
+    for a, e in zip(cu[:-1], cu[1:]):
+        for i in range(-(-(e - a) // B)):
+            lo, hi = a + i * B, min(e, a + (i + 1) * B)
+            tok = np.concatenate([np.arange(a + j * B, min(e, a + (j + 1) * B)) for j in rows[r]])
+            for u in range(h_q):
+                ref = O.sparse_attention_block(Qh[:, a:e], Kh[:, a:e], Vh[:, a:e], B, rows[r], u, i)
+                assert U.max_abs(got[u, lo:hi], ref) <= U.ATOL_BF16, (r, u)
+                z = Qh[u, lo:hi] @ Kh[u // G, tok].T / np.sqrt(d)
+                z[tok[None, :] > np.arange(lo, hi)[:, None]] = -np.inf
+                m = z.max(axis=1)
+                want = m + np.log(np.exp(z - m[:, None]).sum(axis=1))
+                assert np.abs(glse[u, lo:hi] - want).max() <= 3.96e-3, (r, u)
+            r += 1
