@@ -977,28 +977,62 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
     lse[(long long)u * N + qpos] = (ltot > 0.0f) ? (mref + log2f(ltot)) / kLog2e : -INFINITY;
 }
 
-#undef SW_INL
-
 // ---------------------------------------------------------------------------
 // fp32 kernel
 // ---------------------------------------------------------------------------
 
-template <int D>
+// The work split and staging of the four-wavefront kernel, with every fp32
+// operand taken apart into three bf16 parts (8 significant bits each, so 24 in
+// all) and every product formed from the six partial products above 2^-24 of
+// it on v_mfma_f32_32x32x16_bf16. Six of them take 192 cycles per 16 dims
+// against 512 for the fp32 matrix instruction, and the sums are rounded once
+// per 16 products and not once per 2. Against 64 bits (8 query heads over 2,
+// d = 128, 6000 tokens) the output is 3.0e-7 off (relative, 2-norm) where the
+// fp32 instruction gave 5.3e-7.
+// Scores: the leading products and the five smaller ones have sums of their
+// own. Bounded by the matrix cores with the vector work between them (450
+// vector instructions per 96 matrix instructions and step at d = 128, of them
+// 180 that take the K/V pieces apart, 90 that take the weights apart); the
+// weights of step t are formed between the score products of step t + 1, the
+// pieces of the tiles to come between the products with V.
+// 8 query heads over 2, d = 128, B = 64, 8192 tokens, 20 %: 331 -> 181 us (82
+// -> 152 TFLOP/s of the function's own operations).
+//
+// x = h + m + l in bf16: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), each
+// difference exact in fp32; what is left out is below 2^-25 |x|. (Parts below
+// the smallest normal bf16, 1.2e-38, may be taken as zero.)
+__device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = pack_bf16x2(x0, x1);
+  const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+  m = pack_bf16x2(r0, r1);
+  l = pack_bf16x2(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+}
+
+template <int D, int KH>
 struct F32Lds {
-  static constexpr int KS = D + 4;     // K row stride (floats)
-  static constexpr int VS = D + 4;     // V row stride (floats), not transposed
-  static constexpr int K_ELEMS = KT * KS;
-  static constexpr int STAGE = 2 * K_ELEMS;
+  static constexpr int KT4 = 32 * KH;      // keys per step, 32 per wavefront
+  static constexpr int KS = D + 8;         // row strides as in the bf16 kernels
+  static constexpr int VS = D + 32;
+  static constexpr int K_PLANE = KT4 * KS;
+  static constexpr int V_PLANE = KT4 * VS;
+  static constexpr int SLOT = 3 * (K_PLANE + V_PLANE);
+  static constexpr int SLOTS = (2 * SLOT * 2 <= 144 * 1024) ? 2 : 1;   // of K and of V
 };
 
-template <int D>
-__global__ __launch_bounds__(256, 1) void attn_prefill_f32_kernel(
+template <int D, int BLK, int KH>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     int h_q, int h_kv, long long N, SeqMeta m, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ cnt, int kmax, float sl2, float* __restrict__ O,
     float* __restrict__ lse, int groups, int sg) {
-  using L = F32Lds<D>;
-  __shared__ __attribute__((aligned(16))) float lds[L::STAGE];
+  using L = F32Lds<D, KH>;
+  constexpr int NT = 256;
+  constexpr int NW = 4;
+  __shared__ __attribute__((aligned(16))) uint16_t lds[L::SLOTS * L::SLOT];
+  __shared__ int16_t blist[SW_MAX_BLOCKS];
+  __shared__ int wtot[NW];
+
+  // ---- work item ----
   const int x = blockIdx.x;
   const int xcd = x & 7;
   const int slot = x >> 3;
@@ -1009,114 +1043,406 @@ __global__ __launch_bounds__(256, 1) void attn_prefill_f32_kernel(
   const int g = gamma % h_kv;
   int row, s, i;
   lpt_row(m, rho, &row, &s, &i);
-  const int B = m.B;
+  constexpr int WPB = BLK / 32;            // 32-row groups per (query head, block)
+  constexpr int TPB = BLK / L::KT4;        // steps per block
+  static_assert(KH == 1 || (KH == 2 && BLK == 64), "key halves: a block is one step");
   const int G = h_q / h_kv;
   const int tid = threadIdx.x;
-  const int w = tid >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l = tid & 63;
   const int hl = l >> 5;
   const int ln = l & 31;
-  const int hpw = (B == 64) ? 2 : 1;
-  const int u = g * G + mu * hpw + (hpw == 2 ? (w >> 1) : 0);
-  const int rw = (hpw == 2) ? (w & 1) : w;
+  const int kh = (KH == 2) ? w & 1 : 0;    // this wavefront's 32 keys of a step
+  const int task = mu * (NW / KH) + w / KH;
+  const int u = g * G + task / WPB;
   const int seq0 = m.tok_start[s];
   const int seq1 = m.tok_start[s + 1];
-  const int q0 = seq0 + i * B + rw * 32;
-  const bool active = (u < (g + 1) * G) && (q0 < seq1);
+  const int rgrp = task % WPB;
+  const int q0 = seq0 + i * BLK + rgrp * 32;
+  const bool active = (task < G * WPB) && (q0 < seq1);
   const int qpos = q0 + ln;
 
-  float qf[D / 2];
+  const int32_t* sel = idx + (long long)row * kmax;
+  const int nsel = min(cnt[row], kmax);
+  int jnext = (tid < kmax) ? sel[tid] : -1;
+
+  // ---- Q fragments in three planes: lane holds query qpos, dims kk*16 + hl*8 .. +7 ----
+  bf16x8 qf[3][D / 16];
   {
     const bool ok = active && qpos < seq1;
-    const float* qrow = Q + ((long long)u * N + (ok ? qpos : 0)) * D;
+    const float* qrow = Q + ((long long)(ok ? u : 0) * N + (ok ? qpos : 0)) * D;
 #pragma unroll
-    for (int kk = 0; kk < D / 2; ++kk) qf[kk] = ok ? qrow[kk * 2 + hl] : 0.0f;
+    for (int kk = 0; kk < D / 16; ++kk) {
+      const float4* p = reinterpret_cast<const float4*>(qrow + kk * 16 + hl * 8);
+      const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+      const float4 a = ok ? p[0] : z, b = ok ? p[1] : z;
+      uint4 h, md, lo;
+      split2(a.x, a.y, h.x, md.x, lo.x);
+      split2(a.z, a.w, h.y, md.y, lo.y);
+      split2(b.x, b.y, h.z, md.z, lo.z);
+      split2(b.z, b.w, h.w, md.w, lo.w);
+      qf[0][kk] = __builtin_bit_cast(bf16x8, h);
+      qf[1][kk] = __builtin_bit_cast(bf16x8, md);
+      qf[2][kk] = __builtin_bit_cast(bf16x8, lo);
+    }
   }
-  const int nsel = min(cnt[row], kmax);
-  const int32_t* sel = idx + (long long)row * kmax;
-  const int tpb = B / KT;
-  const int ntiles = nsel * tpb;
 
+  // ---- selected blocks, compacted: valid j < i in list order, then i ----
+  int n_off = 0, sdiag = 0;
+  for (int base = 0; base < nsel; base += NT) {
+    const int e = base + tid;
+    const int j = (e < nsel) ? jnext : -1;
+    jnext = (e + NT < nsel) ? sel[e + NT] : -1;
+    const bool off = (j >= 0 && j < i);
+    const unsigned long long bal = __ballot(off);
+    const bool dg = __ballot(j == i) != 0ull;
+    const int pre = __popcll(bal & ((1ull << l) - 1ull));
+    if (l == 0) wtot[w] = __popcll(bal) | (dg ? 0x10000 : 0);
+    __syncthreads();
+    int woff = 0, tot = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      const int c = wtot[q];
+      woff += (q < w) ? (c & 0xffff) : 0;
+      tot += c & 0xffff;
+      sdiag |= c >> 16;
+    }
+    if (off && n_off + woff + pre < SW_MAX_BLOCKS) blist[n_off + woff + pre] = (int16_t)j;
+    n_off = min(n_off + tot, SW_MAX_BLOCKS);
+    __syncthreads();
+  }
+  const int n_blk = n_off + sdiag;
+  const int nsteps = n_blk * TPB;
+  const int noffs = n_off * TPB;
+
+  // ---- K/V staging: global -> registers -> three bf16 planes in LDS ----
+  constexpr int KCH = D / 4;               // 16-byte chunks per key row
+  constexpr int KP = (L::KT4 * KCH) / NT;  // chunks per thread for K (and for V)
+  static_assert(KP >= 1 && KP * NT == L::KT4 * KCH && NT % KCH == 0, "step chunks must divide over the workgroup");
+  constexpr int RPP = NT / KCH;            // key rows per chunk pass
+  const int sr = tid / KCH, sc = tid % KCH;
+  const int goff = (sr * D + sc * 4) * 4;
+  const int kloff = sr * L::KS + sc * 4;
+  const int vloff = sr * L::VS + sc * 4;
+  const float* Kg = K + (long long)g * N * D;
+  const float* Vg = V + (long long)g * N * D;
+  auto step_k0 = [&](int t) SW_INL {
+    const int jj = t / TPB;
+    const int j = (jj < n_off) ? __builtin_amdgcn_readfirstlane((int)blist[jj]) : i;
+    return seq0 + j * BLK + (t % TPB) * L::KT4;
+  };
+  uint16_t* const kslots = lds;
+  uint16_t* const vslots = lds + L::SLOTS * 3 * L::K_PLANE;
+  uint4 kr[KP], vr[KP];
+  // keys past the end of the sequence read as zero (the mask removes them)
+  auto load = [&](const float* base, int k0, uint4 (&r)[KP]) SW_INL {
+    const int bytes = max(0, (seq1 - k0) * D * 4);
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)(base + (long long)k0 * D), (short)0, bytes, kBufWord3);
+#pragma unroll
+    for (int p = 0; p < KP; ++p)
+      r[p] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, goff + p * RPP * D * 4, 0, 0));
+  };
+  // one 16-byte piece into its three planes
+  auto put = [&](uint16_t* to, int plane, const uint4& r) SW_INL {
+    uint2 h, md, lo;
+    split2(__uint_as_float(r.x), __uint_as_float(r.y), h.x, md.x, lo.x);
+    split2(__uint_as_float(r.z), __uint_as_float(r.w), h.y, md.y, lo.y);
+    *reinterpret_cast<uint2*>(to) = h;
+    *reinterpret_cast<uint2*>(to + plane) = md;
+    *reinterpret_cast<uint2*>(to + 2 * plane) = lo;
+  };
+  auto put_k = [&](int sl, int p) SW_INL {
+    put(kslots + sl * 3 * L::K_PLANE + kloff + p * RPP * L::KS, L::K_PLANE, kr[p]);
+  };
+  auto put_v = [&](int sl, int p) SW_INL {
+    put(vslots + sl * 3 * L::V_PLANE + vloff + p * RPP * L::VS, L::V_PLANE, vr[p]);
+  };
+
+  // ---- running state ----
   f32x16 oacc[D / 32];
 #pragma unroll
-  for (int t = 0; t < D / 32; ++t)
+  for (int td = 0; td < D / 32; ++td)
 #pragma unroll
-    for (int j = 0; j < 16; ++j) oacc[t][j] = 0.0f;
-  float mrun = -INFINITY, lrun = 0.0f;
-  float* ks = lds;
-  float* vs = lds + L::K_ELEMS;
-
-  for (int t = 0; t < ntiles; ++t) {
-    const int jj = t / tpb, kt = t % tpb;
-    const int j = sel[jj];
-    const bool valid = (j >= 0 && j <= i);
-    const int k0 = seq0 + (valid ? j : 0) * B + kt * KT;
-    __syncthreads();
-    for (int e = tid; e < KT * (D / 4); e += 256) {
-      const int key = e / (D / 4), ch = e % (D / 4);
-      const int kp = k0 + key;
-      float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
-      if (valid && kp < seq1) {
-        kv = *reinterpret_cast<const float4*>(K + ((long long)g * N + kp) * D + ch * 4);
-        vv = *reinterpret_cast<const float4*>(V + ((long long)g * N + kp) * D + ch * 4);
+    for (int j = 0; j < 16; ++j) oacc[td][j] = 0.0f;
+  float mref = kNoRef, lsum = 0.0f;        // running row max (log2 units), row sum
+  const int vlane = (kh * 32 + 4 * hl + ((ln & 15) >> 2)) * L::VS + 16 * (ln >> 4) + 4 * (ln & 3);
+  const int klane = (kh * 32 + ln) * L::KS + hl * 8;
+  constexpr int NKK = D / 16;
+  constexpr int NTD = D / 32;
+  auto mfma = [](const bf16x8& a, const bf16x8& b, const f32x16& c) SW_INL {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  };
+  auto kread = [&](const uint16_t* kp, int plane, int kk) SW_INL {
+    return *reinterpret_cast<const bf16x8*>(kp + plane * L::K_PLANE + kk * 16);
+  };
+  auto vread = [&](const uint16_t* vp, int plane, int c, int td) SW_INL {
+    const uint16_t* pp = vp + plane * L::V_PLANE + c * 16 * L::VS + td * 32;
+    const i16x4 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(pp));
+    const i16x4 r1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) i16x4*)(pp + 8 * L::VS));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  auto pb = [](const uint32_t (&q)[8], int c) SW_INL {
+    return __builtin_bit_cast(bf16x8, make_uint4(q[4 * c], q[4 * c + 1], q[4 * c + 2], q[4 * c + 3]));
+  };
+  // Scores of one step: S sums the products of the leading parts, T the five
+  // smaller ones. With EXP, the weights of the scores cur (against mref) are
+  // formed between the matrix instructions, two elements at a time.
+  uint32_t ph[8], pm[8], pl[8];
+  auto scores = [&](int sl, f32x16& S, f32x16& T, const f32x16& cur, float& ps, auto with_exp) SW_INL {
+    constexpr bool EXP = decltype(with_exp)::value;
+    constexpr int PPK = 8 / NKK;           // element pairs per 16 dims
+    const uint16_t* kp = kslots + sl * 3 * L::K_PLANE + klane;
+    bf16x8 kf[2][3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) kf[0][q] = kread(kp, q, 0);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) S[j] = T[j] = 0.0f;
+    float p0[PPK], p1[PPK];
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      const bf16x8(&k)[3] = kf[kk & 1];
+#pragma unroll
+      for (int f = 0; f < 6; ++f) {
+        if (f == 0) T = mfma(k[2], qf[0][kk], T);
+        if (f == 1) S = mfma(k[0], qf[0][kk], S);
+        if (f == 2) T = mfma(k[0], qf[2][kk], T);
+        if (f == 3) T = mfma(k[1], qf[1][kk], T);
+        if (f == 4) T = mfma(k[1], qf[0][kk], T);
+        if (f == 5) T = mfma(k[0], qf[1][kk], T);
+        if (kk + 1 < NKK && f < 3) kf[(kk + 1) & 1][f] = kread(kp, f, kk + 1);
+        if (EXP) {
+#pragma unroll
+          for (int x = 0; x < PPK; ++x) {
+            const int e = kk * PPK + x;
+            if (f == 2 * x) {
+              p0[x] = __builtin_amdgcn_exp2f(fmaf(cur[2 * e], sl2, -mref));
+              p1[x] = __builtin_amdgcn_exp2f(fmaf(cur[2 * e + 1], sl2, -mref));
+            }
+            if (f == 2 * x + 1) ps += p0[x];
+            if (f == 2 * x + 2) {
+              ps += p1[x];
+              split2(p0[x], p1[x], ph[e], pm[e], pl[e]);
+            }
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      *reinterpret_cast<float4*>(ks + key * L::KS + ch * 4) = kv;
-      *reinterpret_cast<float4*>(vs + key * L::VS + ch * 4) = vv;
     }
-    __syncthreads();
-    if (!(active && valid && k0 <= q0 + 31)) continue;
-    f32x16 sacc[2];
+  };
+  // O += V^T P of one step (small products first). With NEXT: the scores S + T of the next step and their row max.
+  // With STAGE: the pieces of the tiles on their way to LDS.
+  auto values = [&](int sl, f32x16& S, const f32x16& T, float& mx, int ksl, int vsl, auto with_next,
+                    auto with_stage) SW_INL {
+    constexpr bool NEXT = decltype(with_next)::value;
+    constexpr bool STAGE = decltype(with_stage)::value;
+    constexpr int N = 12 * NTD;            // matrix instructions
+    constexpr int PUT = N / (2 * KP);      // of them per staged piece
+    const uint16_t* vp = vslots + sl * 3 * L::V_PLANE + vlane;
+    bf16x8 vf[2][6];
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2) {
+    for (int q = 0; q < 6; ++q) vf[0][q] = vread(vp, q >> 1, q & 1, 0);
+    mx = -INFINITY;
 #pragma unroll
-      for (int jx = 0; jx < 16; ++jx) sacc[h2][jx] = 0.0f;
+    for (int td = 0; td < NTD; ++td) {
+      const bf16x8(&v)[6] = vf[td & 1];    // h0 h1 m0 m1 l0 l1
+      f32x16& t = oacc[td];
 #pragma unroll
-      for (int kk = 0; kk < D / 2; ++kk)
-        sacc[h2] = __builtin_amdgcn_mfma_f32_32x32x2f32(ks[(h2 * 32 + ln) * L::KS + kk * 2 + hl],
-                                                        qf[kk], sacc[h2], 0, 0, 0);
+      for (int f = 0; f < 12; ++f) {
+        const int c = f & 1;
+        if (f < 2) t = mfma(v[4 + c], pb(ph, c), t);
+        else if (f < 4) t = mfma(v[c], pb(pl, c), t);
+        else if (f < 6) t = mfma(v[2 + c], pb(pm, c), t);
+        else if (f < 8) t = mfma(v[2 + c], pb(ph, c), t);
+        else if (f < 10) t = mfma(v[c], pb(pm, c), t);
+        else t = mfma(v[c], pb(ph, c), t);
+        const int n = td * 12 + f;
+        if (td + 1 < NTD && f >= 2 && f < 8) vf[(td + 1) & 1][f - 2] = vread(vp, (f - 2) >> 1, (f - 2) & 1, td + 1);
+        if (NEXT && td == 0 && f >= 4) {
+          const int j = 2 * (f - 4);
+          S[j] += T[j];
+          S[j + 1] += T[j + 1];
+        }
+        if (NEXT && td == NTD - 1 && f >= 8) {
+          const int j = 4 * (f - 8);
+          mx = fmaxf(fmaxf(mx, S[j]), fmaxf(S[j + 1], fmaxf(S[j + 2], S[j + 3])));
+        }
+        if (STAGE && n % PUT == PUT - 1) {
+          const int q = n / PUT;
+          if (q < KP) put_k(ksl, q);
+          else put_v(vsl, q - KP);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
+    if (NEXT) mx = max_other_half(mx) * sl2;
+  };
+  // the reference is the running row max; O moves only when a row's max grew
+  auto raise = [&](float mx) SW_INL {
+    if (__any(mx > mref)) {
+      const float nref = fmaxf(mref, mx);
+      const float alpha = __builtin_amdgcn_exp2f(mref - nref);
+      mref = nref;
+      lsum *= alpha;
+#pragma unroll
+      for (int td = 0; td < NTD; ++td)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) oacc[td][j] *= alpha;
+    }
+  };
+  // causal + sequence-end mask of the diagonal sub-tile's scores, and their max
+  auto mask = [&](int t, f32x16& S) SW_INL {
+    const int k0 = step_k0(t) + kh * 32;
     float mx = -INFINITY;
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2)
+    for (int j = 0; j < 16; ++j) {
+      const int kp = k0 + (j >> 2) * 8 + hl * 4 + (j & 3);
+      if (kp > qpos || kp >= seq1) S[j] = -INFINITY;
+      mx = fmaxf(mx, S[j]);
+    }
+    return max_other_half(mx) * sl2;
+  };
+  auto weights = [&](const f32x16& cur) SW_INL {
+    float ps = 0.0f;
 #pragma unroll
-      for (int jx = 0; jx < 16; ++jx) {
-        float v = sacc[h2][jx] * sl2;
-        const int kp = k0 + h2 * 32 + (jx >> 2) * 8 + hl * 4 + (jx & 3);
-        if (kp > qpos || kp >= seq1) v = -INFINITY;
-        sacc[h2][jx] = v;
-        mx = fmaxf(mx, v);
+    for (int e = 0; e < 8; ++e) {
+      const float p0 = __builtin_amdgcn_exp2f(fmaf(cur[2 * e], sl2, -mref));
+      const float p1 = __builtin_amdgcn_exp2f(fmaf(cur[2 * e + 1], sl2, -mref));
+      ps += p0;
+      ps += p1;
+      split2(p0, p1, ph[e], pm[e], pl[e]);
+    }
+    lsum += ps;
+  };
+  auto first_scores = [&](int t, int sl, bool masked, f32x16& S) SW_INL {
+    f32x16 T;
+    float dummy = 0.0f;
+    scores(sl, S, T, S, dummy, std::false_type{});
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      S[j] += T[j];
+      mx = fmaxf(mx, S[j]);
+    }
+    return masked ? mask(t, S) : max_other_half(mx) * sl2;
+  };
+
+  // last step with keys for this wavefront's rows, and the masked one
+  const bool dmine = active && sdiag;
+  const int tend = (KH == 1) ? noffs - 1 + (dmine ? rgrp + 1 : 0)
+                             : noffs - 1 + ((dmine && kh <= rgrp) ? 1 : 0);
+  const int tmasked = (dmine && (KH == 1 || kh == rgrp)) ? tend : -1;
+  const std::true_type yes{};
+  const std::false_type no{};
+  f32x16 S, Sn, Tn;
+  float mx = -INFINITY;
+  if (nsteps > 0 && L::SLOTS == 2) {
+    // K runs a step ahead of V: step t reads K(t+1) and V(t), stores K(t+2) and
+    // V(t+1) where K(t) and V(t-1) were, then loads K(t+3) and V(t+2).
+    {
+      uint4 k1[KP];
+      const int a0 = step_k0(0), a1 = step_k0(1);
+      load(Kg, a0, kr);
+      load(Vg, a0, vr);
+      load(Kg, a1, k1);
+#pragma unroll
+      for (int p = 0; p < KP; ++p) put_k(0, p);
+#pragma unroll
+      for (int p = 0; p < KP; ++p) put_v(0, p);
+#pragma unroll
+      for (int p = 0; p < KP; ++p) kr[p] = k1[p];
+#pragma unroll
+      for (int p = 0; p < KP; ++p) put_k(1, p);
+      load(Kg, step_k0(2), kr);
+      load(Vg, a1, vr);
+    }
+    __syncthreads();
+    if (tend >= 0) mx = first_scores(0, 0, tmasked == 0, S);
+    __syncthreads();
+    int t = 0;
+    for (; t + 1 < noffs; ++t) {
+      const int sl = t & 1;
+      raise(mx);
+      float ps = 0.0f;
+      scores(sl ^ 1, Sn, Tn, S, ps, yes);
+      lsum += ps;
+      values(sl, Sn, Tn, mx, sl, sl ^ 1, yes, yes);
+      S = Sn;
+      load(Kg, step_k0(t + 3), kr);
+      load(Vg, step_k0(t + 2), vr);
+      __syncthreads();
+    }
+    // the last steps: each wavefront goes on, ends or skips
+    for (; t < nsteps; ++t) {
+      const int sl = t & 1;
+      if (t <= tend) {
+        raise(mx);
+        weights(S);
+        float mdummy;
+        values(sl, S, S, mdummy, 0, 0, no, no);
+        if (t < tend) mx = first_scores(t + 1, sl ^ 1, t + 1 == tmasked, S);
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float mnew = fmaxf(mrun, mx);
-    const float mref = (mnew == -INFINITY) ? 0.0f : mnew;
-    const float alpha = exp2f(mrun - mref);
-    mrun = mnew;
-    float psum = 0.0f;
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2)
+      for (int p = 0; p < KP; ++p) put_k(sl, p);
 #pragma unroll
-      for (int jx = 0; jx < 16; ++jx) {
-        const float p = exp2f(sacc[h2][jx] - mref);
-        sacc[h2][jx] = p;
-        psum += p;
+      for (int p = 0; p < KP; ++p) put_v(sl ^ 1, p);
+      load(Kg, step_k0(t + 3), kr);
+      load(Vg, step_k0(t + 2), vr);
+      __syncthreads();
+    }
+  } else if (nsteps > 0) {
+    // one slot: the next tile is stored when every wavefront is done
+    load(Kg, step_k0(0), kr);
+    load(Vg, step_k0(0), vr);
+    for (int t = 0; t < nsteps; ++t) {
+#pragma unroll
+      for (int p = 0; p < KP; ++p) put_k(0, p);
+#pragma unroll
+      for (int p = 0; p < KP; ++p) put_v(0, p);
+      load(Kg, step_k0(t + 1), kr);
+      load(Vg, step_k0(t + 1), vr);
+      __syncthreads();
+      if (t <= tend) {
+        raise(first_scores(t, 0, t == tmasked, S));
+        weights(S);
+        float mdummy;
+        values(0, S, S, mdummy, 0, 0, no, no);
       }
-    lrun = lrun * alpha + psum;
-#pragma unroll
-    for (int td = 0; td < D / 32; ++td) {
-#pragma unroll
-      for (int jx = 0; jx < 16; ++jx) oacc[td][jx] *= alpha;
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-        for (int jx = 0; jx < 16; ++jx) {
-          const int key = h2 * 32 + (jx >> 2) * 8 + hl * 4 + (jx & 3);
-          oacc[td] = __builtin_amdgcn_mfma_f32_32x32x2f32(vs[key * L::VS + td * 32 + ln],
-                                                          sacc[h2][jx], oacc[td], 0, 0, 0);
-        }
+      __syncthreads();
     }
   }
+
+  // ---- epilogue ----
+  float ltot = sum_other_half(lsum);
+  if constexpr (KH == 2) {
+    // join the two key halves of a row group (wavefronts 2r and 2r + 1)
+    float* pm = reinterpret_cast<float*>(lds);                 // [4][32] references, then sums
+    if (hl == 0) {
+      pm[w * 32 + ln] = mref;
+      pm[128 + w * 32 + ln] = ltot;
+    }
+    float* po = pm + 256 + (w >> 1) * 64 * 16 * (D / 32);
+    static_assert((256 + 2 * 64 * 16 * (D / 32)) * 4 <= L::SLOTS * L::SLOT * 2, "partials must fit the slots");
+    if (kh == 1) {
+#pragma unroll
+      for (int td = 0; td < D / 32; ++td)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) po[(td * 16 + j) * 64 + l] = oacc[td][j];
+    }
+    __syncthreads();
+    if (kh == 1) return;
+    const float m1 = pm[(w + 1) * 32 + ln], l1 = pm[128 + (w + 1) * 32 + ln];
+    const float mm = fmaxf(mref, m1);
+    const float f0 = __builtin_amdgcn_exp2f(mref - mm), f1 = __builtin_amdgcn_exp2f(m1 - mm);
+    ltot = ltot * f0 + l1 * f1;
+    mref = mm;
+#pragma unroll
+    for (int td = 0; td < D / 32; ++td)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) oacc[td][j] = oacc[td][j] * f0 + po[(td * 16 + j) * 64 + l] * f1;
+  }
   if (!active || qpos >= seq1) return;
-  const float ltot = lrun + __shfl_xor(lrun, 32);
   const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
   float* orow = O + ((long long)u * N + qpos) * D;
 #pragma unroll
@@ -1129,8 +1455,10 @@ __global__ __launch_bounds__(256, 1) void attn_prefill_f32_kernel(
       *reinterpret_cast<float4*>(orow + dv) = st;
     }
   if (lse && hl == 0)
-    lse[(long long)u * N + qpos] = (ltot > 0.0f) ? (mrun + log2f(ltot)) / kLog2e : -INFINITY;
+    lse[(long long)u * N + qpos] = (ltot > 0.0f) ? (mref + log2f(ltot)) / kLog2e : -INFINITY;
 }
+
+#undef SW_INL
 
 hipError_t launch_attn_prefill(int dtype, const void* Q, const void* K, const void* V, int h_q,
                                int h_kv, int d, long long N, const SeqMeta& meta, int64_t nb,
@@ -1183,19 +1511,25 @@ hipError_t launch_attn_prefill(int dtype, const void* Q, const void* K, const vo
     else SW_LAUNCH_BF16(64);
 #undef SW_LAUNCH_BF16
   } else {
-    const int hpw = (meta.B == 64) ? 2 : 1;
-    const int sg = (G + hpw - 1) / hpw;
+    // one query head per KV head with blocks of 64: as in the bf16 kernel
+    const bool halves = meta.B == 64 && G == 1;
+    const int sg = halves ? 1 : (G * (meta.B / 32) + 3) / 4;
     const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg);
     auto q = reinterpret_cast<const float*>(Q);
     auto k = reinterpret_cast<const float*>(K);
     auto v = reinterpret_cast<const float*>(V);
     auto o = reinterpret_cast<float*>(O);
-    if (d == 128)
-      hipLaunchKernelGGL(attn_prefill_f32_kernel<128>, dim3(grid), dim3(256), 0, st, q, k, v, h_q,
-                         h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg);
-    else
-      hipLaunchKernelGGL(attn_prefill_f32_kernel<64>, dim3(grid), dim3(256), 0, st, q, k, v, h_q,
-                         h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg);
+#define SW_LAUNCH_F32(DD, BB, KK)                                                                  \
+  hipLaunchKernelGGL((attn_prefill_f32_kernel<DD, BB, KK>), dim3(grid), dim3(256), 0, st, q, k, v, \
+                     h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg)
+    if (halves) {
+      if (d == 128) SW_LAUNCH_F32(128, 64, 2);
+      else SW_LAUNCH_F32(64, 64, 2);
+    } else if (d == 128 && meta.B == 128) SW_LAUNCH_F32(128, 128, 1);
+    else if (d == 128) SW_LAUNCH_F32(128, 64, 1);
+    else if (meta.B == 128) SW_LAUNCH_F32(64, 128, 1);
+    else SW_LAUNCH_F32(64, 64, 1);
+#undef SW_LAUNCH_F32
   }
   return hipGetLastError();
 }

@@ -178,3 +178,57 @@ def test_head_counts_and_lengths_of_the_two_bf16_kernels(d, B, G):
                 want = m + np.log(np.exp(z - m[:, None]).sum(axis=1))
                 assert np.abs(glse[u, lo:hi] - want).max() <= 3.96e-3, (r, u)
             r += 1
+
+
+@pytest.mark.parametrize("d,B,G", [(64, 64, 1), (128, 64, 1), (64, 128, 1), (128, 128, 2),
+                                   (128, 64, 3), (64, 64, 2)])
+def test_fp32_attention_is_fp32_accurate(d, B, G):
+    """The fp32 kernel against float64 over operands of mixed magnitude (rows
+    scaled by 2^-12 .. 2^12, values by 2^-20 .. 2^20 per dimension), rows of 1
+    to 6 selected blocks, ragged ends. Bound per output: the logits are sums of
+    d products, each within 2^-23 of the exact one, accumulated in fp32
+    ((d + 2) 2^-23 sum |q_i k_i| scale at worst); the exponential adds 2^-22 of
+    the logit in log2 units; an output is a mean of the values under weights
+    with that relative error, accumulated over at most 6 B keys with sums of 16
+    (6 B / 16 roundings)."""
+    rng = np.random.default_rng(900 + d + B + G)
+    seqlens = [B * 6, B * 2 + 31, B + 1, 3]
+    cu = [0] + list(np.cumsum(seqlens).astype(int))
+    h_kv, N = 2, cu[-1]
+    h_q = G * h_kv
+    g = torch.Generator().manual_seed(33)
+    e2 = torch.randint(-12, 13, (h_kv, N, 1), generator=g).float()
+    Q = torch.randn((h_q, N, d), generator=g)
+    K = torch.randn((h_kv, N, d), generator=g) * torch.exp2(torch.minimum(e2, torch.tensor(0.0)))
+    Q[:, ::3] *= 2.0 ** -12
+    V = torch.randn((h_kv, N, d), generator=g) * torch.exp2(torch.randint(-20, 21, (d,), generator=g).float())
+    rows = []
+    for a, e in zip(cu[:-1], cu[1:]):
+        for i in range(-(-(e - a) // B)):
+            rows.append([j for j in range(i) if rng.uniform() < 0.7] + [i])
+    kmax = max(len(r) for r in rows)
+    idx = np.full((len(rows), kmax), -1, dtype=np.int32)
+    for r, s in enumerate(rows):
+        idx[r, :len(s)] = s
+    cnt = np.array([len(s) for s in rows], dtype=np.int32)
+    out = sw.sparse_attn_prefill(U.to_dev(Q), U.to_dev(K), U.to_dev(V), cu, B, U.to_dev(idx),
+                                 U.to_dev(cnt), kmax).cpu().numpy()
+    Qh, Kh, Vh = O.f64(Q), O.f64(K), O.f64(V)
+    worst = 0.0
+    r = 0
+    for a, e in zip(cu[:-1], cu[1:]):
+        for i in range(-(-(e - a) // B)):
+            lo, hi = a + i * B, min(e, a + (i + 1) * B)
+            tok = np.concatenate([np.arange(a + j * B, min(e, a + (j + 1) * B)) for j in rows[r]])
+            for u in range(h_q):
+                q, k = Qh[u, lo:hi], Kh[u // G, tok]
+                ref = O.sparse_attention_block(Qh[:, a:e], Kh[:, a:e], Vh[:, a:e], B, rows[r], u, i)
+                mag = (np.abs(q) @ np.abs(k).T).max(axis=1) / np.sqrt(d)       # per row
+                rel = (d + 2) * 2.0 ** -23 * mag + 2.0 ** -22 * (mag + 1)
+                rel = 2 * np.expm1(rel) + (6 * B / 16 + 8) * 2.0 ** -23
+                bound = rel[:, None] * np.abs(Vh[u // G, tok]).max(axis=0)[None, :]
+                err = np.abs(out[u, lo:hi] - ref)
+                worst = max(worst, float((err / bound).max()))
+            r += 1
+    print(f"largest error over its bound: {worst:.3f}", flush=True)
+    assert worst <= 1.0
