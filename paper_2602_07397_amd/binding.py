@@ -124,7 +124,7 @@ def _cu(cu_seqlens) -> Tuple[ctypes.Array, int]:
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None) -> int:
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise SketchWalkError(f"{name} must be a CUDA (HIP) tensor")
     if not t.is_contiguous():
         raise SketchWalkError(f"{name} must be contiguous")
@@ -137,8 +137,16 @@ def _opt(t: Optional[torch.Tensor], name: str, dtype=None) -> Optional[int]:
     return None if t is None else _dev(t, name, dtype)
 
 
+def _fill(out: dict, shapes: dict, dtype, dev) -> None:
+    """Allocates the outputs that the caller did not pass."""
+    for name, shape in shapes.items():
+        if name not in out:
+            out[name] = torch.empty(shape, dtype=dtype, device=dev)
+
+
 def _stream(dev: torch.device) -> int:
-    return torch.cuda.current_stream(dev).cuda_stream
+    # the handle itself: building a torch.cuda.Stream around it takes 2 us
+    return torch._C._cuda_getCurrentRawStream(dev.index)
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -156,6 +164,10 @@ def abi_version() -> int:
 def layout(cu_seqlens, B: int) -> Tuple[int, int, int]:
     """(nb, nm, max_b): total block rows, total matrix elements, largest b_s."""
     cu, n = _cu(cu_seqlens)
+    return _layout(cu, n, B)
+
+
+def _layout(cu: ctypes.Array, n: int, B: int) -> Tuple[int, int, int]:
     nb, nm, mb = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_int32()
     _check(load().sw_layout(n, cu, B, ctypes.byref(nb), ctypes.byref(nm), ctypes.byref(mb)), "sw_layout")
     return nb.value, nm.value, mb.value
@@ -189,20 +201,18 @@ def sketch_scores(Q: torch.Tensor, K: torch.Tensor, cu_seqlens, B: int, signs: t
     h_q, N, d = Q.shape
     h_kv = K.shape[0]
     r = int(cols.numel())
-    nb, nm, _ = layout(cu_seqlens, B)
     cu, n = _cu(cu_seqlens)
+    nb, nm, _ = _layout(cu, n, B)
     o = dict(out or {})
-    f64 = dict(dtype=torch.float64, device=dev)
-    o.setdefault("Qs", torch.empty((nb, r), **f64))
-    o.setdefault("Ks", torch.empty((nb, r), **f64))
-    o.setdefault("A", torch.empty((nm,), **f64))
-    o.setdefault("A_scale", torch.empty((n,), **f64))
+    shapes = {"Qs": (nb, r), "Ks": (nb, r), "A": (nm,), "A_scale": (n,)}
     if want_means:
-        o.setdefault("Qbar", torch.empty((nb, d), **f64))
-        o.setdefault("Kbar", torch.empty((nb, d), **f64))
-    wsb = sketch_workspace_bytes(h_q, h_kv, d, cu_seqlens, B)
-    if workspace is None or workspace.numel() < wsb:
-        workspace = torch.empty((max(wsb, 256),), dtype=torch.uint8, device=dev)
+        shapes["Qbar"] = shapes["Kbar"] = (nb, d)
+    _fill(o, shapes, torch.float64, dev)
+    wsb = lib.sw_sketch_workspace_bytes(h_q, h_kv, d, n, cu, B)
+    if wsb < 0:
+        _check(1, "sw_sketch_workspace_bytes")
+    if wsb > 0 and (workspace is None or workspace.numel() < wsb):
+        workspace = torch.empty((wsb,), dtype=torch.uint8, device=dev)
     if K.dtype != Q.dtype:
         raise SketchWalkError("Q and K must share a dtype")
     rc = lib.sw_sketch_scores(
@@ -211,7 +221,7 @@ def sketch_scores(Q: torch.Tensor, K: torch.Tensor, cu_seqlens, B: int, signs: t
         _dev(o["Qs"], "Qs", torch.float64), _dev(o["Ks"], "Ks", torch.float64),
         _dev(o["A"], "A", torch.float64), _dev(o["A_scale"], "A_scale", torch.float64),
         _opt(o.get("Qbar"), "Qbar", torch.float64), _opt(o.get("Kbar"), "Kbar", torch.float64),
-        _dev(workspace, "workspace"), workspace.numel(), _stream(dev))
+        _opt(workspace, "workspace"), 0 if workspace is None else workspace.numel(), _stream(dev))
     _check(rc, "sw_sketch_scores")
     return o
 
@@ -266,9 +276,13 @@ def select_topk_blocks(R: torch.Tensor, cu_seqlens, B: int, k: int = 0, density_
                        cnt: Optional[torch.Tensor] = None) -> Tuple[torch.Tensor, torch.Tensor, int]:
     lib = load()
     cu, n = _cu(cu_seqlens)
-    nb, _, _ = layout(cu_seqlens, B)
+    if idx is None or cnt is None or kmax is None:
+        nb, _, _ = _layout(cu, n, B)
     if kmax is None:
-        kmax = select_max_count(cu_seqlens, B, k, density_pct, flags)
+        out = ctypes.c_int32()
+        _check(lib.sw_select_max_count(n, cu, B, k, density_pct, flags, ctypes.byref(out)),
+               "sw_select_max_count")
+        kmax = out.value
     if idx is None:
         idx = torch.empty((nb, kmax), dtype=torch.int32, device=R.device)
     if cnt is None:
@@ -480,10 +494,10 @@ def decode_step(q_new: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, K
     if kmax is None:
         kmax = select_max_count_decode(b_max, k=k, density_pct=density_pct, flags=flags)
     o = dict(out or {})
-    o.setdefault("rows", torch.empty((L, batch, b_max), dtype=torch.float64, device=dev))
-    o.setdefault("idx", torch.empty((L, batch, kmax), dtype=torch.int32, device=dev))
-    o.setdefault("cnt", torch.empty((L, batch), dtype=torch.int32, device=dev))
-    o.setdefault("O", torch.empty_like(q_new))
+    _fill(o, {"rows": (L, batch, b_max)}, torch.float64, dev)
+    _fill(o, {"idx": (L, batch, kmax), "cnt": (L, batch)}, torch.int32, dev)
+    if "O" not in o:
+        o["O"] = torch.empty_like(q_new)
     least = decode_attn_workspace_bytes(batch, h_q, h_kv, d)
     if workspace is None or workspace.numel() < least:
         wsb = int(load().sw_decode_step_workspace_bytes(batch, h_q, h_kv, d))

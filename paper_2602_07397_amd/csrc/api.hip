@@ -97,17 +97,19 @@ int budget(int avail, int nf, int k, int pct) {
   return t;
 }
 
+// Largest budget of rows of 1 .. b available blocks. The budget does not fall
+// as the row grows (nor does the forced set), so the last row has it.
+int last_row_budget(int b, int k, int pct, uint32_t flags) {
+  const int first = (flags & SW_FORCE_FIRST) ? 0 : -1;
+  const int last = (flags & SW_FORCE_LAST) ? b - 1 : -1;
+  return budget(b, (first >= 0) + (last >= 0 && last != first), k, pct);
+}
+
 int max_count(const sw::SeqMeta& m, int k, int pct, uint32_t flags) {
   int best = 0;
   for (int s = 0; s < m.n_seqs; ++s) {
-    const int b = m.blk_start[s + 1] - m.blk_start[s];
-    for (int i = 0; i < b; ++i) {
-      const int first = (flags & SW_FORCE_FIRST) ? 0 : -1;
-      const int last = (flags & SW_FORCE_LAST) ? i : -1;
-      const int nf = (first >= 0) + (last >= 0 && last != first);
-      const int t = budget(i + 1, nf, k, pct);
-      if (t > best) best = t;
-    }
+    const int t = last_row_budget(m.blk_start[s + 1] - m.blk_start[s], k, pct, flags);
+    if (t > best) best = t;
   }
   return best;
 }
@@ -306,18 +308,6 @@ static int check_decode_shape(int batch, int d, int r, int b_max, int B) {
   return SW_OK;
 }
 
-static int max_count_decode(int b_max, int k, int pct, uint32_t flags) {
-  int best = 0;
-  for (int a = 1; a <= b_max; ++a) {
-    const int first = (flags & SW_FORCE_FIRST) ? 0 : -1;
-    const int last = (flags & SW_FORCE_LAST) ? a - 1 : -1;
-    const int nf = (first >= 0) + (last >= 0 && last != first);
-    const int t = budget(a, nf, k, pct);
-    if (t > best) best = t;
-  }
-  return best;
-}
-
 int64_t sw_decode_state_bytes(int batch, int d, int r, int b_max) {
   if (check_decode_shape(batch, d, r, b_max, 64) != SW_OK) return -1;
   ok();
@@ -410,7 +400,7 @@ int sw_select_max_count_decode(int b_max, int k, int density_pct, uint32_t flags
     return fail(SW_ERR_INVALID_ARG, "b_max=%d outside [1, %d]", b_max, SW_MAX_BLOCKS);
   CHECK(check_budget_args(k, density_pct, flags));
   if (kmax == nullptr) return fail(SW_ERR_INVALID_ARG, "kmax is NULL");
-  *kmax = max_count_decode(b_max, k, density_pct, flags);
+  *kmax = last_row_budget(b_max, k, density_pct, flags);
   return ok();
 }
 
@@ -423,7 +413,7 @@ int sw_select_topk_blocks_decode(const double* rows, int batch, int b_max, int B
   CHECK(check_ptr(pos, 4, "pos"));
   CHECK(check_ptr(idx, 4, "idx"));
   CHECK(check_ptr(cnt, 4, "cnt"));
-  const int need = max_count_decode(b_max, k, density_pct, flags);
+  const int need = last_row_budget(b_max, k, density_pct, flags);
   if (kmax < need) return fail(SW_ERR_INVALID_ARG, "kmax=%d < largest budget %d", kmax, need);
   hipError_t e = sw::launch_select_decode(rows, batch, b_max, B, pos, k, density_pct, flags, idx,
                                           cnt, kmax, reinterpret_cast<hipStream_t>(stream));
@@ -527,7 +517,7 @@ int sw_decode_step(int dtype, int layers, int batch, int h_q, int h_kv, int d, i
     return fail(SW_ERR_INVALID_ARG, "T_max=%d must be in [1, b_max * B = %lld]", T_max,
                 (long long)b_max * B);
   CHECK(check_budget_args(k, density_pct, flags));
-  const int need_k = max_count_decode(b_max, k, density_pct, flags);
+  const int need_k = last_row_budget(b_max, k, density_pct, flags);
   if (kmax < need_k) return fail(SW_ERR_INVALID_ARG, "kmax=%d < largest budget %d", kmax, need_k);
   CHECK(check_ptr(q_new, 16, "q_new"));
   CHECK(check_ptr(k_new, 16, "k_new"));
