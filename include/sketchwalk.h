@@ -77,7 +77,7 @@ int sw_abi_version(void);
 int sw_layout(int n_seqs, const int32_t* cu_seqlens /* [host] */, int B,
               int64_t* nb, int64_t* nm, int32_t* max_b);
 
-/* Host-only: bytes of workspace sw_sketch_scores needs (>= 0), or -1 on
+/* Host-only: bytes of workspace sw_sketch_scores can use (>= 0), or -1 on
    invalid arguments. */
 int64_t sw_sketch_workspace_bytes(int h_q, int h_kv, int d, int n_seqs,
                                   const int32_t* cu_seqlens /* [host] */, int B);
@@ -110,8 +110,10 @@ int sw_select_max_count(int n_seqs, const int32_t* cu_seqlens /* [host] */, int 
  * range-checked); 1 <= r <= d.
  * Outputs (float64): Qs, Ks [nb][r]; A [nm]; A_scale [n_seqs]; Qbar, Kbar
  * [nb][d] block means (optional, may be NULL).
- * workspace: >= sw_sketch_workspace_bytes(...) bytes, 256-byte aligned (the
- * current kernels need none: the query returns 0 and workspace may be NULL).
+ * workspace: optional. With sw_sketch_workspace_bytes(...) bytes, 256-byte
+ * aligned, few block rows are summed by several workgroups each (the query is
+ * 0 where that would not help); with less, or NULL, by one each. The two
+ * differ in the order of the fp64 sums. Its contents are scratch.
  */
 int sw_sketch_scores(int dtype, const void* Q, const void* K, int h_q, int h_kv, int d,
                      int n_seqs, const int32_t* cu_seqlens /* [host] */, int B,

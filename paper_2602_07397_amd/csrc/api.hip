@@ -157,7 +157,7 @@ int64_t sw_sketch_workspace_bytes(int h_q, int h_kv, int d, int n_seqs, const in
     return -1;
   }
   ok();
-  return sw::sketch_workspace_bytes(h_q, h_kv, d, nb);
+  return sw::sketch_workspace_bytes(h_q, h_kv, d, B, nb);
 }
 
 int sw_select_max_count(int n_seqs, const int32_t* cu_seqlens, int B, int k, int density_pct,
@@ -194,11 +194,11 @@ int sw_sketch_scores(int dtype, const void* Q, const void* K, int h_q, int h_kv,
   CHECK(check_ptr(A_scale, 8, "A_scale"));
   if (Qbar && !aligned(Qbar, 8)) return fail(SW_ERR_INVALID_ARG, "Qbar misaligned");
   if (Kbar && !aligned(Kbar, 8)) return fail(SW_ERR_INVALID_ARG, "Kbar misaligned");
-  const int64_t need = sw::sketch_workspace_bytes(h_q, h_kv, d, nb);
-  if (need > 0) CHECK(check_ptr(workspace, 256, "workspace"));
-  if (workspace_bytes < need)
-    return fail(SW_ERR_INVALID_ARG, "workspace_bytes=%lld < required %lld",
-                (long long)workspace_bytes, (long long)need);
+  if (workspace_bytes < 0)
+    return fail(SW_ERR_INVALID_ARG, "workspace_bytes=%lld < 0", (long long)workspace_bytes);
+  // the sketch does without a workspace: few block rows are then not split
+  if (workspace_bytes < sw::sketch_workspace_bytes(h_q, h_kv, d, B, nb) || !aligned(workspace, 256))
+    workspace = nullptr;
   hipError_t e = sw::launch_sketch(dtype, Q, K, h_q, h_kv, d, m, nb, (long long)cu_seqlens[n_seqs],
                                    signs, cols, r, Qs, Ks, A, A_scale, Qbar, Kbar, workspace,
                                    reinterpret_cast<hipStream_t>(stream));

@@ -8,7 +8,10 @@
 //                      tokens, applies the random signs, runs the
 //                      Walsh-Hadamard transform of the query mean and of the
 //                      key mean (one wavefront each, lane exchanges), samples
-//                      the columns and scales by 1/sqrt(r).
+//                      the columns and scales by 1/sqrt(r). Few block rows
+//                      are split over several workgroups each, which leave
+//                      their sums in the workspace, and
+//  sketch_parts_kernel adds them in order and goes on from there.
 //  scores_kernel       A = Qs Ks^T / sqrt(r) with fp64 MFMA 16x16x4 tiles,
 //                      causal mask, per-sequence max |A| by integer atomicMax
 //                      on the (non-negative) double bit pattern.
@@ -30,13 +33,49 @@ constexpr int kPoolThreads = SW_POOL_THREADS;
 #ifndef SW_POOL_UNROLL
 #define SW_POOL_UNROLL 8
 #endif
+constexpr int kMaxParts = 16;            // workgroups a block row is split over
 
-template <typename T>
+// The rest of a block row's sketch from the sums of its queries and keys
+// (thread t < d holds dimension t's): means, signs, the two transforms, the
+// sampled columns. x holds 2 * 256 doubles of LDS; the whole workgroup calls it.
+__device__ __forceinline__ void finish_row(double sq, double sk, int row, int cnt, int h_q, int h_kv,
+                                           int d, const int8_t* __restrict__ signs,
+                                           const int32_t* __restrict__ cols, int r,
+                                           double* __restrict__ Qs, double* __restrict__ Ks,
+                                           double* __restrict__ Qbar, double* __restrict__ Kbar,
+                                           double* x) {
+  double* xq = x;
+  double* xk = x + 256;
+  const int t = threadIdx.x;
+  if (t < d) {
+    const double mq = sq / ((double)h_q * (double)cnt);
+    const double mk = sk / ((double)h_kv * (double)cnt);
+    if (Qbar) Qbar[(long long)row * d + t] = mq;
+    if (Kbar) Kbar[(long long)row * d + t] = mk;
+    const double sg = (double)signs[t];
+    xq[t] = mq * sg;
+    xk[t] = mk * sg;
+  }
+  __syncthreads();
+  if ((t >> 6) == 0) wave_fwht(xq, d);
+  else if ((t >> 6) == 1) wave_fwht(xk, d);
+  __syncthreads();
+  if (t < r) {
+    const int c = cols[t] & (d - 1);
+    Qs[(long long)row * r + t] = xq[c] / sqrt((double)r);
+    Ks[(long long)row * r + t] = xk[c] / sqrt((double)r);
+  }
+}
+
+// SPLIT: blockIdx.y is the part of the row's (head, token) items; the sums go
+// to parts [row][part][query, key][d] and the sketch is left to
+// sketch_parts_kernel.
+template <typename T, bool SPLIT>
 __global__ __launch_bounds__(kPoolThreads) void pool_sketch_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, int h_q, int h_kv, int d, SeqMeta m,
     long long N, const int8_t* __restrict__ signs, const int32_t* __restrict__ cols, int r,
     double* __restrict__ Qs, double* __restrict__ Ks, double* __restrict__ Qbar,
-    double* __restrict__ Kbar, double* __restrict__ A_scale) {
+    double* __restrict__ Kbar, double* __restrict__ A_scale, double* __restrict__ parts) {
   constexpr int VEC = 16 / sizeof(T);
   constexpr int NW = kPoolThreads / 64;
   // per-wavefront sums of the query and key means, then (reused) the two
@@ -44,9 +83,8 @@ __global__ __launch_bounds__(kPoolThreads) void pool_sketch_kernel(
   __shared__ double red[2 * NW * 256];
   double* redq = red;
   double* redk = red + NW * 256;
-  double* xq = red;
-  double* xk = red + 256;
   const int row = blockIdx.x;
+  const int part = SPLIT ? blockIdx.y : 0, np = SPLIT ? gridDim.y : 1;
   const int s = seq_of_block(m, row);
   const int i = row - m.blk_start[s];
   const int t0 = m.tok_start[s] + i * m.B;
@@ -56,7 +94,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_sketch_kernel(
   const int slots = kPoolThreads / lpr;  // token rows in flight per pass
   const int lane = t % lpr;
   const int slot = t / lpr;
-  if (i == 0 && t == 0) A_scale[s] = 0.0;
+  if (i == 0 && t == 0 && part == 0) A_scale[s] = 0.0;
 
   auto add = [](double (&acc)[VEC], const T* p) {
     // non-temporal: Q and K are streamed once here
@@ -78,12 +116,16 @@ __global__ __launch_bounds__(kPoolThreads) void pool_sketch_kernel(
   for (int e = 0; e < VEC; ++e) aq[e] = ak[e] = 0.0;
   // items (head, token) in head-major order, `slots` apart: the head and
   // token of the next item follow by subtraction, not division
-  const int nq = h_q * cnt, nk = h_kv * cnt;
   const int dh = slots / cnt, dt = slots % cnt;
+  // (two loops written out: through one function of the operand they compiled
+  // to 164 VGPRs instead of 92 and took twice the time)
   {
-    int h = slot / cnt, tok = slot % cnt;
+    const int n = h_q * cnt;
+    const int lo = SPLIT ? (int)((long long)n * part / np) : 0;
+    const int hi = SPLIT ? (int)((long long)n * (part + 1) / np) : n;
+    int h = (lo + slot) / cnt, tok = (lo + slot) % cnt;
 _Pragma(SW_STR(unroll SW_POOL_UNROLL))
-    for (int it = slot; it < nq; it += slots) {
+    for (int it = lo + slot; it < hi; it += slots) {
       add(aq, Q + ((long long)h * N + t0 + tok) * d + lane * VEC);
       h += dh;
       tok += dt;
@@ -94,9 +136,12 @@ _Pragma(SW_STR(unroll SW_POOL_UNROLL))
     }
   }
   {
-    int h = slot / cnt, tok = slot % cnt;
+    const int n = h_kv * cnt;
+    const int lo = SPLIT ? (int)((long long)n * part / np) : 0;
+    const int hi = SPLIT ? (int)((long long)n * (part + 1) / np) : n;
+    int h = (lo + slot) / cnt, tok = (lo + slot) % cnt;
 _Pragma(SW_STR(unroll SW_POOL_UNROLL))
-    for (int it = slot; it < nk; it += slots) {
+    for (int it = lo + slot; it < hi; it += slots) {
       add(ak, K + ((long long)h * N + t0 + tok) * d + lane * VEC);
       h += dh;
       tok += dt;
@@ -123,33 +168,54 @@ _Pragma(SW_STR(unroll SW_POOL_UNROLL))
     }
   }
   __syncthreads();
-  double mq = 0.0, mk = 0.0;
+  double sq = 0.0, sk = 0.0;
   if (t < d) {
-    double sq = 0.0, sk = 0.0;
     for (int w = 0; w < NW; ++w) {
       sq += redq[w * d + t];
       sk += redk[w * d + t];
     }
-    mq = sq / ((double)h_q * (double)cnt);
-    mk = sk / ((double)h_kv * (double)cnt);
-    if (Qbar) Qbar[(long long)row * d + t] = mq;
-    if (Kbar) Kbar[(long long)row * d + t] = mk;
   }
-  __syncthreads();                       // the sums are read; xq/xk reuse them
-  if (t < d) {
-    const double sg = (double)signs[t];
-    xq[t] = mq * sg;
-    xk[t] = mk * sg;
+  if constexpr (SPLIT) {
+    if (t < d) {
+      double* o = parts + ((long long)row * np + part) * 2 * d;
+      o[t] = sq;
+      o[d + t] = sk;
+    }
+    return;
   }
-  __syncthreads();
-  if (wv == 0) wave_fwht(xq, d);
-  else if (wv == 1) wave_fwht(xk, d);
-  __syncthreads();
-  if (t < r) {
-    const int c = cols[t] & (d - 1);
-    Qs[(long long)row * r + t] = xq[c] / sqrt((double)r);
-    Ks[(long long)row * r + t] = xk[c] / sqrt((double)r);
+  __syncthreads();                       // the sums are read; the vectors reuse them
+  finish_row(sq, sk, row, cnt, h_q, h_kv, d, signs, cols, r, Qs, Ks, Qbar, Kbar, red);
+}
+
+// Block rows whose sums lie in np parts each: the parts added in order, then
+// the rest of the sketch.
+__global__ __launch_bounds__(256) void sketch_parts_kernel(
+    const double* __restrict__ parts, int np, int h_q, int h_kv, int d, SeqMeta m,
+    const int8_t* __restrict__ signs, const int32_t* __restrict__ cols, int r,
+    double* __restrict__ Qs, double* __restrict__ Ks, double* __restrict__ Qbar,
+    double* __restrict__ Kbar) {
+  __shared__ double x[2 * 256];
+  const int row = blockIdx.x;
+  const int t = threadIdx.x;
+  const double* p = parts + (long long)row * np * 2 * d + min(t, d - 1);
+  // every load goes out before the first sum (indices clamped, no condition)
+  double vq[kMaxParts], vk[kMaxParts];
+#pragma unroll
+  for (int i = 0; i < kMaxParts; ++i) {
+    vq[i] = p[(long long)min(i, np - 1) * 2 * d];
+    vk[i] = p[(long long)min(i, np - 1) * 2 * d + d];
   }
+  double sq = 0.0, sk = 0.0;
+#pragma unroll
+  for (int i = 0; i < kMaxParts; ++i)
+    if (i < np) {
+      sq += vq[i];
+      sk += vk[i];
+    }
+  const int s = seq_of_block(m, row);
+  const int t0 = m.tok_start[s] + (row - m.blk_start[s]) * m.B;
+  const int cnt = min(m.tok_start[s + 1], t0 + m.B) - t0;
+  finish_row(sq, sk, row, cnt, h_q, h_kv, d, signs, cols, r, Qs, Ks, Qbar, Kbar, x);
 }
 
 // Four 16 x 16 tiles per workgroup, one per wavefront; the per-sequence max
@@ -242,21 +308,47 @@ __global__ __launch_bounds__(256) void scores_kernel(const double* __restrict__ 
   }
 }
 
-int64_t sketch_workspace_bytes(int, int, int, int64_t) { return 0; }
+// Workgroups per block row. One workgroup streams about 50 GB/s, so from 128
+// rows on they reach what the memory gives (6.2 TB/s) and below that a call
+// took as long as its one row; split into about 256 workgroups, 32 heads + 8
+// of d = 128 with B = 128 take (with the block scores) 35.8 -> 15.6 us at 1000
+// tokens, 39.1 -> 20.0 at 4000, 40.9 -> 30.6 at 8000 and 41.2 -> 39.0 at 12000;
+// at 20000 (157 rows) it would be 42.9 -> 51.4. The launch that adds the parts
+// costs 3 us, which a row has to be worth: 80 KB rows went from 13.8 to 16.5.
+static int sketch_parts(int h_q, int h_kv, int d, int B, int64_t nb) {
+  const int64_t bytes = (int64_t)(h_q + h_kv) * B * d * 2;    // of a row in bf16
+  if (nb >= 128 || bytes < 256 * 1024) return 1;
+  const int64_t p = (256 + nb - 1) / nb;
+  return (int)(p > kMaxParts ? kMaxParts : p);
+}
+
+int64_t sketch_workspace_bytes(int h_q, int h_kv, int d, int B, int64_t nb) {
+  const int np = sketch_parts(h_q, h_kv, d, B, nb);
+  return np > 1 ? nb * np * 2 * d * (int64_t)sizeof(double) : 0;
+}
 
 hipError_t launch_sketch(int dtype, const void* Q, const void* K, int h_q, int h_kv, int d,
                          const SeqMeta& meta, int64_t nb, long long N, const int8_t* signs,
                          const int32_t* cols, int r, double* Qs, double* Ks, double* A,
-                         double* A_scale, double* Qbar, double* Kbar, void* /*ws*/,
-                         hipStream_t st) {
-  if (dtype == SW_BF16)
-    hipLaunchKernelGGL(pool_sketch_kernel<uint16_t>, dim3((unsigned)nb), dim3(kPoolThreads), 0, st,
-                       reinterpret_cast<const uint16_t*>(Q), reinterpret_cast<const uint16_t*>(K),
-                       h_q, h_kv, d, meta, N, signs, cols, r, Qs, Ks, Qbar, Kbar, A_scale);
-  else
-    hipLaunchKernelGGL(pool_sketch_kernel<float>, dim3((unsigned)nb), dim3(kPoolThreads), 0, st,
-                       reinterpret_cast<const float*>(Q), reinterpret_cast<const float*>(K), h_q,
-                       h_kv, d, meta, N, signs, cols, r, Qs, Ks, Qbar, Kbar, A_scale);
+                         double* A_scale, double* Qbar, double* Kbar, void* ws, hipStream_t st) {
+  const int np = ws != nullptr ? sketch_parts(h_q, h_kv, d, meta.B, nb) : 1;
+  double* parts = static_cast<double*>(ws);
+  const dim3 grid((unsigned)nb, (unsigned)np);
+#define SW_POOL(T, SPLIT)                                                                         \
+  hipLaunchKernelGGL((pool_sketch_kernel<T, SPLIT>), grid, dim3(kPoolThreads), 0, st,             \
+                     reinterpret_cast<const T*>(Q), reinterpret_cast<const T*>(K), h_q, h_kv, d,  \
+                     meta, N, signs, cols, r, Qs, Ks, Qbar, Kbar, A_scale, parts)
+  if (dtype == SW_BF16) {
+    if (np > 1) SW_POOL(uint16_t, true);
+    else SW_POOL(uint16_t, false);
+  } else {
+    if (np > 1) SW_POOL(float, true);
+    else SW_POOL(float, false);
+  }
+#undef SW_POOL
+  if (np > 1)
+    hipLaunchKernelGGL(sketch_parts_kernel, dim3((unsigned)nb), dim3(256), 0, st, parts, np, h_q,
+                       h_kv, d, meta, signs, cols, r, Qs, Ks, Qbar, Kbar);
   // tile prefix per sequence
   SeqMeta m2 = meta;
   int total = 0;

@@ -261,3 +261,49 @@ def test_outputs_are_deterministic():
     b = U.gpu_prefill_layer(Q, K, V, cu, w.B, ts, tc, 8, None)
     for key in ("A", "A_scale", "Qs", "Ks", "R", "idx", "cnt", "O"):
         assert torch.equal(a[key], b[key]), key
+
+
+@pytest.mark.parametrize("dtype,h_q,h_kv,d,B,seqlens", [
+    ("bf16", 32, 8, 128, 128, [700]),                  # 6 rows: 16 parts each
+    ("bf16", 32, 8, 128, 128, [1, 130, 1029]),         # rows of 1, 2 and 5 tokens
+    ("bf16", 28, 4, 128, 128, [127 * 128]),            # the most rows that are split
+    ("f32", 32, 8, 64, 64, [2100]),
+    ("bf16", 3, 1, 256, 1024, [2500])])
+def test_sketch_split_over_workgroups(dtype, h_q, h_kv, d, B, seqlens):
+    """Few large block rows are summed in parts when there is a workspace: the
+    result with one, with none (NULL) and with one that is too small against
+    the oracle; means and scores within 1e-12 of each other (two orders of the
+    same fp64 sums of at most 44000 terms: 44000 * 2^-53 = 5e-12 of the largest
+    partial sum at worst, about its root in practice)."""
+    r = min(64, d)
+    signs, cols, ts, tc = U.srht_dev(d, r, 5)
+    g = torch.Generator().manual_seed(17)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    N = sum(seqlens)
+    Q = torch.randn((h_q, N, d), generator=g).to(td)
+    K = torch.randn((h_kv, N, d), generator=g).to(td)
+    cu = [0] + list(np.cumsum(seqlens).astype(int))
+    need = sw.sketch_workspace_bytes(h_q, h_kv, d, cu, B)
+    assert need > 0
+    dQ, dK = U.to_dev(Q), U.to_dev(K)
+    sk = sw.sketch_scores(dQ, dK, cu, B, ts, tc, want_means=True)
+    for s, (a, e) in enumerate(zip(cu[:-1], cu[1:])):
+        ref = O.sketch_scores(Q[:, a:e], K[:, a:e], B, signs, cols)
+        got = U.split_mats(sk["A"].cpu().numpy(), cu, B)[s]
+        np.testing.assert_allclose(got, ref["A"], rtol=1e-12, atol=1e-12 * np.abs(ref["A"]).max())
+        assert abs(float(sk["A_scale"][s]) - np.abs(ref["A"]).max()) <= 1e-12 * np.abs(ref["A"]).max()
+    lib = sw.load()
+    ccu, n = sw._cu(cu)
+    small = torch.empty((need - 8,), dtype=torch.uint8, device=U.DEV)
+    for ws, wb in ((None, 0), (small.data_ptr(), small.numel())):
+        o = {k: torch.empty_like(v) for k, v in sk.items()}
+        rc = lib.sw_sketch_scores(sw._dtype_code(dQ), dQ.data_ptr(), dK.data_ptr(), h_q, h_kv, d, n,
+                                  ccu, B, ts.data_ptr(), tc.data_ptr(), r, o["Qs"].data_ptr(),
+                                  o["Ks"].data_ptr(), o["A"].data_ptr(), o["A_scale"].data_ptr(),
+                                  o["Qbar"].data_ptr(), o["Kbar"].data_ptr(), ws, wb,
+                                  torch.cuda.current_stream().cuda_stream)
+        assert rc == 0, lib.sw_last_error()
+        torch.cuda.synchronize()
+        for k in sk:
+            big = float(sk[k].abs().max())
+            assert float((o[k] - sk[k]).abs().max()) <= 1e-12 * max(big, 1e-3), (k, wb)
