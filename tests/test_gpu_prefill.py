@@ -307,3 +307,28 @@ def test_sketch_split_over_workgroups(dtype, h_q, h_kv, d, B, seqlens):
         for k in sk:
             big = float(sk[k].abs().max())
             assert float((o[k] - sk[k]).abs().max()) <= 1e-12 * max(big, 1e-3), (k, wb)
+
+
+@pytest.mark.parametrize("blocks", [[512, 31], [513], [545, 17, 1], [640], [1, 16, 33]])
+@pytest.mark.parametrize("s,relu", [(8, False), (3, False), (8, True), (5, True)])
+def test_walk_product_on_both_tile_sizes(blocks, s, relu):
+    """The walk product on each side of 512 blocks, at the edges of its tiles,
+    against numpy: 1e-12 of the row's largest magnitude (rows are divided by
+    it), as for the other walk tests; signed scores, so sums cancel."""
+    B = 16
+    rng = np.random.default_rng(40 + len(blocks) + blocks[0] + s)
+    cu = [0] + list(np.cumsum([B * b for b in blocks]).astype(int))
+    A = [np.tril(rng.normal(size=(b, b))) for b in blocks]
+    P = [np.tril(rng.normal(size=(b, b))) for b in blocks]
+    P = [p / np.abs(p).max(axis=1, keepdims=True) for p in P]
+    c = np.array([np.abs(a).max() for a in A])
+    dA = U.to_dev(np.concatenate([a.ravel() for a in A]))
+    dP = U.to_dev(np.concatenate([p.ravel() for p in P]))
+    R = sw.walk_update_variant(sw.WALK_RELU if relu else sw.WALK_POWER, dA, U.to_dev(c), s, cu, B,
+                               R_prev=dP)
+    for got, a, p, cc in zip(U.split_mats(R.cpu().numpy(), cu, B), A, P, c):
+        x = a / cc
+        want = p @ ((np.maximum(x, 0.0) if relu else x) ** s)
+        mx = np.abs(want).max(axis=1, keepdims=True)
+        want = want / np.where(mx > 0, mx, 1.0)
+        np.testing.assert_allclose(got, np.tril(want), rtol=0, atol=1e-12)
