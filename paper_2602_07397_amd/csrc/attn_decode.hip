@@ -6,10 +6,8 @@
 //                           K/V groups of 16 tokens are streamed with raw buffer
 //                           loads and the G query heads of the KV group are
 //                           scored and accumulated on MFMA
-//  attn_decode_kernel       fp32: each workgroup streams an equal share of the
-//                           selected tokens of one (sequence, KV head) for all
-//                           G query heads of the group with 16-byte loads and
-//                           keeps an online softmax per (key lane group, head)
+//  attn_decode_f32_kernel   fp32: the same on the fp32 matrix instructions, the
+//                           operands straight from the loads
 //  attn_merge_kernel        log-sum-exp merge of the splits, one workgroup per
 //                           (sequence, query head)
 // The layers of a one-call decode step share a launch (blockIdx.y is the
@@ -47,8 +45,6 @@ struct DecodeAttnSteps {
   long long q, cache, idx, cnt, ws;
 };
 
-constexpr int kDecodeSelCache = 512;   // selected-block entries cached per workgroup
-
 // Tuning constants (overridable at build time).
 #ifndef SW_DEC_GPS
 #define SW_DEC_GPS 2          // 16-token groups per wavefront step in decode attention
@@ -59,205 +55,6 @@ constexpr int kDecodeSelCache = 512;   // selected-block entries cached per work
 // ---------------------------------------------------------------------------
 // split-K decode attention
 // ---------------------------------------------------------------------------
-
-// LPK lanes share one key row (8 elements of 16 bytes each... per lane: 8
-// elements); KPW = 64 / LPK keys per wavefront per step.
-template <typename T, int D, int G>
-__global__ __launch_bounds__(256) void attn_decode_kernel(const T* __restrict__ q,
-                                                          const T* __restrict__ Kc,
-                                                          const T* __restrict__ Vc, int h_kv,
-                                                          int T_max, int B,
-                                                          const int32_t* __restrict__ pos,
-                                                          const int32_t* __restrict__ idx,
-                                                          const int32_t* __restrict__ cnt,
-                                                          int kmax, float sl2, int S,
-                                                          float* __restrict__ ws,
-                                                          DecodeAttnSteps ls) {
-  q += blockIdx.y * ls.q;
-  Kc += blockIdx.y * ls.cache;
-  Vc += blockIdx.y * ls.cache;
-  idx += blockIdx.y * ls.idx;
-  cnt += blockIdx.y * ls.cnt;
-  ws += blockIdx.y * ls.ws;
-  constexpr int EPL = 16 / sizeof(T);            // elements per lane per row
-  constexpr int LPK = D / EPL;                   // lanes per key row
-  constexpr int KPW = 64 / LPK;                  // key rows per wave per step
-  constexpr int NG = 4 * KPW;                    // key groups per workgroup
-  __shared__ float sm_m[NG][G], sm_l[NG][G];
-  __shared__ float sm_o[NG][G][D];
-  const int sp = blockIdx.x % S;
-  const int bg = blockIdx.x / S;                 // (sequence, kv head)
-  const int bi = bg / h_kv;
-  const int g = bg % h_kv;
-  const int h_q = h_kv * G;
-  const int tid = threadIdx.x;
-  const int w = tid >> 6, l = tid & 63;
-  const int kg = l / LPK, sub = l % LPK;
-  const int grp = w * KPW + kg;                  // key group id in the workgroup
-  const int p = pos[bi];
-  const bool ok = p >= 0 && p < T_max;
-  const int bc = ok ? p / B : 0;
-  const int tau = ok ? max(0, min(cnt[bi], kmax)) : 0;
-  const long long total = (long long)tau * B;
-  const long long f0 = total * sp / S, f1 = total * (sp + 1) / S;
-  const int32_t* sel = idx + (long long)bi * kmax;
-
-  float qv[G][EPL];
-#pragma unroll
-  for (int u = 0; u < G; ++u) {
-    const T* qp = q + ((long long)bi * h_q + g * G + u) * D + sub * EPL;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-      if constexpr (sizeof(T) == 2)
-        qv[u][e] = bf16_to_f32(reinterpret_cast<const uint16_t*>(qp)[e]) * sl2;
-      else
-        qv[u][e] = qp[e] * sl2;
-    }
-  }
-  float mrun[G], lrun[G], o[G][EPL];
-#pragma unroll
-  for (int u = 0; u < G; ++u) {
-    mrun[u] = -INFINITY;
-    lrun[u] = 0.0f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) o[u][e] = 0.0f;
-  }
-  const T* Kb = Kc + (long long)bg * T_max * D + sub * EPL;
-  const T* Vb = Vc + (long long)bg * T_max * D + sub * EPL;
-
-  // this workgroup's slice of the selected-block list, cached in LDS
-  __shared__ int sel_sh[kDecodeSelCache];
-  const int jj0 = (int)(f0 / B);
-  const int nsh = (f1 > f0) ? (int)((f1 - 1) / B) - jj0 + 1 : 0;
-  const bool cached = nsh <= kDecodeSelCache;
-  if (cached)
-    for (int x = tid; x < nsh; x += 256) sel_sh[x] = sel[jj0 + x];
-  __syncthreads();
-
-  constexpr int U = 4;                           // tokens per key group per step
-  for (long long fb = f0 + (long long)grp * U; fb < f1; fb += (long long)NG * U) {
-    uint4 kraw[U], vraw[U];
-    bool valid[U];
-#pragma unroll
-    for (int x = 0; x < U; ++x) {
-      const long long f = fb + x;
-      bool ok2 = f < f1;
-      int tok = 0;
-      if (ok2) {
-        const int jj = (int)(f / B);
-        const int off = (int)(f - (long long)jj * B);
-        const int j = cached ? sel_sh[jj - jj0] : sel[jj];
-        tok = j * B + off;
-        ok2 = (j >= 0 && j <= bc && tok <= p);
-      }
-      valid[x] = ok2;
-      kraw[x] = make_uint4(0, 0, 0, 0);
-      vraw[x] = make_uint4(0, 0, 0, 0);
-      if (ok2) {
-        kraw[x] = *reinterpret_cast<const uint4*>(Kb + (long long)tok * D);
-        vraw[x] = *reinterpret_cast<const uint4*>(Vb + (long long)tok * D);
-      }
-    }
-    float sc[U][G];
-#pragma unroll
-    for (int x = 0; x < U; ++x) {
-      float kf[EPL];
-      if constexpr (sizeof(T) == 2) {
-        const uint32_t kw[4] = {kraw[x].x, kraw[x].y, kraw[x].z, kraw[x].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          kf[2 * e] = __uint_as_float(kw[e] << 16);
-          kf[2 * e + 1] = __uint_as_float(kw[e] & 0xffff0000u);
-        }
-      } else {
-        kf[0] = __uint_as_float(kraw[x].x); kf[1] = __uint_as_float(kraw[x].y);
-        kf[2] = __uint_as_float(kraw[x].z); kf[3] = __uint_as_float(kraw[x].w);
-      }
-#pragma unroll
-      for (int u = 0; u < G; ++u) {
-        float a = 0.0f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) a += qv[u][e] * kf[e];
-#pragma unroll
-        for (int off2 = LPK / 2; off2 > 0; off2 >>= 1) a += __shfl_xor(a, off2);
-        sc[x][u] = valid[x] ? a : -INFINITY;
-      }
-    }
-    float vf[U][EPL];
-#pragma unroll
-    for (int x = 0; x < U; ++x) {
-      if constexpr (sizeof(T) == 2) {
-        const uint32_t vw[4] = {vraw[x].x, vraw[x].y, vraw[x].z, vraw[x].w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          vf[x][2 * e] = __uint_as_float(vw[e] << 16);
-          vf[x][2 * e + 1] = __uint_as_float(vw[e] & 0xffff0000u);
-        }
-      } else {
-        vf[x][0] = __uint_as_float(vraw[x].x); vf[x][1] = __uint_as_float(vraw[x].y);
-        vf[x][2] = __uint_as_float(vraw[x].z); vf[x][3] = __uint_as_float(vraw[x].w);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-      float mx = sc[0][u];
-#pragma unroll
-      for (int x = 1; x < U; ++x) mx = fmaxf(mx, sc[x][u]);
-      if (mx == -INFINITY) continue;               // no valid token in this step
-      const float mnew = fmaxf(mrun[u], mx);
-      const float alpha = exp2f(mrun[u] - mnew);
-      float pv[U];
-      float ps = 0.0f;
-#pragma unroll
-      for (int x = 0; x < U; ++x) {
-        pv[x] = exp2f(sc[x][u] - mnew);
-        ps += pv[x];
-      }
-      mrun[u] = mnew;
-      lrun[u] = lrun[u] * alpha + ps;
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) {
-        float acc = o[u][e] * alpha;
-#pragma unroll
-        for (int x = 0; x < U; ++x) acc += pv[x] * vf[x][e];
-        o[u][e] = acc;
-      }
-    }
-  }
-  // combine the key groups of the workgroup
-#pragma unroll
-  for (int u = 0; u < G; ++u) {
-    if (sub == 0) {
-      sm_m[grp][u] = mrun[u];
-      sm_l[grp][u] = lrun[u];
-    }
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) sm_o[grp][u][sub * EPL + e] = o[u][e];
-  }
-  __syncthreads();
-  const int nsp = S;
-  float* ws_ml = ws;                                          // [bi][u][S][2]
-  float* ws_o = ws + (long long)gridDim.x / S * G * nsp * 2;  // [bi][u][S][D]
-  for (int x = tid; x < G * D; x += 256) {
-    const int u = x / D, dim = x % D;
-    float M = -INFINITY;
-    for (int k = 0; k < NG; ++k) M = fmaxf(M, sm_m[k][u]);
-    float Lsum = 0.0f, Osum = 0.0f;
-    if (M != -INFINITY) {
-      for (int k = 0; k < NG; ++k) {
-        const float sc = exp2f(sm_m[k][u] - M);
-        Lsum += sm_l[k][u] * sc;
-        Osum += sm_o[k][u][dim] * sc;
-      }
-    }
-    const long long hu = (long long)bi * h_q + g * G + u;   // global (sequence, q head)
-    ws_o[(hu * nsp + sp) * D + dim] = Osum;
-    if (dim == 0) {
-      ws_ml[(hu * nsp + sp) * 2 + 0] = M;
-      ws_ml[(hu * nsp + sp) * 2 + 1] = Lsum;
-    }
-  }
-}
 
 // bf16 split-K decode attention on MFMA. Workgroup = (sequence, KV head,
 // split), 4 wavefronts; a wavefront takes groups of 16 consecutive selected
@@ -514,6 +311,228 @@ __global__ __launch_bounds__(256) void attn_decode_mfma_kernel(
   }
 }
 
+// fp32 split-K decode attention. Workgroups, splits and steps as in the bf16
+// kernel, one group of 16 tokens per wavefront and step (16 KB of K and V at
+// d = 128), the next one loading during the math. (At d = 64 two groups a step,
+// or two steps ahead, were up to 10 % slower.)
+//   S = K q^T       v_mfma_f32_16x16x4f32: lane (key ln, lg) holds dims
+//                   16 c + 4 lg .. + 3 of its key, and of head ln of the
+//                   queries; the product of step (c, e) takes element e of
+//                   both, so any 4 dims may share an instruction. Lane
+//                   n + 16 (m / 4) receives key m of head n.
+//   O^T += V^T P^T  step v takes key 4 lg + v: the lane's own weight of that
+//                   key as the B operand, and element t of the dims
+//                   ln D / 16 .. + D / 16 - 1 it loaded of the key's value row
+//                   as the A operand of the t-th product, whose row m is dim
+//                   m D / 16 + t. No exchange, no LDS.
+// Bounded by the reads: 6.1 to 6.4 TB/s at 512 blocks of 64 (32 query heads over
+// 8, d = 128, batch 4 and 16; 285 -> 174 and 1118 -> 675 us), where products on
+// the vector unit, a 64-bit division per token and no load in flight during the
+// math gave 3.8. The logits are added as a tree and each group's sums enter the
+// running ones once, so that nothing is less exact than it was (relative error
+// against 64 bits 1.8e-7 on average over four shapes, 1.9e-7 before; one chain
+// of products per logit gave 3.5 times the error at logits of several hundred).
+template <int D>
+__global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
+    const float* __restrict__ q, const float* __restrict__ Kc, const float* __restrict__ Vc, int h_kv,
+    int G, int T_max, int B, const int32_t* __restrict__ pos, const int32_t* __restrict__ idx,
+    const int32_t* __restrict__ cnt, int kmax, float sl2, int S, float* __restrict__ ws,
+    DecodeAttnSteps ls) {
+  q += blockIdx.y * ls.q;
+  Kc += blockIdx.y * ls.cache;
+  Vc += blockIdx.y * ls.cache;
+  idx += blockIdx.y * ls.idx;
+  cnt += blockIdx.y * ls.cnt;
+  ws += blockIdx.y * ls.ws;
+  constexpr int NC = D / 16;                       // 16-byte pieces of a key per lane
+  constexpr int DPL = D / 16;                      // value dims per lane
+  constexpr int NV = DPL / 4;                      // 16-byte pieces of a value row per lane
+  constexpr int GMAX = 8;
+  __shared__ float sm_o[4][GMAX][D];
+  __shared__ float sm_m[4][GMAX], sm_l[4][GMAX];
+  __shared__ int16_t ssel[SW_MAX_BLOCKS + 2];      // this split's block indices
+  const int sp = blockIdx.x % S;
+  const int bg = blockIdx.x / S;                   // (sequence, kv head)
+  const int bi = bg / h_kv;
+  const int g = bg % h_kv;
+  const int h_q = h_kv * G;
+  const int tid = threadIdx.x;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+  const int ln = l & 15, lg = l >> 4;
+  const int p = pos[bi];
+  const bool ok = p >= 0 && p < T_max;
+  const int bc = ok ? p / B : 0;
+  // a valid selection has at most SW_MAX_BLOCKS distinct blocks
+  const int tau = ok ? max(0, min(min(cnt[bi], kmax), SW_MAX_BLOCKS)) : 0;
+  const int gpb = B / 16;                          // 16-token groups per block
+  const int ngroups = tau * gpb;
+  const int g0 = (int)((long long)ngroups * sp / S), g1 = (int)((long long)ngroups * (sp + 1) / S);
+  const int jlo = g0 / gpb;
+  const int nj = (g1 > g0) ? (g1 - 1) / gpb - jlo + 1 : 0;
+  {
+    const int32_t* sel = idx + (long long)bi * kmax + jlo;
+    for (int e = tid; e < nj; e += 256) ssel[e] = (int16_t)max(-1, min(sel[e], 32767));
+  }
+  // query operand: head ln, dims 16 c + 4 lg + e
+  float4 qf[NC];
+  {
+    const bool hv = ln < G;
+    const float* qp = q + ((long long)bi * h_q + g * G + (hv ? ln : 0)) * D + lg * 4;
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      qf[c] = hv ? *reinterpret_cast<const float4*>(qp + 16 * c) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  f32x4d oacc[DPL];
+#pragma unroll
+  for (int t = 0; t < DPL; ++t) oacc[t] = f32x4d{0.f, 0.f, 0.f, 0.f};
+  float mrun = -INFINITY, lrun = 0.0f;
+  const float* Kb = Kc + (long long)bg * T_max * D;
+  const float* Vb = Vc + (long long)bg * T_max * D;
+  const int koff = (ln * D + lg * 4) * 4;          // per-lane byte offsets inside a group
+  const int voff = (4 * lg * D + ln * DPL) * 4;
+  __syncthreads();                                 // ssel visible
+
+  const int nsteps = (g1 - g0 + 3) / 4;
+  // loads as in the bf16 kernel: no branch, keys past p read as zero, the
+  // streaming hint
+  auto issue = [&](int step, uint4 (&kr)[NC], uint4 (&vr)[4][NV], int& t0out) {
+    const int gi = g0 + step * 4 + w;
+    int t0 = -1;
+    if (step < nsteps && gi < g1) {
+      const int f = gi * 16;
+      const int jj = f / B;
+      const int j = __builtin_amdgcn_readfirstlane((int)ssel[jj - jlo]);
+      const int tt = j * B + (f - jj * B);
+      t0 = (j >= 0 && j <= bc && tt <= p) ? tt : -1;
+    }
+    t0 = __builtin_amdgcn_readfirstlane(t0);
+    t0out = t0;
+    const int tb = max(t0, 0);
+    const int bytes = (t0 >= 0) ? (p + 1 - t0) * D * 4 : 0;
+    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(Kb + (long long)tb * D), (short)0, bytes, kDecBufWord3);
+    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(Vb + (long long)tb * D), (short)0, bytes, kDecBufWord3);
+#pragma unroll
+    for (int c = 0; c < NC; ++c)
+      kr[c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rk, koff + c * 64, 0, 2));
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int n = 0; n < NV; ++n)
+        vr[v][n] = __builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(rv, voff + v * D * 4 + n * 16, 0, 2));
+  };
+  auto compute = [&](const uint4 (&kr)[NC], const uint4 (&vr)[4][NV], int t0) {
+    if (t0 < 0) return;                            // uniform across the wavefront
+    // Sums of 8 products, added as a tree (as the lanes of a key added theirs
+    // when the products were on the vector unit): the logits are as exact.
+    f32x4d part[NC / 2];
+#pragma unroll
+    for (int c = 0; c < NC; c += 2) {
+      const float k0[4] = {__uint_as_float(kr[c].x), __uint_as_float(kr[c].y),
+                           __uint_as_float(kr[c].z), __uint_as_float(kr[c].w)};
+      const float k1[4] = {__uint_as_float(kr[c + 1].x), __uint_as_float(kr[c + 1].y),
+                           __uint_as_float(kr[c + 1].z), __uint_as_float(kr[c + 1].w)};
+      const float q0[4] = {qf[c].x, qf[c].y, qf[c].z, qf[c].w};
+      const float q1[4] = {qf[c + 1].x, qf[c + 1].y, qf[c + 1].z, qf[c + 1].w};
+      f32x4d e4[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        e4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(k0[e], q0[e], f32x4d{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        e4[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(k1[e], q1[e], e4[e], 0, 0, 0);
+      part[c / 2] = (e4[0] + e4[1]) + (e4[2] + e4[3]);
+    }
+#pragma unroll
+    for (int n = NC / 4; n > 0; n /= 2)
+#pragma unroll
+      for (int i = 0; i < n; ++i) part[i] += part[i + n];
+    const f32x4d& sacc = part[0];
+    float mx = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (t0 + 4 * lg + v <= p) mx = fmaxf(mx, sacc[v] * sl2);
+    mx = fmax_xor16(mx);
+    mx = fmax_xor32(mx);
+    const float mnew = fmaxf(mrun, mx);            // finite: key t0 <= p is valid
+    const float alpha = exp2f(mrun - mnew);
+    mrun = mnew;
+    float pv[4];
+    float ps = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      pv[v] = (t0 + 4 * lg + v <= p) ? exp2f(fmaf(sacc[v], sl2, -mnew)) : 0.0f;
+      ps += pv[v];
+    }
+    lrun = lrun * alpha + ps;
+    // the group's sums on their own, then onto the running ones
+#pragma unroll
+    for (int n = 0; n < NV; ++n) {
+      f32x4d o4[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o4[e] = f32x4d{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const uint4& r = vr[v][n];
+        o4[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(r.x), pv[v], o4[0], 0, 0, 0);
+        o4[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(r.y), pv[v], o4[1], 0, 0, 0);
+        o4[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(r.z), pv[v], o4[2], 0, 0, 0);
+        o4[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(r.w), pv[v], o4[3], 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) oacc[4 * n + e] = oacc[4 * n + e] * alpha + o4[e];
+    }
+  };
+  uint4 kA[NC], vA[4][NV], kB[NC], vB[4][NV];
+  int tA, tB;
+  issue(0, kA, vA, tA);
+  for (int it = 0; it < nsteps; it += 2) {
+    issue(it + 1, kB, vB, tB);
+    compute(kA, vA, tA);
+    if (it + 1 >= nsteps) break;
+    issue(it + 2, kA, vA, tA);
+    compute(kB, vB, tB);
+  }
+  // per-wave partials: head ln; the lane groups hold disjoint keys (sum l)
+  // and disjoint output dims
+  float lsum = sum_xor16(lrun);
+  lsum = sum_xor32(lsum);
+  if (ln < GMAX) {
+    if (lg == 0) {
+      sm_m[w][ln] = mrun;
+      sm_l[w][ln] = lsum;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+      for (int t = 0; t < DPL; ++t) sm_o[w][ln][(4 * lg + v) * DPL + t] = oacc[t][v];
+  }
+  __syncthreads();
+  float* ws_ml = ws;
+  float* ws_o = ws + (long long)gridDim.x / S * G * S * 2;
+  for (int xx = tid; xx < G * D; xx += 256) {
+    const int u = xx / D, dim = xx % D;
+    float M = -INFINITY;
+    for (int k = 0; k < 4; ++k) M = fmaxf(M, sm_m[k][u]);
+    float Lsum = 0.0f, Osum = 0.0f;
+    if (M != -INFINITY) {
+      for (int k = 0; k < 4; ++k) {
+        const float sc = exp2f(sm_m[k][u] - M);
+        Lsum += sm_l[k][u] * sc;
+        Osum += sm_o[k][u][dim] * sc;
+      }
+    }
+    const long long hu = (long long)bi * h_q + g * G + u;
+    ws_o[(hu * S + sp) * D + dim] = Osum;
+    if (dim == 0) {
+      ws_ml[(hu * S + sp) * 2 + 0] = M;
+      ws_ml[(hu * S + sp) * 2 + 1] = Lsum;
+    }
+  }
+}
+
 // Four wavefronts per (sequence, query head): every wavefront holds the splits'
 // maxima and sums (lane s holds split s) and adds the outputs of splits w,
 // w + 4, ..., all loaded before the first is used; the four sums are added in
@@ -574,19 +593,6 @@ int decode_attn_splits(int batch, int h_kv) {
   if (S < 1) S = 1;
   if (S > kDecodeMaxSplits) S = kDecodeMaxSplits;
   return S;
-}
-
-template <typename T, int D>
-static void launch_attn_decode_t(int G, dim3 grid, hipStream_t st, const T* q, const T* Kc,
-                                 const T* Vc, int h_kv, int T_max, int B, const int32_t* pos,
-                                 const int32_t* idx, const int32_t* cnt, int kmax, float sl2,
-                                 int S, float* ws, const DecodeAttnSteps& ls) {
-  switch (G) {
-    case 1: hipLaunchKernelGGL((attn_decode_kernel<T, D, 1>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
-    case 2: hipLaunchKernelGGL((attn_decode_kernel<T, D, 2>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
-    case 4: hipLaunchKernelGGL((attn_decode_kernel<T, D, 4>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
-    default: hipLaunchKernelGGL((attn_decode_kernel<T, D, 8>), grid, dim3(256), 0, st, q, Kc, Vc, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls); break;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -664,10 +670,12 @@ hipError_t launch_attn_decode(int dtype, int layers, const void* q, const void* 
     auto kk = reinterpret_cast<const float*>(Kc);
     auto vv = reinterpret_cast<const float*>(Vc);
     if (d == 128) {
-      launch_attn_decode_t<float, 128>(G, grid, st, qq, kk, vv, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
+      hipLaunchKernelGGL(attn_decode_f32_kernel<128>, grid, dim3(256), 0, st, qq, kk, vv, h_kv, G,
+                         T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
       SW_MERGE(float, 128);
     } else {
-      launch_attn_decode_t<float, 64>(G, grid, st, qq, kk, vv, h_kv, T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
+      hipLaunchKernelGGL(attn_decode_f32_kernel<64>, grid, dim3(256), 0, st, qq, kk, vv, h_kv, G,
+                         T_max, B, pos, idx, cnt, kmax, sl2, S, ws, ls);
       SW_MERGE(float, 64);
     }
   }

@@ -141,3 +141,45 @@ def test_decode_attention_large_logits_and_identical_keys(dtype):
     mean = Vh[1, 0, toks].mean(axis=0)
     for u in range(h_q):
         assert U.max_abs(got[1, u], mean) <= (U.ATOL_BF16 if dtype == "bf16" else U.ATOL_F32)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G", [1, 2, 4, 8])
+def test_fp32_decode_attention_at_group_edges(d, G):
+    """fp32 decode attention where groups and splits begin and end: positions
+    on the first and last token of a 16-token group and of a block, selections
+    of 1 to 33 groups over up to 32 splits (most of them empty), values of
+    mixed magnitude per dimension. Bound per output as for an fp32 dot product
+    added as a tree: logits within (log2(d) + 6) 2^-24 sum |q_i k_i| scale, the
+    exponential 2^-22 of the logit, 40 roundings of the sums."""
+    B = 16
+    pos = [0, 15, 16, 31, 500, 527]
+    sels = [[0], [0], [0, 1], [1], list(range(0, 32, 2)), list(range(33))]
+    batch, h_kv, T_max = len(pos), 2, 528
+    h_q = G * h_kv
+    g = torch.Generator().manual_seed(50 + G)
+    q = torch.randn((batch, h_q, d), generator=g) * 3.0
+    Kc = torch.randn((batch, h_kv, T_max, d), generator=g)
+    Vc = torch.randn((batch, h_kv, T_max, d), generator=g)
+    Vc *= torch.exp2(torch.randint(-20, 21, (d,), generator=g).float())
+    kmax = 33
+    idx = np.full((batch, kmax), -1, dtype=np.int32)
+    cnt = np.array([len(s) for s in sels], dtype=np.int32)
+    for b, s in enumerate(sels):
+        idx[b, :len(s)] = s
+    got = sw.sparse_attn_decode(U.to_dev(q), U.to_dev(Kc), U.to_dev(Vc), B,
+                                U.to_dev(np.array(pos, dtype=np.int32)), U.to_dev(idx),
+                                U.to_dev(cnt), kmax).cpu().numpy()
+    qh, Kh, Vh = O.f64(q), O.f64(Kc), O.f64(Vc)
+    worst = 0.0
+    for b in range(batch):
+        ref = O.decode_attention(qh[b], Kh[b], Vh[b], sels[b], pos[b], B)
+        tok = np.concatenate([np.arange(j * B, (j + 1) * B) for j in sels[b]])
+        tok = tok[tok <= pos[b]]
+        for u in range(h_q):
+            mag = (np.abs(Kh[b, u // G, tok]) @ np.abs(qh[b, u])).max() / np.sqrt(d)
+            rel = 2 * np.expm1((np.log2(d) + 6) * 2.0 ** -24 * mag + 2.0 ** -22 * (mag + 1)) + 40 * 2.0 ** -24
+            bound = rel * np.abs(Vh[b, u // G, tok]).max(axis=0)
+            worst = max(worst, float((np.abs(got[b, u] - ref[u]) / bound).max()))
+    print(f"largest error over its bound: {worst:.3f}", flush=True)
+    assert worst <= 1.0
