@@ -112,14 +112,17 @@ __global__ __launch_bounds__(256) void attn_decode_mfma_kernel(
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int ln = l & 15, lg = l >> 4;
-  const int p = pos[bi];
+  const int p = pos[bi], have = cnt[bi];           // both loads before either is used
   const bool ok = p >= 0 && p < T_max;
   const int bc = ok ? p / B : 0;
-  // a valid selection has at most SW_MAX_BLOCKS distinct blocks
-  const int tau = ok ? max(0, min(min(cnt[bi], kmax), SW_MAX_BLOCKS)) : 0;
+  // a valid selection has at most SW_MAX_BLOCKS distinct blocks, so 32 bits
+  // hold groups (at most 64 per block) times splits
+  const int tau = ok ? max(0, min(min(have, kmax), SW_MAX_BLOCKS)) : 0;
   const int gpb = B / 16;                          // 16-token groups per block
   const int ngroups = tau * gpb;
-  const int g0 = (int)((long long)ngroups * sp / S), g1 = (int)((long long)ngroups * (sp + 1) / S);
+  static_assert((long long)SW_MAX_BLOCKS * 64 * (kDecodeMaxSplits + 1) < (1ll << 31), "32-bit split bounds");
+  const int g0 = (int)((unsigned)(ngroups * sp) / (unsigned)S);
+  const int g1 = (int)((unsigned)(ngroups * (sp + 1)) / (unsigned)S);
   const int jlo = g0 / gpb;
   const int nj = (g1 > g0) ? (g1 - 1) / gpb - jlo + 1 : 0;
   {
@@ -359,14 +362,17 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
   const int ln = l & 15, lg = l >> 4;
-  const int p = pos[bi];
+  const int p = pos[bi], have = cnt[bi];           // both loads before either is used
   const bool ok = p >= 0 && p < T_max;
   const int bc = ok ? p / B : 0;
-  // a valid selection has at most SW_MAX_BLOCKS distinct blocks
-  const int tau = ok ? max(0, min(min(cnt[bi], kmax), SW_MAX_BLOCKS)) : 0;
+  // a valid selection has at most SW_MAX_BLOCKS distinct blocks, so 32 bits
+  // hold groups (at most 64 per block) times splits
+  const int tau = ok ? max(0, min(min(have, kmax), SW_MAX_BLOCKS)) : 0;
   const int gpb = B / 16;                          // 16-token groups per block
   const int ngroups = tau * gpb;
-  const int g0 = (int)((long long)ngroups * sp / S), g1 = (int)((long long)ngroups * (sp + 1) / S);
+  static_assert((long long)SW_MAX_BLOCKS * 64 * (kDecodeMaxSplits + 1) < (1ll << 31), "32-bit split bounds");
+  const int g0 = (int)((unsigned)(ngroups * sp) / (unsigned)S);
+  const int g1 = (int)((unsigned)(ngroups * (sp + 1)) / (unsigned)S);
   const int jlo = g0 / gpb;
   const int nj = (g1 > g0) ? (g1 - 1) / gpb - jlo + 1 : 0;
   {

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kPfWaves * 64, 1) void attn_prefill_bf16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, int h_q, int h_kv, long long N, SeqMeta m,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int kmax, float sl2,
-    uint16_t* __restrict__ O, float* __restrict__ lse, int groups, int sg) {
+    uint16_t* __restrict__ O, float* __restrict__ lse, int groups, int sg, int heads) {
   using L = BfLds<D>;
   constexpr int NT = kPfWaves * 64;        // threads
   __shared__ __attribute__((aligned(16))) uint16_t lds[L::NST * L::STAGE];
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kPfWaves * 64, 1) void attn_prefill_bf16_kernel(
   // same number of unmasked diagonal sub-tiles.
   const int rgrp = (w >= kPfWaves / 2) ? WPB - 1 - task % WPB : task % WPB;
   const int q0 = seq0 + i * BLK + rgrp * 32;   // first query row of this wavefront
-  const bool active = (task < G * WPB) && (q0 < seq1);
+  const bool active = (task < heads * WPB) && (q0 < seq1);
   const int qpos = q0 + ln;                // this lane's query row
 
   // The selection count and the first chunk of the selection list are
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, int h_q, int h_kv, long long N, SeqMeta m,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int kmax, float sl2,
-    uint16_t* __restrict__ O, float* __restrict__ lse, int groups, int sg) {
+    uint16_t* __restrict__ O, float* __restrict__ lse, int groups, int sg, int head0) {
   using L = W4Lds<D, KH>;
   constexpr int NT = 256;
   constexpr int NW = 4;
@@ -613,12 +613,13 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
   const int ln = l & 31;                   // lane within half
   const int kh = (KH == 2) ? w & 1 : 0;    // this wavefront's 32 keys of a step
   const int task = mu * (NW / KH) + w / KH;
-  const int u = g * G + task / WPB;        // query head (meaningful only when active)
+  const int hd = head0 + task / WPB;       // query head of the group
+  const int u = g * G + hd;                // (meaningful only when active)
   const int seq0 = m.tok_start[s];
   const int seq1 = m.tok_start[s + 1];
   const int rgrp = task % WPB;
   const int q0 = seq0 + i * BLK + rgrp * 32;   // first query row of this wavefront
-  const bool active = (task < G * WPB) && (q0 < seq1);
+  const bool active = (hd < G) && (q0 < seq1);
   const int qpos = q0 + ln;                // this lane's query row
 
   const int32_t* sel = idx + (long long)row * kmax;
@@ -1484,15 +1485,17 @@ hipError_t launch_attn_prefill(int dtype, const void* Q, const void* K, const vo
     // win by what the eight leave idle: B = 128 113 / 74, B = 64 194 / 90 and,
     // d = 64, 146 / 51.
     const bool four = d == 64 || tasks * 8 < sg * kPfWaves * 7;
-    if (four) {
-      // G = 1 and B = 64 have rows for two wavefronts only: the other two
+    // query heads of a group from head0 on, four wavefronts per workgroup
+    auto launch4 = [&](int head0) {
+      // one head and B = 64 give rows to two wavefronts only: the other two
       // take the other half of the keys, if the row's blocks fit the list
-      const bool halves = meta.B == 64 && G == 1 && kmax <= W4Lds<128, 2>::LIST;
-      const int sg4 = halves ? 1 : (tasks + 3) / 4;
+      const int n = G - head0;
+      const bool halves = meta.B == 64 && n == 1 && kmax <= W4Lds<128, 2>::LIST;
+      const int sg4 = halves ? 1 : (n * (meta.B / 32) + 3) / 4;
       const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg4);
 #define SW_LAUNCH_W4(DD, BB, KK)                                                                  \
   hipLaunchKernelGGL((attn_prefill_w4_kernel<DD, BB, KK>), dim3(grid), dim3(256), 0, st, q, k, v, \
-                     h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg4)
+                     h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg4, head0)
       if (halves) {
         if (d == 128) SW_LAUNCH_W4(128, 64, 2);
         else SW_LAUNCH_W4(64, 64, 2);
@@ -1501,15 +1504,28 @@ hipError_t launch_attn_prefill(int dtype, const void* Q, const void* K, const vo
       else if (meta.B == 128) SW_LAUNCH_W4(64, 128, 1);
       else SW_LAUNCH_W4(64, 64, 1);
 #undef SW_LAUNCH_W4
+    };
+    if (four) {
+      launch4(0);
       return hipGetLastError();
     }
-    const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg);
+    // Workgroups of eight; the heads of a last one that would be half empty go
+    // to workgroups of four in a second launch, where there is work to outlast
+    // its longest row: 28 heads over 4, B = 128, in one launch / two: 376
+    // (block, KV head) groups 239 / 253 us, 512 419 / 411, 752 313 / 298, 1024
+    // 1572 / 1459, 1564 3597 / 3311.
+    const int full = tasks / kPfWaves, rest = tasks % kPfWaves;
+    const bool both = rest >= 1 && rest <= kPfWaves / 2 && groups >= 640;
+    const int sg8 = both ? full : sg;
+    const int heads = both ? full * kPfWaves / (meta.B / 32) : G;
+    const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg8);
 #define SW_LAUNCH_BF16(BB)                                                                        \
   hipLaunchKernelGGL((attn_prefill_bf16_kernel<128, BB>), dim3(grid), dim3(kPfWaves * 64), 0, st, q, k, v, \
-                     h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg)
+                     h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg8, heads)
     if (meta.B == 128) SW_LAUNCH_BF16(128);
     else SW_LAUNCH_BF16(64);
 #undef SW_LAUNCH_BF16
+    if (both) launch4(heads);
   } else {
     // one query head per KV head with blocks of 64: as in the bf16 kernel
     const bool halves = meta.B == 64 && G == 1;

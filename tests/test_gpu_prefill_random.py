@@ -232,3 +232,35 @@ def test_fp32_attention_is_fp32_accurate(d, B, G):
             r += 1
     print(f"largest error over its bound: {worst:.3f}", flush=True)
     assert worst <= 1.0
+
+
+@pytest.mark.parametrize("G,B,h_kv,blocks", [(7, 128, 4, [159, 1]), (7, 128, 4, [158, 1]),
+                                             (9, 64, 8, [50, 30])])
+def test_heads_divided_between_the_two_bf16_kernels(G, B, h_kv, blocks):
+    """640 (block, KV head) groups and just below: the heads that would half
+    fill a workgroup of eight wavefronts go to a second launch. Rows of up to
+    four blocks; every head of sampled rows against the oracle."""
+    d, h_q = 128, G * h_kv
+    rng = np.random.default_rng(G + B)
+    seqlens = [b * B - 5 for b in blocks]
+    cu = [0] + list(np.cumsum(seqlens).astype(int))
+    N = cu[-1]
+    g = torch.Generator().manual_seed(77)
+    Q, K, V = (torch.randn((h, N, d), generator=g).to(torch.bfloat16) for h in (h_q, h_kv, h_kv))
+    rows = [sorted(set(rng.integers(0, i + 1, size=3).tolist()) | {i}) for b in blocks for i in range(b)]
+    idx = np.full((len(rows), 4), -1, dtype=np.int32)
+    for r, s in enumerate(rows):
+        idx[r, :len(s)] = s
+    cnt = np.array([len(s) for s in rows], dtype=np.int32)
+    got = sw.sparse_attn_prefill(U.to_dev(Q), U.to_dev(K), U.to_dev(V), cu, B, U.to_dev(idx),
+                                 U.to_dev(cnt), 4).float().cpu().numpy()
+    r0 = 0
+    for b, a, e in zip(blocks, cu[:-1], cu[1:]):
+        Qh, Kh, Vh = O.f64(Q[:, a:e]), O.f64(K[:, a:e]), O.f64(V[:, a:e])
+        for i in sorted({0, b // 2, b - 1}):
+            for u in range(h_q):
+                ref = O.sparse_attention_block(Qh, Kh, Vh, B, rows[r0 + i], u, i)
+                lo, hi = a + i * B, min(e, a + (i + 1) * B)
+                assert U.max_abs(got[u, lo:hi], ref) <= U.ATOL_BF16, (b, i, u)
+        r0 += b
+    assert np.isfinite(got).all()
