@@ -1346,17 +1346,19 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
       const int a0 = step_k0(0), a1 = step_k0(1);
       load(Kg, a0, kr);
       load(Vg, a0, vr);
-      load(Kg, a1, k1);
+      if (nsteps > 1) load(Kg, a1, k1);
 #pragma unroll
       for (int p = 0; p < KP; ++p) put_k(0, p);
 #pragma unroll
       for (int p = 0; p < KP; ++p) put_v(0, p);
+      if (nsteps > 1) {
+        load(Vg, a1, vr);
 #pragma unroll
-      for (int p = 0; p < KP; ++p) kr[p] = k1[p];
+        for (int p = 0; p < KP; ++p) kr[p] = k1[p];
 #pragma unroll
-      for (int p = 0; p < KP; ++p) put_k(1, p);
-      load(Kg, step_k0(2), kr);
-      load(Vg, a1, vr);
+        for (int p = 0; p < KP; ++p) put_k(1, p);
+        if (nsteps > 2) load(Kg, step_k0(2), kr);
+      }
     }
     __syncthreads();
     if (tend >= 0) mx = first_scores(0, 0, tmasked == 0, S);
@@ -1374,7 +1376,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
       load(Vg, step_k0(t + 2), vr);
       __syncthreads();
     }
-    // the last steps: each wavefront goes on, ends or skips
+    // the last steps: each wavefront goes on, ends or skips; tiles that no
+    // later step reads are neither stored nor loaded
     for (; t < nsteps; ++t) {
       const int sl = t & 1;
       if (t <= tend) {
@@ -1384,14 +1387,18 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
         values(sl, S, S, mdummy, 0, 0, no, no);
         if (t < tend) mx = first_scores(t + 1, sl ^ 1, t + 1 == tmasked, S);
       }
+      if (t + 1 >= nsteps) break;
+      if (t + 2 < nsteps) {
 #pragma unroll
-      for (int p = 0; p < KP; ++p) put_k(sl, p);
+        for (int p = 0; p < KP; ++p) put_k(sl, p);
+        if (t + 3 < nsteps) load(Kg, step_k0(t + 3), kr);
+      }
 #pragma unroll
       for (int p = 0; p < KP; ++p) put_v(sl ^ 1, p);
-      load(Kg, step_k0(t + 3), kr);
-      load(Vg, step_k0(t + 2), vr);
+      if (t + 2 < nsteps) load(Vg, step_k0(t + 2), vr);
       __syncthreads();
     }
+    __syncthreads();                       // every wavefront is done with the slots
   } else if (nsteps > 0) {
     // one slot: the next tile is stored when every wavefront is done
     load(Kg, step_k0(0), kr);
