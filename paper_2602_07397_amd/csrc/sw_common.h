@@ -11,10 +11,11 @@ namespace sw {
 // Lane layouts of the matrix instructions used here (measured on gfx950):
 //  v_mfma_f64_16x16x4f64: A[m][k] from lane m + 16k, B[k][n] from lane n + 16k,
 //    D[m][n] in lane n + 16 (m % 4), element m / 4.
-//  v_mfma_f32_32x32x16_bf16 / v_mfma_f32_32x32x2f32: A[m][k] from lane
-//    m + 32 (k / K_lane), element k % K_lane (K_lane = 8 / 1), B[k][n] from lane
-//    n + 32 (k / K_lane); D[m][n] in lane n + 32 ((m / 4) % 2), element
-//    4 (m / 8) + m % 4.
+//  v_mfma_f32_32x32x16_bf16: A[m][k] from lane m + 32 (k / 8), element k % 8,
+//    B[k][n] from lane n + 32 (k / 8), element k % 8; D[m][n] in lane
+//    n + 32 ((m / 4) % 2), element 4 (m / 8) + m % 4.
+//  v_mfma_f32_16x16x4f32: A[m][k] from lane m + 16 k, B[k][n] from lane
+//    n + 16 k; D[m][n] in lane n + 16 (m / 4), element m % 4.
 
 // Per-call sequence layout, passed to kernels by value (fits the kernel
 // argument space for up to SW_MAX_SEQS sequences).
