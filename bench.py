@@ -45,10 +45,10 @@ PEAK_HBM_GBS = 8000.0
 # measured on: a changed source reports null.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 MEASURED_TRAFFIC = {
-    "attn_prefill.hip": ("2149d18851d90f262dfc6f4961c3e5831781851fa204e37a2fc0bb1999ee0fa0",
-                         334347.4 * 1024, 262144.0 * 1024),
-    "attn_decode.hip": ("63befefed809dbbb7d18ce6f2ea196fd42b541d037ae887a09056ecb2c0f901d",
-                        419749.8 * 1024, 1088.0 * 1024),
+    "attn_prefill.hip": ("b2edf270af78ed78ea2f36634e4797c0ab297d25e00c8872b74dc1cddaca28b0",
+                         334476.9 * 1024, 262144.0 * 1024),
+    "attn_decode.hip": ("550fcd2958fbc46480c1ad2aebcc9a22cc1694d335bb001ee2edca197fb82cac",
+                        419787.5 * 1024, 1088.0 * 1024),
 }
 
 
