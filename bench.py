@@ -45,7 +45,7 @@ PEAK_HBM_GBS = 8000.0
 # measured on: a changed source reports null.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 MEASURED_TRAFFIC = {
-    "attn_prefill.hip": ("b2edf270af78ed78ea2f36634e4797c0ab297d25e00c8872b74dc1cddaca28b0",
+    "attn_prefill.hip": ("9f72bcd7d3bea8db874fde3734aa66b0e8a0ab311546c3014af48815f9a7be83",
                          334476.9 * 1024, 262144.0 * 1024),
     "attn_decode.hip": ("550fcd2958fbc46480c1ad2aebcc9a22cc1694d335bb001ee2edca197fb82cac",
                         419787.5 * 1024, 1088.0 * 1024),

@@ -996,8 +996,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
 // 180 that take the K/V pieces apart, 90 that take the weights apart); the
 // weights of step t are formed between the score products of step t + 1, the
 // pieces of the tiles to come between the products with V.
-// 8 query heads over 2, d = 128, B = 64, 8192 tokens, 20 %: 331 -> 181 us (82
-// -> 152 TFLOP/s of the function's own operations).
+// 8 query heads over 2, d = 128, B = 64, 8192 tokens, 20 %: 331 -> 177 us (82
+// -> 156 TFLOP/s of the function's own operations).
 //
 // x = h + m + l in bf16: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), each
 // difference exact in fp32; what is left out is below 2^-25 |x|. (Parts below
