@@ -45,8 +45,8 @@ PEAK_HBM_GBS = 8000.0
 # measured on: a changed source reports null.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 MEASURED_TRAFFIC = {
-    "attn_prefill.hip": ("9f72bcd7d3bea8db874fde3734aa66b0e8a0ab311546c3014af48815f9a7be83",
-                         334476.9 * 1024, 262144.0 * 1024),
+    "attn_prefill.hip": ("47415f5f57de4fb646bc708d878452ee5cdc0aca891f005a5c397df262d704b5",
+                         334359.2 * 1024, 262144.0 * 1024),
     "attn_decode.hip": ("550fcd2958fbc46480c1ad2aebcc9a22cc1694d335bb001ee2edca197fb82cac",
                         419787.5 * 1024, 1088.0 * 1024),
 }

@@ -1491,7 +1491,11 @@ hipError_t launch_attn_prefill(int dtype, const void* Q, const void* K, const vo
     // B = 128: 937 / 929); with one query head per KV head (16 over 16) they
     // win by what the eight leave idle: B = 128 113 / 74, B = 64 194 / 90 and,
     // d = 64, 146 / 51.
-    const bool four = d == 64 || tasks * 8 < sg * kPfWaves * 7;
+    // Where the eight's workgroups do not fill the chip's 256 CUs once, the
+    // shorter start and end of the four decide (32 heads over 8, B = 128: 1000
+    // tokens 16.0 / 14.5, 2000 22.8 / 22.6, 3000 37.0 / 38.5; 8 over 2: 4000 tokens
+    // 30.0 / 27.9, 8000 48.3 / 48.5).
+    const bool four = d == 64 || tasks * 8 < sg * kPfWaves * 7 || groups * sg <= 240;
     // query heads of a group from head0 on, four wavefronts per workgroup
     auto launch4 = [&](int head0) {
       // one head and B = 64 give rows to two wavefronts only: the other two

@@ -124,11 +124,14 @@ def test_rows_selecting_every_block_at_max_blocks():
             assert U.max_abs(got[u, i * B:(i + 1) * B], ref) <= U.ATOL_BF16, (i, u)
 
 
-@pytest.mark.parametrize("d,B,G", [(128, 64, 1), (64, 64, 1), (128, 128, 1), (128, 64, 2),
-                                   (128, 64, 3), (128, 128, 3), (64, 64, 2), (64, 128, 3),
-                                   (128, 128, 2), (128, 64, 4)])
-def test_head_counts_and_lengths_of_the_two_bf16_kernels(d, B, G):
-    """Both sides of the head-count rule, rows of 1 to 9 selected blocks (every
+@pytest.mark.parametrize("d,B,G,h_kv", [(128, 64, 1, 2), (64, 64, 1, 2), (128, 128, 1, 2),
+                                        (128, 64, 2, 2), (128, 64, 3, 2), (128, 128, 3, 2),
+                                        (64, 64, 2, 2), (64, 128, 3, 2), (128, 128, 2, 2),
+                                        (128, 64, 4, 2), (128, 128, 2, 16), (128, 64, 4, 16),
+                                        (128, 128, 4, 8)])
+def test_head_counts_and_lengths_of_the_two_bf16_kernels(d, B, G, h_kv):
+    """Both sides of the head-count and launch-size rules (the last three are
+    the eight-wavefront kernel's; six of their heads are checked), rows of 1 to 9 selected blocks (every
     remainder of the unrolled steps), sequences ending on every 32-row group of
     a block, and keys that grow along the sequence, so that the exponent
     reference moves and the two key halves of a row end with different ones.
@@ -141,8 +144,9 @@ def test_head_counts_and_lengths_of_the_two_bf16_kernels(d, B, G):
     rng = np.random.default_rng(700 + d + B + G)
     seqlens = [B * 9, B * 3 + 1, B + 33, B * 2 + B // 2 + 7, 5]
     cu = [0] + list(np.cumsum(seqlens).astype(int))
-    h_kv, N = 2, cu[-1]
+    N = cu[-1]
     h_q = G * h_kv
+    heads = range(h_q) if h_kv == 2 else sorted(rng.choice(h_q, size=6, replace=False).tolist())
     g = torch.Generator().manual_seed(31)
     Q = torch.randn((h_q, N, d), generator=g)
     K = torch.randn((h_kv, N, d), generator=g)
@@ -169,7 +173,7 @@ def test_head_counts_and_lengths_of_the_two_bf16_kernels(d, B, G):
         for i in range(-(-(e - a) // B)):
             lo, hi = a + i * B, min(e, a + (i + 1) * B)
             tok = np.concatenate([np.arange(a + j * B, min(e, a + (j + 1) * B)) for j in rows[r]])
-            for u in range(h_q):
+            for u in heads:
                 ref = O.sparse_attention_block(Qh[:, a:e], Kh[:, a:e], Vh[:, a:e], B, rows[r], u, i)
                 assert U.max_abs(got[u, lo:hi], ref) <= U.ATOL_BF16, (r, u)
                 z = Qh[u, lo:hi] @ Kh[u // G, tok].T / np.sqrt(d)
