@@ -4,8 +4,8 @@
 // over those keys only.
 //
 // bf16 kernels: one of eight wavefronts per workgroup, described here, and one
-// of four for head dimension 64 and for head counts that leave the eight
-// without rows (further down). Work item = (query block, KV head g, slice of
+// of four or two for head dimension 64, for head counts that leave the eight
+// without rows and for small launches (further down). Work item = (query block, KV head g, slice of
 // the group's query heads). A 512-thread workgroup has 8 wavefronts, two per
 // SIMD; each owns 32 query rows of one head (a B = 128 block takes four wavefronts per head, a
 // B = 64 block two), so a workgroup serves two (B = 128) or four (B = 64)
@@ -548,47 +548,43 @@ __global__ __launch_bounds__(kPfWaves * 64, 1) void attn_prefill_bf16_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// bf16 kernel, four wavefronts
+// bf16 kernel, four or two wavefronts
 // ---------------------------------------------------------------------------
 
-// The pipeline of the eight-wavefront kernel for workgroups of four
+// The pipeline of the eight-wavefront kernel for workgroups of NW = 4
 // wavefronts, two or three to a CU: one workgroup's list, first tiles and
 // output run beside another's math. A step is 32 keys per wavefront: the
 // scores of step t + 1 and the P.V of step t, so K is staged one step ahead of
 // V and two slots of each suffice, with one barrier a step.
-// KH = 2 (one query head per KV head, blocks of 64): a block has 32-row groups
-// for two wavefronts, so wavefronts 2r and 2r + 1 take the two 32-key halves of
-// each 64-key step for row group r and join their sums at the end.
+// NW = 2 where there are rows for two wavefronts only (one query head and
+// blocks of 64): half the threads, twice the workgroups on a CU.
+// A wavefront does what one of the eight does for the same rows, in the same
+// order, so that a row's bits do not depend on which of the kernels took it.
 // Bounded by the matrix cores and the softmax beside them as the other kernel;
-// each K/V tile serves 128 query rows (64 with KH = 2) and not 256, so its
+// each K/V tile serves 128 query rows (64 with NW = 2) and not 256, so its
 // staging weighs more. The steps at the end (a wavefront goes on, masks, ends
 // or skips) run one at a time with the state copied over: unrolled by two like
 // the main loop they took 282 VGPRs at D = 128 and spilled.
-template <int D, int KH>
+template <int D>
 struct W4Lds {
-  static constexpr int KT4 = 32 * KH;      // keys per step, 32 per wavefront
+  static constexpr int KT4 = 32;           // keys per step
   static constexpr int KS = BfLds<D>::KS;
   static constexpr int VS = BfLds<D>::VS;
   static constexpr int K_ELEMS = KT4 * KS;
   static constexpr int V_ELEMS = KT4 * VS;
   static constexpr int SLOTS = 2 * (K_ELEMS + V_ELEMS);   // two K slots, two V slots
-  // selected blocks a row can hold: two workgroups share a CU's 160 KB
-  static constexpr int LIST = (80 * 1024 - 2 * SLOTS - 64) / 2 < SW_MAX_BLOCKS
-                                  ? (80 * 1024 - 2 * SLOTS - 64) / 2
-                                  : SW_MAX_BLOCKS;
 };
 
-template <int D, int BLK, int KH>
-__global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
+template <int D, int BLK, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void attn_prefill_w4_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, int h_q, int h_kv, long long N, SeqMeta m,
     const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt, int kmax, float sl2,
     uint16_t* __restrict__ O, float* __restrict__ lse, int groups, int sg, int head0) {
-  using L = W4Lds<D, KH>;
-  constexpr int NT = 256;
-  constexpr int NW = 4;
+  using L = W4Lds<D>;
+  constexpr int NT = NW * 64;
   __shared__ __attribute__((aligned(16))) uint16_t lds[L::SLOTS];
-  __shared__ int16_t blist[L::LIST];
+  __shared__ int16_t blist[SW_MAX_BLOCKS];
   __shared__ int wtot[NW];
 
   // ---- work item ----
@@ -604,15 +600,13 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
   lpt_row(m, rho, &row, &s, &i);
   constexpr int WPB = BLK / 32;            // 32-row groups per (query head, block)
   constexpr int TPB = BLK / L::KT4;        // steps per block
-  static_assert(KH == 1 || (KH == 2 && BLK == 64), "key halves: a block is one step");
   const int G = h_q / h_kv;
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l = tid & 63;
   const int hl = l >> 5;                   // half-wave
   const int ln = l & 31;                   // lane within half
-  const int kh = (KH == 2) ? w & 1 : 0;    // this wavefront's 32 keys of a step
-  const int task = mu * (NW / KH) + w / KH;
+  const int task = mu * NW + w;
   const int hd = head0 + task / WPB;       // query head of the group
   const int u = g * G + hd;                // (meaningful only when active)
   const int seq0 = m.tok_start[s];
@@ -658,8 +652,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
       tot += c & 0xffff;
       sdiag |= c >> 16;
     }
-    if (off && n_off + woff + pre < L::LIST) blist[n_off + woff + pre] = (int16_t)j;
-    n_off = min(n_off + tot, L::LIST);
+    if (off && n_off + woff + pre < SW_MAX_BLOCKS) blist[n_off + woff + pre] = (int16_t)j;
+    n_off = min(n_off + tot, SW_MAX_BLOCKS);
     __syncthreads();
   }
   const int n_blk = n_off + sdiag;
@@ -720,12 +714,12 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
   constexpr int PV_PER_PAIR = NPV / 4;     // P.V MFMAs per element pair (phase B)
   constexpr int kAhead = 3;                // K and V^T operands are read this many MFMAs ahead
   // V^T operand lane offset (see the eight-wavefront kernel)
-  const int vlane = (kh * 32 + 4 * hl + ((ln & 15) >> 2)) * L::VS + 16 * (ln >> 4) + 4 * (ln & 3);
-  const int klane = (kh * 32 + ln) * L::KS + hl * 8;
+  const int vlane = (4 * hl + ((ln & 15) >> 2)) * L::VS + 16 * (ln >> 4) + 4 * (ln & 3);
+  const int klane = ln * L::KS + hl * 8;
 
   // causal + sequence-end mask of the diagonal sub-tile (raw scores)
   auto mask_sub = [&](int t, f32x16& S) SW_INL {
-    const int k0 = step_k0(t) + kh * 32;
+    const int k0 = step_k0(t);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
       const int kp = k0 + (j >> 2) * 8 + hl * 4 + (j & 3);
@@ -838,9 +832,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
   // then in the diagonal block those up to the sub-tile its rows cross, the
   // masked one (later ones lie after all its rows).
   const bool dmine = active && sdiag;
-  const int tend = (KH == 1) ? noffs - 1 + (dmine ? rgrp + 1 : 0)
-                             : noffs - 1 + ((dmine && kh <= rgrp) ? 1 : 0);
-  const int tmasked = (dmine && (KH == 1 || kh == rgrp)) ? tend : -1;
+  const int tend = noffs - 1 + (dmine ? rgrp + 1 : 0);
+  const int tmasked = dmine ? tend : -1;
   f32x16 sX, sY;
   uint32_t wX[4], wY[4];
   float tX = 0.0f, tY = 0.0f;
@@ -899,59 +892,33 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_w4_kernel(
       sub(sY, wY, tY, sX, wX, tX, 0, 1, -1);
       __syncthreads();
     }
-    // the last steps: each wavefront goes on, ends or skips
+    // the last steps: each wavefront goes on, ends, then keeps the others company
+    for (; t < tend; ++t) {
+      io(t);
+      sub(sX, wX, tX, sY, wY, tY, (t + 1) & 1, t & 1, (t + 1 == tmasked) ? t + 1 : -1);
+      sX = sY;
+      tX = tY;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) wX[e] = wY[e];
+      __syncthreads();
+    }
+    if (t == tend) {
+      io(t);
+      sub_last(sX, wX, tX, t & 1);
+      __syncthreads();
+      ++t;
+    }
     for (; t < nsteps; ++t) {
       io(t);
-      if (t < tend) {
-        sub(sX, wX, tX, sY, wY, tY, (t + 1) & 1, t & 1, (t + 1 == tmasked) ? t + 1 : -1);
-        sX = sY;
-        tX = tY;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) wX[e] = wY[e];
-      } else if (t == tend) {
-        sub_last(sX, wX, tX, t & 1);
-      }
       __syncthreads();
     }
   }
 
   // ---- epilogue (the slots are free: every run ended before the last barrier) ----
-  float ltot = sum_other_half(lsum);
-  if constexpr (KH == 2) {
-    // the two key halves of a row group (wavefronts 2r and 2r + 1) are joined
-    // under their common reference, two 32-dim blocks at a time
-    float* pm = reinterpret_cast<float*>(lds);                 // [4][32] references, then sums
-    if (hl == 0) {
-      pm[w * 32 + ln] = mref;
-      pm[128 + w * 32 + ln] = ltot;
-    }
-    float* po = pm + 256 + (w >> 1) * 64 * 16 * (D / 32);      // [D/32][16][64]
-    static_assert((256 + 2 * 64 * 16 * (D / 32)) * 4 <= L::SLOTS * 2, "partials must fit the slots");
-    if (kh == 1) {
-#pragma unroll
-      for (int td = 0; td < D / 32; ++td)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) po[(td * 16 + j) * 64 + l] = oacc[td][j];
-    }
-    __syncthreads();
-    if (kh == 0) {
-      const float m1 = pm[(w + 1) * 32 + ln], l1 = pm[128 + (w + 1) * 32 + ln];
-      // a half without keys has a sum of 0 and the reference kNoRef
-      const float mm = fmaxf(mref, m1);
-      const float f0 = __builtin_amdgcn_exp2f(mref - mm), f1 = __builtin_amdgcn_exp2f(m1 - mm);
-      ltot = ltot * f0 + l1 * f1;
-      mref = mm;
-#pragma unroll
-      for (int td = 0; td < D / 32; ++td)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) oacc[td][j] = oacc[td][j] * f0 + po[(td * 16 + j) * 64 + l] * f1;
-    }
-    __syncthreads();
-  }
+  const float ltot = sum_other_half(lsum);
   const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
   constexpr int OS = D + 8;                // output row stride in LDS (elements)
   static_assert(NW * 32 * OS <= L::SLOTS, "output staging must fit the slots");
-  if (KH == 2 && kh == 1) return;
   uint16_t* ob = lds + w * 32 * OS;        // this wavefront's own rows: no barrier
 #pragma unroll
   for (int td = 0; td < D / 32; ++td) {
@@ -1489,31 +1456,31 @@ hipError_t launch_attn_prefill(int dtype, const void* Q, const void* K, const vo
     // 1641 / 1829 us, B = 64 121 / 126; d = 64: 84 / 79 and 81 / 74. Where the
     // eight have rows for seven at most, four are as fast (28 heads over 4,
     // B = 128: 937 / 929); with one query head per KV head (16 over 16) they
-    // win by what the eight leave idle: B = 128 113 / 74, B = 64 194 / 90 and,
-    // d = 64, 146 / 51.
+    // win by what the eight leave idle: B = 128 113 / 74 and, with two
+    // wavefronts, B = 64 197 / 92 and, d = 64, 142 / 52. (One head over 8000
+    // tokens, 125 workgroups: 44 / 39 and 33 / 32.)
     // Where the eight's workgroups do not fill the chip's 256 CUs once, the
     // shorter start and end of the four decide (32 heads over 8, B = 128: 1000
     // tokens 16.0 / 14.5, 2000 22.8 / 22.6, 3000 37.0 / 38.5; 8 over 2: 4000 tokens
     // 30.0 / 27.9, 8000 48.3 / 48.5).
     const bool four = d == 64 || tasks * 8 < sg * kPfWaves * 7 || groups * sg <= 240;
-    // query heads of a group from head0 on, four wavefronts per workgroup
+    // query heads of a group from head0 on
     auto launch4 = [&](int head0) {
-      // one head and B = 64 give rows to two wavefronts only: the other two
-      // take the other half of the keys, if the row's blocks fit the list
+      // one head and B = 64: rows for two wavefronts
       const int n = G - head0;
-      const bool halves = meta.B == 64 && n == 1 && kmax <= W4Lds<128, 2>::LIST;
-      const int sg4 = halves ? 1 : (n * (meta.B / 32) + 3) / 4;
+      const bool two = meta.B == 64 && n == 1;
+      const int sg4 = two ? 1 : (n * (meta.B / 32) + 3) / 4;
       const unsigned grid = (unsigned)(((groups + 7) / 8) * 8 * sg4);
-#define SW_LAUNCH_W4(DD, BB, KK)                                                                  \
-  hipLaunchKernelGGL((attn_prefill_w4_kernel<DD, BB, KK>), dim3(grid), dim3(256), 0, st, q, k, v, \
+#define SW_LAUNCH_W4(DD, BB, WW)                                                                     \
+  hipLaunchKernelGGL((attn_prefill_w4_kernel<DD, BB, WW>), dim3(grid), dim3(WW * 64), 0, st, q, k, v, \
                      h_q, h_kv, N, meta, idx, cnt, kmax, sl2, o, lse, groups, sg4, head0)
-      if (halves) {
+      if (two) {
         if (d == 128) SW_LAUNCH_W4(128, 64, 2);
         else SW_LAUNCH_W4(64, 64, 2);
-      } else if (d == 128 && meta.B == 128) SW_LAUNCH_W4(128, 128, 1);
-      else if (d == 128) SW_LAUNCH_W4(128, 64, 1);
-      else if (meta.B == 128) SW_LAUNCH_W4(64, 128, 1);
-      else SW_LAUNCH_W4(64, 64, 1);
+      } else if (d == 128 && meta.B == 128) SW_LAUNCH_W4(128, 128, 4);
+      else if (d == 128) SW_LAUNCH_W4(128, 64, 4);
+      else if (meta.B == 128) SW_LAUNCH_W4(64, 128, 4);
+      else SW_LAUNCH_W4(64, 64, 4);
 #undef SW_LAUNCH_W4
     };
     if (four) {

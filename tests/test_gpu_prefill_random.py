@@ -268,3 +268,72 @@ def test_heads_divided_between_the_two_bf16_kernels(G, B, h_kv, blocks):
                 assert U.max_abs(got[u, lo:hi], ref) <= U.ATOL_BF16, (b, i, u)
         r0 += b
     assert np.isfinite(got).all()
+
+
+def _selected_rows(rng, b, kmax):
+    """A selection of up to kmax blocks per row, the own block among them."""
+    idx = np.full((b, kmax), -1, dtype=np.int32)
+    cnt = np.zeros(b, dtype=np.int32)
+    for i in range(b):
+        s = sorted(set(rng.integers(0, i + 1, size=min(i, kmax - 1)).tolist()) | {i})
+        idx[i, :len(s)] = s
+        cnt[i] = len(s)
+    return idx, cnt
+
+
+@pytest.mark.parametrize("d,B,n", [(64, 64, 2000), (128, 64, 2000), (128, 64, 5000), (64, 128, 2000),
+                                   (128, 128, 5000)])
+def test_a_bf16_head_has_the_same_bits_in_every_kernel(d, B, n):
+    """A query head's attention is bit-identical whatever the number of heads,
+    the launch size and kmax make of the call: alone (workgroups of two or four
+    wavefronts), in groups of 2, 3, 4 and 8 (four, or eight at d = 128 where the
+    launch fills the chip), and with the list padded beyond 3040 entries. Keys
+    that grow along the sequence move the exponent references, so another order
+    or another reference would show."""
+    rng = np.random.default_rng(d + B + n)
+    b = -(-n // B)
+    idx, cnt = _selected_rows(rng, b, 9)
+    g = torch.Generator().manual_seed(n)
+    Q = torch.randn((8, n, d), generator=g).to(torch.bfloat16)
+    V = torch.randn((1, n, d), generator=g).to(torch.bfloat16)
+    K = (torch.randn((1, n, d), generator=g) * torch.linspace(0.5, 3.0, n)[None, :, None]).to(torch.bfloat16)
+    dQ, dK, dV, dc = U.to_dev(Q), U.to_dev(K), U.to_dev(V), U.to_dev(cnt)
+
+    def call(heads, h_kv=1, kmax=9):
+        wide = np.full((b, kmax), -1, dtype=np.int32)
+        wide[:, :9] = idx
+        q = dQ[:heads].repeat(h_kv, 1, 1).contiguous()
+        return sw.sparse_attn_prefill(q, dK.repeat(h_kv, 1, 1).contiguous(), dV.repeat(h_kv, 1, 1).contiguous(),
+                                      [0, n], B, U.to_dev(wide), dc, kmax, want_lse=True)
+
+    O1, l1 = call(8, h_kv=32)                   # 256 or more workgroups: eight wavefronts at d = 128
+    for heads, h_kv, kmax in ((1, 1, 9), (2, 1, 9), (3, 1, 9), (4, 1, 9), (8, 1, 9), (1, 32, 9),
+                              (1, 1, 3040), (1, 1, 3041), (1, 1, 4096)):
+        out, lse = call(heads, h_kv, kmax)
+        for u in range(heads * h_kv):
+            assert torch.equal(out[u], O1[u % heads]), (heads, h_kv, kmax, u)
+            assert torch.equal(lse[u], l1[u % heads]), (heads, h_kv, kmax, u)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_long_lists_of_one_query_head(dtype, d):
+    """Rows of exactly 3040, 3041 and 4096 selected blocks (SW_MAX_BLOCKS) with
+    one query head and blocks of 64."""
+    B, b = 64, sw.MAX_BLOCKS
+    N = b * B
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator().manual_seed(92)
+    Q, K, V = (torch.randn((1, N, d), generator=g).to(td) for _ in range(3))
+    full = {3039: 3040, 3040: 3041, 3500: 3041, b - 2: 3040, b - 1: b}
+    sel = [list(range(full[i] - 1)) + [i] if i in full else [i] for i in range(b)]
+    idx = np.full((b, b), -1, dtype=np.int32)
+    cnt = np.array([len(s) for s in sel], dtype=np.int32)
+    for r, s in enumerate(sel):
+        idx[r, :len(s)] = s
+    got = sw.sparse_attn_prefill(U.to_dev(Q), U.to_dev(K), U.to_dev(V), [0, N], B, U.to_dev(idx),
+                                 U.to_dev(cnt), b).float().cpu().numpy()
+    tol = U.ATOL_BF16 if dtype == "bf16" else U.ATOL_F32
+    Qh, Kh, Vh = O.f64(Q), O.f64(K), O.f64(V)
+    for i in sorted(full) + [0, 1, 2000]:
+        ref = O.sparse_attention_block(Qh, Kh, Vh, B, sel[i], 0, i)
+        assert U.max_abs(got[0, i * B:(i + 1) * B], ref) <= tol, i
