@@ -12,6 +12,7 @@
 //                           (sequence, query head)
 // The layers of a one-call decode step share a launch (blockIdx.y is the
 // layer; buffers are stacked over the layers).
+#include <climits>
 #include <mutex>
 
 #include "sw_common.h"
@@ -353,7 +354,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
   constexpr int GMAX = 8;
   __shared__ float sm_o[4][GMAX][D];
   __shared__ float sm_m[4][GMAX], sm_l[4][GMAX];
-  __shared__ int16_t ssel[SW_MAX_BLOCKS + 2];      // this split's block indices
+  __shared__ int ssel[SW_MAX_BLOCKS];              // this split's block indices
   const int sp = blockIdx.x % S;
   const int bg = blockIdx.x / S;                   // (sequence, kv head)
   const int bi = bg / h_kv;
@@ -365,20 +366,19 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
   const int p = pos[bi], have = cnt[bi];           // both loads before either is used
   const bool ok = p >= 0 && p < T_max;
   const int bc = ok ? p / B : 0;
-  // a valid selection has at most SW_MAX_BLOCKS distinct blocks, so 32 bits
-  // hold groups (at most 64 per block) times splits
-  const int tau = ok ? max(0, min(min(have, kmax), SW_MAX_BLOCKS)) : 0;
+  const int tau = ok ? max(0, min(min(have, kmax), INT_MAX / 64)) : 0;
   const int gpb = B / 16;                          // 16-token groups per block
   const int ngroups = tau * gpb;
-  static_assert((long long)SW_MAX_BLOCKS * 64 * (kDecodeMaxSplits + 1) < (1ll << 31), "32-bit split bounds");
-  const int g0 = (int)((unsigned)(ngroups * sp) / (unsigned)S);
-  const int g1 = (int)((unsigned)(ngroups * (sp + 1)) / (unsigned)S);
-  const int jlo = g0 / gpb;
-  const int nj = (g1 > g0) ? (g1 - 1) / gpb - jlo + 1 : 0;
-  {
-    const int32_t* sel = idx + (long long)bi * kmax + jlo;
-    for (int e = tid; e < nj; e += 256) ssel[e] = (int16_t)max(-1, min(sel[e], 32767));
+  int g0, g1;
+  if (tau <= SW_MAX_BLOCKS) {
+    static_assert((long long)SW_MAX_BLOCKS * 64 * (kDecodeMaxSplits + 1) < (1ll << 31), "32-bit split bounds");
+    g0 = (int)((unsigned)(ngroups * sp) / (unsigned)S);
+    g1 = (int)((unsigned)(ngroups * (sp + 1)) / (unsigned)S);
+  } else {
+    g0 = (int)((long long)ngroups * sp / S);
+    g1 = (int)((long long)ngroups * (sp + 1) / S);
   }
+  const int32_t* sel = idx + (long long)bi * kmax;
   // query operand: head ln, dims 16 c + 4 lg + e
   float4 qf[NC];
   {
@@ -391,30 +391,31 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
   f32x4d oacc[DPL];
 #pragma unroll
   for (int t = 0; t < DPL; ++t) oacc[t] = f32x4d{0.f, 0.f, 0.f, 0.f};
+  // largest raw score and the sum of the weights. The scale comes after the
+  // subtraction: the largest weight is exactly 1 however large the scores are.
   float mrun = -INFINITY, lrun = 0.0f;
   const float* Kb = Kc + (long long)bg * T_max * D;
   const float* Vb = Vc + (long long)bg * T_max * D;
   const int koff = (ln * D + lg * 4) * 4;          // per-lane byte offsets inside a group
   const int voff = (4 * lg * D + ln * DPL) * 4;
-  __syncthreads();                                 // ssel visible
 
-  const int nsteps = (g1 - g0 + 3) / 4;
+  // the groups c0 .. c1 of one piece of the list, whose blocks start at jlo
+  int c0 = g0, c1 = g0, jlo = 0, nsteps = 0;
   // loads as in the bf16 kernel: no branch, keys past p read as zero, the
   // streaming hint
   auto issue = [&](int step, uint4 (&kr)[NC], uint4 (&vr)[4][NV], int& t0out) {
-    const int gi = g0 + step * 4 + w;
+    const int gi = c0 + step * 4 + w;
     int t0 = -1;
-    if (step < nsteps && gi < g1) {
-      const int f = gi * 16;
-      const int jj = f / B;
-      const int j = __builtin_amdgcn_readfirstlane((int)ssel[jj - jlo]);
-      const int tt = j * B + (f - jj * B);
-      t0 = (j >= 0 && j <= bc && tt <= p) ? tt : -1;
+    if (step < nsteps && gi < c1) {
+      const int jj = gi / gpb;
+      const int j = __builtin_amdgcn_readfirstlane(ssel[jj - jlo]);
+      const int tt = (j >= 0 && j <= bc) ? j * B + (gi - jj * gpb) * 16 : INT_MAX;
+      t0 = tt <= p ? tt : -1;
     }
     t0 = __builtin_amdgcn_readfirstlane(t0);
     t0out = t0;
     const int tb = max(t0, 0);
-    const int bytes = (t0 >= 0) ? (p + 1 - t0) * D * 4 : 0;
+    const int bytes = (t0 >= 0) ? min(p + 1 - t0, 16) * D * 4 : 0;
     const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(Kb + (long long)tb * D), (short)0, bytes, kDecBufWord3);
     const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
@@ -459,17 +460,19 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
     float mx = -INFINITY;
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      if (t0 + 4 * lg + v <= p) mx = fmaxf(mx, sacc[v] * sl2);
+      if (t0 + 4 * lg + v <= p) mx = fmaxf(mx, sacc[v]);
     mx = fmax_xor16(mx);
     mx = fmax_xor32(mx);
-    const float mnew = fmaxf(mrun, mx);            // finite: key t0 <= p is valid
-    const float alpha = exp2f(mrun - mnew);
-    mrun = mnew;
+    mx = fmaxf(mrun, mx);
+    // -infinity while every score so far was: those keys have weight 0
+    const float mnew = mx == -INFINITY ? 0.0f : mx;
+    const float alpha = exp2f((mrun - mnew) * sl2);
+    mrun = mx;
     float pv[4];
     float ps = 0.0f;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      pv[v] = (t0 + 4 * lg + v <= p) ? exp2f(fmaf(sacc[v], sl2, -mnew)) : 0.0f;
+      pv[v] = (t0 + 4 * lg + v <= p) ? exp2f((sacc[v] - mnew) * sl2) : 0.0f;
       ps += pv[v];
     }
     lrun = lrun * alpha + ps;
@@ -493,13 +496,23 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
   };
   uint4 kA[NC], vA[4][NV], kB[NC], vB[4][NV];
   int tA, tB;
-  issue(0, kA, vA, tA);
-  for (int it = 0; it < nsteps; it += 2) {
-    issue(it + 1, kB, vB, tB);
-    compute(kA, vA, tA);
-    if (it + 1 >= nsteps) break;
-    issue(it + 2, kA, vA, tA);
-    compute(kB, vB, tB);
+  // the list in pieces of SW_MAX_BLOCKS entries (one, but for longer selections)
+  while (c1 < g1) {
+    c0 = c1;
+    jlo = c0 / gpb;
+    c1 = min((long long)g1, ((long long)jlo + SW_MAX_BLOCKS) * gpb);
+    nsteps = (c1 - c0 + 3) / 4;
+    if (c0 > g0) __syncthreads();                  // the piece before is done with ssel
+    for (int e = tid; e < (c1 - 1) / gpb - jlo + 1; e += 256) ssel[e] = sel[jlo + e];
+    __syncthreads();
+    issue(0, kA, vA, tA);
+    for (int it = 0; it < nsteps; it += 2) {
+      issue(it + 1, kB, vB, tB);
+      compute(kA, vA, tA);
+      if (it + 1 >= nsteps) break;
+      issue(it + 2, kA, vA, tA);
+      compute(kB, vB, tB);
+    }
   }
   // per-wave partials: head ln; the lane groups hold disjoint keys (sum l)
   // and disjoint output dims
@@ -525,7 +538,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
     float Lsum = 0.0f, Osum = 0.0f;
     if (M != -INFINITY) {
       for (int k = 0; k < 4; ++k) {
-        const float sc = exp2f(sm_m[k][u] - M);
+        const float sc = exp2f((sm_m[k][u] - M) * sl2);
         Lsum += sm_l[k][u] * sc;
         Osum += sm_o[k][u][dim] * sc;
       }
@@ -539,7 +552,8 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
   }
 }
 
-// Four wavefronts per (sequence, query head): every wavefront holds the splits'
+// The splits' maxima are in units of 1 / ms log2 (fp32: raw scores, ms = the
+// scale; bf16: ms = 1). Four wavefronts per (sequence, query head): every wavefront holds the splits'
 // maxima and sums (lane s holds split s) and adds the outputs of splits w,
 // w + 4, ..., all loaded before the first is used; the four sums are added in
 // order. The splits' outputs come from another launch, so the kernel is two
@@ -548,7 +562,7 @@ __global__ __launch_bounds__(256, 2) void attn_decode_f32_kernel(
 template <typename T, int D, int NLOAD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict__ ws, int S,
                                                          long long n_hu, T* __restrict__ O,
-                                                         long long ws_step) {
+                                                         long long ws_step, float ms) {
   static_assert(kDecodeMaxSplits <= 64, "one split per lane");   // and S <= 4 * NLOAD
   constexpr int V = D / 64;                        // output dims per lane
   typedef float vec __attribute__((ext_vector_type(V)));
@@ -568,7 +582,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* __restrict
   float M = m;
   for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
   // a split without keys (m = -inf) has weight 0; without any key all have
-  const float sc = (M != -INFINITY && l < S) ? exp2f(m - M) : 0.0f;
+  const float sc = (M != -INFINITY && l < S) ? exp2f((m - M) * ms) : 0.0f;
   float Lsum = ls * sc;
   for (int off = 32; off > 0; off >>= 1) Lsum += __shfl_xor(Lsum, off);
   vec acc = {};
@@ -651,7 +665,7 @@ hipError_t launch_attn_decode(int dtype, int layers, const void* q, const void* 
   ls.ws = n_hu * S * (d + 2);
 #define SW_MERGE_N(T, D, N)                                                                    \
   hipLaunchKernelGGL((attn_merge_kernel<T, D, N>), mgrid, dim3(256), 0, st, ws, S, n_hu,       \
-                     reinterpret_cast<T*>(O), ls.ws)
+                     reinterpret_cast<T*>(O), ls.ws, sizeof(T) == 4 ? sl2 : 1.0f)
 #define SW_MERGE(T, D)                                      \
   do {                                                      \
     if (S <= 4) SW_MERGE_N(T, D, 1);                        \

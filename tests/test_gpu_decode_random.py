@@ -183,3 +183,94 @@ def test_fp32_decode_attention_at_group_edges(d, G):
             worst = max(worst, float((np.abs(got[b, u] - ref[u]) / bound).max()))
     print(f"largest error over its bound: {worst:.3f}", flush=True)
     assert worst <= 1.0
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_decode_attention_with_extreme_logits(d):
+    """Finite inputs at the ends of the range. Sequence 0: the logits of its
+    first 40 tokens overflow to -infinity (whole 16-token groups of them before
+    and after the first key that counts), so those keys have weight 0. Sequence
+    1: all of them do, the output is 0. Sequences 2 and 3: logits of 1e12 and
+    -1e33, far apart: all the weight is on the largest (values equal to its
+    value, exactly). Sequence 4: the largest value a float holds, in K (weight
+    0) and V."""
+    B, T_max, batch, h_kv, G = 16, 96, 5, 1, 2
+    big = float(np.finfo(np.float32).max)
+    g = torch.Generator().manual_seed(8)
+    q = torch.full((batch, G, d), 2e19)
+    K = torch.randn((batch, h_kv, T_max, d), generator=g) * 5e-21
+    V = torch.randn((batch, h_kv, T_max, d), generator=g)
+    K[0, :, :40] = -2e19
+    K[0, :, 64:] = -2e19
+    K[1] = -2e19
+    lev = torch.randperm(T_max, generator=g).float()
+    q[2], q[3] = 1e10, 1e30
+    K[2, 0] = ((lev - 48) * (2.0 / d))[:, None]
+    K[3, 0] = (-(lev + 10) * (100.0 / d))[:, None]
+    q[4] = 1.0
+    K[4] = 0.0
+    K[4, 0, 3, 0] = -big
+    V[4, 0, :, 1] = 0.0
+    V[4, 0, 50, 1] = big
+    idx = np.arange(T_max // B, dtype=np.int32)[None, :].repeat(batch, 0)
+    cnt = np.full(batch, T_max // B, dtype=np.int32)
+    pos = np.full(batch, T_max - 1, dtype=np.int32)
+    got = sw.sparse_attn_decode(U.to_dev(q), U.to_dev(K), U.to_dev(V), B, U.to_dev(pos),
+                                U.to_dev(idx), U.to_dev(cnt), T_max // B).cpu().numpy()
+    qh, Kh, Vh = O.f64(q), O.f64(K), O.f64(V)
+    for u in range(G):
+        z = Kh[0, 0, 40:64] @ qh[0, u] / np.sqrt(d)
+        w = np.exp(z - z.max())
+        assert U.max_abs(got[0, u], (w / w.sum()) @ Vh[0, 0, 40:64]) <= U.ATOL_F32
+        assert (got[1, u] == 0.0).all()
+        for b in (2, 3):
+            top = int(np.argmax(Kh[b, 0] @ qh[b, u]))
+            assert (got[b, u] == V[b, 0, top].numpy()).all(), b
+        w = np.exp(Kh[4, 0] @ qh[4, u] / np.sqrt(d))
+        want = (w / w.sum()) @ Vh[4, 0]
+        assert np.isfinite(got[4, u]).all()
+        assert (np.abs(got[4, u] - want) <= U.ATOL_F32 * np.maximum(np.abs(want), 1.0)).all()
+
+
+@pytest.mark.parametrize("batch,n", [(1, 4097), (1, 9000), (600, 4096), (600, 4097), (600, 9000)])
+def test_fp32_decode_attention_over_long_lists(batch, n):
+    """More list entries than SW_MAX_BLOCKS (a selection of the caller's own):
+    split 32 ways (batch 1) and in one piece (batch 600). The first 4096 entries
+    run through two blocks, the others through two more; keys that are listed r
+    times count r times. A wavefront adds the sums of its n / 4 groups one after
+    the other, and the weights' likewise: 2 n / 4 roundings of 2^-24."""
+    B, d, T_max = 16, 64, 64
+    g = torch.Generator().manual_seed(n)
+    q = torch.randn((batch, 1, d), generator=g)
+    K, V = (torch.randn((batch, 1, T_max, d), generator=g) for _ in range(2))
+    lst = np.arange(n, dtype=np.int32) % 2 + np.where(np.arange(n) < 4096, 0, 2).astype(np.int32)
+    got = sw.sparse_attn_decode(U.to_dev(q), U.to_dev(K), U.to_dev(V), B,
+                                U.to_dev(np.full(batch, T_max - 3, dtype=np.int32)),
+                                U.to_dev(np.tile(lst, (batch, 1))),
+                                U.to_dev(np.full(batch, n, dtype=np.int32)), n).cpu().numpy()
+    mult = np.bincount(lst, minlength=4).repeat(B)[:T_max - 2]
+    for b in {0, batch // 2, batch - 1}:
+        z = O.f64(K)[b, 0, :T_max - 2] @ O.f64(q)[b, 0] / np.sqrt(d)
+        w = mult * np.exp(z - z.max())
+        want = (w / w.sum()) @ O.f64(V)[b, 0, :T_max - 2]
+        tol = U.ATOL_F32 + 2 * (n / 4) * 2.0 ** -24 * float(V[b].abs().max())
+        assert U.max_abs(got[b, 0], want) <= tol, b
+
+
+def test_fp32_decode_attention_of_distant_blocks():
+    """Block numbers past 32767 (attention over a cache of 640000 tokens)."""
+    B, d, T_max = 16, 64, 640000
+    g = torch.Generator().manual_seed(3)
+    q = torch.randn((1, 2, d), generator=g)
+    K, V = (torch.randn((1, 1, T_max, d), generator=g) for _ in range(2))
+    sel = [0, 32767, 32768, 36000, 39999]
+    pos = T_max - 2
+    got = sw.sparse_attn_decode(U.to_dev(q), U.to_dev(K), U.to_dev(V), B,
+                                U.to_dev(np.array([pos], dtype=np.int32)),
+                                U.to_dev(np.array([sel], dtype=np.int32)),
+                                U.to_dev(np.array([len(sel)], dtype=np.int32)), len(sel)).cpu().numpy()
+    tok = np.concatenate([np.arange(j * B, min((j + 1) * B, pos + 1)) for j in sel])
+    for u in range(2):
+        z = O.f64(K[0, 0, tok]) @ O.f64(q[0, u]) / np.sqrt(d)
+        w = np.exp(z - z.max())
+        assert U.max_abs(got[0, u], (w / w.sum()) @ O.f64(V[0, 0, tok])) <= U.ATOL_F32
