@@ -274,3 +274,28 @@ def test_fp32_decode_attention_of_distant_blocks():
         z = O.f64(K[0, 0, tok]) @ O.f64(q[0, u]) / np.sqrt(d)
         w = np.exp(z - z.max())
         assert U.max_abs(got[0, u], (w / w.sum()) @ O.f64(V[0, 0, tok])) <= U.ATOL_F32
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,batch,h_kv,G", [(64, 515, 1, 1), (128, 129, 4, 2), (128, 511, 1, 1)])
+def test_one_split_and_two(dtype, d, batch, h_kv, G):
+    """512 (sequence, KV head) pairs and more have one split, fewer have two:
+    numbers of heads that leave the merge's last workgroup without some, and
+    sequences that are skipped (zeros)."""
+    B, T_max = 16, 48
+    g = torch.Generator().manual_seed(batch)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    q = torch.randn((batch, G * h_kv, d), generator=g).to(td)
+    K, V = (torch.randn((batch, h_kv, T_max, d), generator=g).to(td) for _ in range(2))
+    pos = (np.arange(batch) % 50 - 1).astype(np.int32)               # -1 and 48 are skipped
+    idx = np.tile(np.arange(3, dtype=np.int32), (batch, 1))
+    got = sw.sparse_attn_decode(U.to_dev(q), U.to_dev(K), U.to_dev(V), B, U.to_dev(pos), U.to_dev(idx),
+                                U.to_dev(np.full(batch, 3, dtype=np.int32)), 3).float().cpu().numpy()
+    qh, Kh, Vh = O.f64(q), O.f64(K), O.f64(V)
+    tol = U.ATOL_BF16 if dtype == "bf16" else U.ATOL_F32
+    for b in range(batch):
+        p = int(pos[b])
+        if p < 0 or p >= T_max:
+            assert (got[b] == 0.0).all(), b
+        else:
+            assert U.max_abs(got[b], O.decode_attention(qh[b], Kh[b], Vh[b], [0, 1, 2], p, B)) <= tol, b
