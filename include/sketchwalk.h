@@ -201,6 +201,8 @@ int sw_select_topk_blocks(const double* R, int n_seqs, const int32_t* cu_seqlens
  * each <= its row's block index; entries outside [0, i] are skipped and
  * cnt is clamped to kmax, so malformed selections cannot read out of
  * bounds).
+ * SW_F32: Q, K and V count to their 24 bits from 2^-110 (7.7e-34) in magnitude
+ * on, smaller values with an error of up to 2^-134.
  */
 int sw_sparse_attn_prefill(int dtype, const void* Q, const void* K, const void* V,
                            int h_q, int h_kv, int d,

@@ -958,19 +958,25 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_prefill_w4_kernel(
 // d = 128, 6000 tokens) the output is 3.0e-7 off (relative, 2-norm) where the
 // fp32 instruction gave 5.3e-7.
 // Scores: the leading products and the five smaller ones have sums of their
-// own. Bounded by the matrix cores with the vector work between them (450
+// own. Bounded by the matrix cores with the vector work between them (490
 // vector instructions per 96 matrix instructions and step at d = 128, of them
-// 180 that take the K/V pieces apart, 90 that take the weights apart); the
+// 208 that take the K/V pieces apart, 88 that take the weights apart); the
 // weights of step t are formed between the score products of step t + 1, the
 // pieces of the tiles to come between the products with V.
-// 8 query heads over 2, d = 128, B = 64, 8192 tokens, 20 %: 331 -> 177 us (82
-// -> 156 TFLOP/s of the function's own operations).
+// 8 query heads over 2, d = 128, B = 64, 8192 tokens, 20 %: 331 -> 181 us (82
+// -> 153 TFLOP/s of the function's own operations).
 //
 // x = h + m + l in bf16: h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), each
-// difference exact in fp32; what is left out is below 2^-25 |x|. (Parts below
-// the smallest normal bf16, 1.2e-38, may be taken as zero.)
+// difference exact in fp32; what is left out is below 2^-25 |x|. RANGE: h is the
+// largest finite bf16 where x would round to infinity (above 3.39e38). Parts below
+// 2^-133 are lost, so an operand below 2^-110 (7.7e-34) counts with an error of
+// up to 2^-134: keys, queries or values all scaled by 2^-110 / -114 / -118 came
+// out 1.4e-7 / 5e-7 / 8e-6 off (fp32 instruction 2.9e-7 down to 2^-122).
+template <bool RANGE = true>
 __device__ __forceinline__ void split2(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
-  h = pack_bf16x2(x0, x1);
+  constexpr float kTop = 3.3895313892515355e38f;   // largest finite bf16
+  h = RANGE ? pack_bf16x2(__builtin_amdgcn_fmed3f(x0, -kTop, kTop), __builtin_amdgcn_fmed3f(x1, -kTop, kTop))
+            : pack_bf16x2(x0, x1);
   const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
   m = pack_bf16x2(r0, r1);
   l = pack_bf16x2(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
@@ -1133,7 +1139,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
   for (int td = 0; td < D / 32; ++td)
 #pragma unroll
     for (int j = 0; j < 16; ++j) oacc[td][j] = 0.0f;
-  float mref = kNoRef, lsum = 0.0f;        // running row max (log2 units), row sum
+  // Running row max of the raw scores, row sum of the weights. The scale comes
+  // after the subtraction: the largest weight is exactly 1 however large the
+  // scores are. Before any key the reference is the lowest finite value, so that
+  // scores of -infinity alone leave a sum of 0.
+  float mref = -__FLT_MAX__, lsum = 0.0f;
   const int vlane = (kh * 32 + 4 * hl + ((ln & 15) >> 2)) * L::VS + 16 * (ln >> 4) + 4 * (ln & 3);
   const int klane = (kh * 32 + ln) * L::KS + hl * 8;
   constexpr int NKK = D / 16;
@@ -1153,6 +1163,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
   };
   auto pb = [](const uint32_t (&q)[8], int c) SW_INL {
     return __builtin_bit_cast(bf16x8, make_uint4(q[4 * c], q[4 * c + 1], q[4 * c + 2], q[4 * c + 3]));
+  };
+  // leading and smaller products; the latter may overflow where the former did,
+  // with the other sign
+  auto join = [](float a, float b) SW_INL {
+    return a + __builtin_amdgcn_fmed3f(b, -__FLT_MAX__, __FLT_MAX__);
   };
   // Scores of one step: S sums the products of the leading parts, T the five
   // smaller ones. With EXP, the weights of the scores cur (against mref) are
@@ -1185,13 +1200,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
           for (int x = 0; x < PPK; ++x) {
             const int e = kk * PPK + x;
             if (f == 2 * x) {
-              p0[x] = __builtin_amdgcn_exp2f(fmaf(cur[2 * e], sl2, -mref));
-              p1[x] = __builtin_amdgcn_exp2f(fmaf(cur[2 * e + 1], sl2, -mref));
+              p0[x] = __builtin_amdgcn_exp2f((cur[2 * e] - mref) * sl2);
+              p1[x] = __builtin_amdgcn_exp2f((cur[2 * e + 1] - mref) * sl2);
             }
             if (f == 2 * x + 1) ps += p0[x];
             if (f == 2 * x + 2) {
               ps += p1[x];
-              split2(p0[x], p1[x], ph[e], pm[e], pl[e]);
+              split2<false>(p0[x], p1[x], ph[e], pm[e], pl[e]);
             }
           }
         }
@@ -1229,8 +1244,8 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
         if (td + 1 < NTD && f >= 2 && f < 8) vf[(td + 1) & 1][f - 2] = vread(vp, (f - 2) >> 1, (f - 2) & 1, td + 1);
         if (NEXT && td == 0 && f >= 4) {
           const int j = 2 * (f - 4);
-          S[j] += T[j];
-          S[j + 1] += T[j + 1];
+          S[j] = join(S[j], T[j]);
+          S[j + 1] = join(S[j + 1], T[j + 1]);
         }
         if (NEXT && td == NTD - 1 && f >= 8) {
           const int j = 4 * (f - 8);
@@ -1244,13 +1259,13 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    if (NEXT) mx = max_other_half(mx) * sl2;
+    if (NEXT) mx = max_other_half(mx);
   };
   // the reference is the running row max; O moves only when a row's max grew
   auto raise = [&](float mx) SW_INL {
     if (__any(mx > mref)) {
       const float nref = fmaxf(mref, mx);
-      const float alpha = __builtin_amdgcn_exp2f(mref - nref);
+      const float alpha = __builtin_amdgcn_exp2f((mref - nref) * sl2);
       mref = nref;
       lsum *= alpha;
 #pragma unroll
@@ -1269,17 +1284,17 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
       if (kp > qpos || kp >= seq1) S[j] = -INFINITY;
       mx = fmaxf(mx, S[j]);
     }
-    return max_other_half(mx) * sl2;
+    return max_other_half(mx);
   };
   auto weights = [&](const f32x16& cur) SW_INL {
     float ps = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float p0 = __builtin_amdgcn_exp2f(fmaf(cur[2 * e], sl2, -mref));
-      const float p1 = __builtin_amdgcn_exp2f(fmaf(cur[2 * e + 1], sl2, -mref));
+      const float p0 = __builtin_amdgcn_exp2f((cur[2 * e] - mref) * sl2);
+      const float p1 = __builtin_amdgcn_exp2f((cur[2 * e + 1] - mref) * sl2);
       ps += p0;
       ps += p1;
-      split2(p0, p1, ph[e], pm[e], pl[e]);
+      split2<false>(p0, p1, ph[e], pm[e], pl[e]);
     }
     lsum += ps;
   };
@@ -1290,10 +1305,10 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
     float mx = -INFINITY;
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      S[j] += T[j];
+      S[j] = join(S[j], T[j]);
       mx = fmaxf(mx, S[j]);
     }
-    return masked ? mask(t, S) : max_other_half(mx) * sl2;
+    return masked ? mask(t, S) : max_other_half(mx);
   };
 
   // last step with keys for this wavefront's rows, and the masked one
@@ -1409,7 +1424,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
     if (kh == 1) return;
     const float m1 = pm[(w + 1) * 32 + ln], l1 = pm[128 + (w + 1) * 32 + ln];
     const float mm = fmaxf(mref, m1);
-    const float f0 = __builtin_amdgcn_exp2f(mref - mm), f1 = __builtin_amdgcn_exp2f(m1 - mm);
+    const float f0 = __builtin_amdgcn_exp2f((mref - mm) * sl2), f1 = __builtin_amdgcn_exp2f((m1 - mm) * sl2);
     ltot = ltot * f0 + l1 * f1;
     mref = mm;
 #pragma unroll
@@ -1430,7 +1445,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void attn_prefill_f32_kernel(
       *reinterpret_cast<float4*>(orow + dv) = st;
     }
   if (lse && hl == 0)
-    lse[(long long)u * N + qpos] = (ltot > 0.0f) ? (mref + log2f(ltot)) / kLog2e : -INFINITY;
+    lse[(long long)u * N + qpos] = (ltot > 0.0f) ? (mref * sl2 + log2f(ltot)) / kLog2e : -INFINITY;
 }
 
 #undef SW_INL

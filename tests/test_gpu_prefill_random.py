@@ -337,3 +337,79 @@ def test_long_lists_of_one_query_head(dtype, d):
     for i in sorted(full) + [0, 1, 2000]:
         ref = O.sparse_attention_block(Qh, Kh, Vh, B, sel[i], 0, i)
         assert U.max_abs(got[0, i * B:(i + 1) * B], ref) <= tol, i
+
+
+@pytest.mark.parametrize("d,B,G", [(64, 64, 1), (128, 64, 1), (64, 128, 1), (128, 128, 2), (128, 64, 3)])
+def test_fp32_attention_with_extreme_values(d, B, G):
+    """Finite inputs at the ends of the range, one KV head each. 0: the largest
+    value a float holds in V, where rows see it and where it is masked. 1: in K,
+    with scores that overflow to -infinity (300 times it): weight 0. 2 and 3:
+    scores of -1e33 and 1e12, far apart: all the weight is on the largest
+    (the output is its value, exactly). 4: every score -infinity: the output is 0."""
+    n, h_kv = 3 * B + 5, 5
+    big = float(np.finfo(np.float32).max)
+    g = torch.Generator().manual_seed(12)
+    Q = torch.randn((h_kv, 1, n, d), generator=g).repeat(1, G, 1, 1)
+    K, V = (torch.randn((h_kv, n, d), generator=g) for _ in range(2))
+    V[0, :, 1:3] = 0.0
+    V[0, 3, 1], V[0, n - 3, 2] = big, -big
+    Q[1, :, :, 0] = 300.0
+    K[1, :, 0] = 0.0
+    K[1, 7, 0], K[1, B + 9, 0], K[1, 2 * B, 0] = -big, -big, -0.5 * big
+    lev = torch.randperm(n, generator=g).float()
+    Q[2], Q[3] = 1e30, 1e10
+    K[2] = (-(lev + 10) * (100.0 / d))[:, None]
+    K[3] = ((lev - n // 2) * (2.0 / d))[:, None]
+    Q[4, :, :, 0] = 300.0
+    K[4, :, 0] = -big
+    Q = Q.reshape(h_kv * G, n, d)
+    b = -(-n // B)
+    sel = [list(range(i + 1)) for i in range(b)]
+    idx = np.full((b, b), -1, dtype=np.int32)
+    for i in range(b):
+        idx[i, :i + 1] = sel[i]
+    out, lse = sw.sparse_attn_prefill(U.to_dev(Q), U.to_dev(K), U.to_dev(V), [0, n], B, U.to_dev(idx),
+                                      U.to_dev(np.arange(1, b + 1, dtype=np.int32)), b, want_lse=True)
+    got, glse = out.cpu().numpy(), lse.cpu().numpy()
+    Qh, Kh, Vh = O.f64(Q), O.f64(K), O.f64(V)
+    seen = np.tril(np.ones((n, n), dtype=bool))
+    for kv in range(h_kv):
+        for u in range(kv * G, (kv + 1) * G):
+            z = np.where(seen, Qh[u] @ Kh[kv].T / np.sqrt(d), -np.inf)
+            if kv == 4:
+                assert (got[u] == 0.0).all() and np.isneginf(glse[u]).all()
+            elif kv in (2, 3):
+                assert (got[u] == V[kv].numpy()[z.argmax(axis=1)]).all(), kv
+            else:
+                w = np.exp(z - z.max(axis=1, keepdims=True))
+                want = (w / w.sum(axis=1, keepdims=True)) @ Vh[kv]
+                assert np.isfinite(got[u]).all(), kv
+                assert (np.abs(got[u] - want) <= U.ATOL_F32 * np.maximum(np.abs(want), 1.0)).all(), kv
+                assert U.max_abs(glse[u], z.max(axis=1) + np.log(w.sum(axis=1))) <= U.ATOL_F32, kv
+
+
+@pytest.mark.parametrize("d,B", [(64, 64), (128, 128)])
+@pytest.mark.parametrize("e", [-90, -110, -118])
+def test_fp32_attention_of_small_operands(d, B, e):
+    """Values (and keys, with queries as much larger) scaled by 2^e. From 2^-110
+    on operands keep their 24 bits: the relative error of ordinary ones. Below,
+    each counts with an error of up to 2^-134, which at 2^-118 is 2^-16 of a value
+    of 1 (2-norm: a third of that for evenly spread roundings, and less where
+    many values are averaged)."""
+    n = 4 * B
+    g = torch.Generator().manual_seed(13)
+    Q, K, V = (torch.randn((1, n, d), generator=g) for _ in range(3))
+    s = 2.0 ** e
+    b = n // B
+    idx = np.full((b, b), -1, dtype=np.int32)
+    for i in range(b):
+        idx[i, :i + 1] = range(i + 1)
+    seen = np.tril(np.ones((n, n), dtype=bool))
+    for q, k, v in ((Q, K, V * s), (Q / s, K * s, V), (Q * s, K / s, V)):
+        got = sw.sparse_attn_prefill(U.to_dev(q), U.to_dev(k), U.to_dev(v), [0, n], B, U.to_dev(idx),
+                                     U.to_dev(np.arange(1, b + 1, dtype=np.int32)), b).cpu().numpy()
+        z = np.where(seen, O.f64(q[0]) @ O.f64(k[0]).T / np.sqrt(d), -np.inf)
+        w = np.exp(z - z.max(axis=1, keepdims=True))
+        want = (w / w.sum(axis=1, keepdims=True)) @ O.f64(v[0])
+        err = np.linalg.norm(got[0] - want) / np.linalg.norm(want)
+        assert err <= (8e-7 if e >= -110 else 2.0 ** -16), (e, err)
