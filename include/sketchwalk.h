@@ -112,8 +112,9 @@ int sw_select_max_count(int n_seqs, const int32_t* cu_seqlens /* [host] */, int 
  * [nb][d] block means (optional, may be NULL).
  * workspace: optional. With sw_sketch_workspace_bytes(...) bytes, 256-byte
  * aligned, few block rows are summed by several workgroups each (the query is
- * 0 where that would not help); with less, or NULL, by one each. The two
- * differ in the order of the fp64 sums. Its contents are scratch.
+ * 0 where that would not help with either type); with less, or NULL, by one
+ * each. The sums are taken in the same order: a sequence's outputs have the same
+ * bits with and without, alone and beside others. Its contents are scratch.
  */
 int sw_sketch_scores(int dtype, const void* Q, const void* K, int h_q, int h_kv, int d,
                      int n_seqs, const int32_t* cu_seqlens /* [host] */, int B,

@@ -8,13 +8,16 @@
 //                      tokens, applies the random signs, runs the
 //                      Walsh-Hadamard transform of the query mean and of the
 //                      key mean (one wavefront each, lane exchanges), samples
-//                      the columns and scales by 1/sqrt(r). Few block rows
-//                      are split over several workgroups each, which leave
-//                      their sums in the workspace, and
-//  sketch_parts_kernel adds them in order and goes on from there.
+//                      the columns and scales by 1/sqrt(r).
+//  pool_split_kernel   for few block rows: the work of each of a row's
+//                      wavefronts spread over a workgroup, which leaves its
+//                      sums in the workspace;
+//  sketch_parts_kernel adds them and goes on from there.
 //  scores_kernel       A = Qs Ks^T / sqrt(r) with fp64 MFMA 16x16x4 tiles,
 //                      causal mask, per-sequence max |A| by integer atomicMax
 //                      on the (non-negative) double bit pattern.
+#include <type_traits>
+
 #include "sw_common.h"
 #include "sw_internal.h"
 
@@ -33,7 +36,10 @@ constexpr int kPoolThreads = SW_POOL_THREADS;
 #ifndef SW_POOL_UNROLL
 #define SW_POOL_UNROLL 8
 #endif
-constexpr int kMaxParts = 16;            // workgroups a block row is split over
+constexpr int kPoolWaves = kPoolThreads / 64;
+#ifndef SW_POOL_AHEAD
+#define SW_POOL_AHEAD 32                 // loads in flight per thread of a split row
+#endif
 
 // The rest of a block row's sketch from the sums of its queries and keys
 // (thread t < d holds dimension t's): means, signs, the two transforms, the
@@ -67,24 +73,20 @@ __device__ __forceinline__ void finish_row(double sq, double sk, int row, int cn
   }
 }
 
-// SPLIT: blockIdx.y is the part of the row's (head, token) items; the sums go
-// to parts [row][part][query, key][d] and the sketch is left to
-// sketch_parts_kernel.
-template <typename T, bool SPLIT>
+template <typename T>
 __global__ __launch_bounds__(kPoolThreads) void pool_sketch_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, int h_q, int h_kv, int d, SeqMeta m,
     long long N, const int8_t* __restrict__ signs, const int32_t* __restrict__ cols, int r,
     double* __restrict__ Qs, double* __restrict__ Ks, double* __restrict__ Qbar,
-    double* __restrict__ Kbar, double* __restrict__ A_scale, double* __restrict__ parts) {
+    double* __restrict__ Kbar, double* __restrict__ A_scale) {
   constexpr int VEC = 16 / sizeof(T);
-  constexpr int NW = kPoolThreads / 64;
+  constexpr int NW = kPoolWaves;
   // per-wavefront sums of the query and key means, then (reused) the two
   // vectors the transforms work on
   __shared__ double red[2 * NW * 256];
   double* redq = red;
   double* redk = red + NW * 256;
   const int row = blockIdx.x;
-  const int part = SPLIT ? blockIdx.y : 0, np = SPLIT ? gridDim.y : 1;
   const int s = seq_of_block(m, row);
   const int i = row - m.blk_start[s];
   const int t0 = m.tok_start[s] + i * m.B;
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_sketch_kernel(
   const int slots = kPoolThreads / lpr;  // token rows in flight per pass
   const int lane = t % lpr;
   const int slot = t / lpr;
-  if (i == 0 && t == 0 && part == 0) A_scale[s] = 0.0;
+  if (i == 0 && t == 0) A_scale[s] = 0.0;
 
   auto add = [](double (&acc)[VEC], const T* p) {
     // non-temporal: Q and K are streamed once here
@@ -121,11 +123,9 @@ __global__ __launch_bounds__(kPoolThreads) void pool_sketch_kernel(
   // to 164 VGPRs instead of 92 and took twice the time)
   {
     const int n = h_q * cnt;
-    const int lo = SPLIT ? (int)((long long)n * part / np) : 0;
-    const int hi = SPLIT ? (int)((long long)n * (part + 1) / np) : n;
-    int h = (lo + slot) / cnt, tok = (lo + slot) % cnt;
+    int h = slot / cnt, tok = slot % cnt;
 _Pragma(SW_STR(unroll SW_POOL_UNROLL))
-    for (int it = lo + slot; it < hi; it += slots) {
+    for (int it = slot; it < n; it += slots) {
       add(aq, Q + ((long long)h * N + t0 + tok) * d + lane * VEC);
       h += dh;
       tok += dt;
@@ -137,11 +137,9 @@ _Pragma(SW_STR(unroll SW_POOL_UNROLL))
   }
   {
     const int n = h_kv * cnt;
-    const int lo = SPLIT ? (int)((long long)n * part / np) : 0;
-    const int hi = SPLIT ? (int)((long long)n * (part + 1) / np) : n;
-    int h = (lo + slot) / cnt, tok = (lo + slot) % cnt;
+    int h = slot / cnt, tok = slot % cnt;
 _Pragma(SW_STR(unroll SW_POOL_UNROLL))
-    for (int it = lo + slot; it < hi; it += slots) {
+    for (int it = slot; it < n; it += slots) {
       add(ak, K + ((long long)h * N + t0 + tok) * d + lane * VEC);
       h += dh;
       tok += dt;
@@ -175,43 +173,113 @@ _Pragma(SW_STR(unroll SW_POOL_UNROLL))
       sk += redk[w * d + t];
     }
   }
-  if constexpr (SPLIT) {
-    if (t < d) {
-      double* o = parts + ((long long)row * np + part) * 2 * d;
-      o[t] = sq;
-      o[d + t] = sk;
-    }
-    return;
-  }
   __syncthreads();                       // the sums are read; the vectors reuse them
   finish_row(sq, sk, row, cnt, h_q, h_kv, d, signs, cols, r, Qs, Ks, Qbar, Kbar, red);
 }
 
-// Block rows whose sums lie in np parts each: the parts added in order, then
-// the rest of the sketch.
+// The sums of wavefront blockIdx.y of pool_sketch_kernel's workgroup for a row,
+// by a workgroup of VEC / 2 times the threads: each takes two of the dimensions
+// of a slot and adds the slot's items in the same order, and the slots are added
+// in the order of the lane exchanges, so that a row's bits do not depend on which
+// of the kernels summed it. To parts [row][wavefront][query, key][d].
+template <typename T>
+__global__ __launch_bounds__(256) void pool_split_kernel(
+    const T* __restrict__ Q, const T* __restrict__ K, int h_q, int h_kv, int d, SeqMeta m,
+    long long N, double* __restrict__ A_scale, double* __restrict__ parts) {
+  constexpr int VEC = 16 / sizeof(T);
+  constexpr int NT = 32 * VEC;
+  typedef typename std::conditional<sizeof(T) == 2, uint32_t, unsigned long long>::type Pair;
+  __shared__ double red[4][NT];
+  const int row = blockIdx.x;
+  const int s = seq_of_block(m, row);
+  const int i = row - m.blk_start[s];
+  const int t0 = m.tok_start[s] + i * m.B;
+  const int cnt = min(m.tok_start[s + 1], t0 + m.B) - t0;
+  const int t = threadIdx.x;
+  const int wslots = 64 * VEC / d;       // slots of the wavefront
+  const int slots = kPoolWaves * wslots;
+  const int sl = t / (d / 2), dim = 2 * (t % (d / 2));
+  const int slot = blockIdx.y * wslots + sl;
+  if (i == 0 && t == 0 && blockIdx.y == 0) A_scale[s] = 0.0;
+  const int dh = slots / cnt, dt = slots % cnt;
+  auto sums = [&](double (&acc)[2], const T* X, int heads) {
+    acc[0] = acc[1] = 0.0;
+    const int n = heads * cnt;
+    int h = slot / cnt, tok = slot % cnt;
+    for (int it = slot; it < n; it += SW_POOL_AHEAD * slots) {
+      Pair v[SW_POOL_AHEAD];
+#pragma unroll
+      for (int u = 0; u < SW_POOL_AHEAD; ++u) {
+        // past the last item the loads are of other items and count as zeros
+        v[u] = __builtin_nontemporal_load(
+            reinterpret_cast<const Pair*>(X + ((long long)min(h, heads - 1) * N + t0 + tok) * d + dim));
+        h += dh;
+        tok += dt;
+        if (tok >= cnt) {
+          tok -= cnt;
+          ++h;
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);   // the loads stay together
+#pragma unroll
+      for (int u = 0; u < SW_POOL_AHEAD; ++u) {
+        const Pair x = it + u * slots < n ? v[u] : 0;
+        if constexpr (sizeof(T) == 2) {
+          acc[0] += (double)__uint_as_float(x << 16);
+          acc[1] += (double)__uint_as_float(x & 0xffff0000u);
+        } else {
+          acc[0] += (double)__uint_as_float((uint32_t)x);
+          acc[1] += (double)__uint_as_float((uint32_t)(x >> 32));
+        }
+      }
+    }
+  };
+  double aq[2], ak[2];
+  sums(aq, Q, h_q);
+  sums(ak, K, h_kv);
+  double* x[4] = {&red[0][t], &red[1][t], &red[2][t], &red[3][t]};
+  *x[0] = aq[0];
+  *x[1] = aq[1];
+  *x[2] = ak[0];
+  *x[3] = ak[1];
+  for (int off = 1; off < wslots; off <<= 1) {
+    __syncthreads();
+    if (sl % (2 * off) == 0)
+      for (int c = 0; c < 4; ++c) *x[c] += x[c][off * (d / 2)];
+  }
+  if (sl == 0) {                         // its own sums
+    double* o = parts + ((long long)row * kPoolWaves + blockIdx.y) * 2 * d + dim;
+    o[0] = *x[0];
+    o[1] = *x[1];
+    o[d] = *x[2];
+    o[d + 1] = *x[3];
+  }
+}
+
+// Block rows whose wavefronts' sums lie in parts: added in order, then the rest
+// of the sketch.
 __global__ __launch_bounds__(256) void sketch_parts_kernel(
-    const double* __restrict__ parts, int np, int h_q, int h_kv, int d, SeqMeta m,
+    const double* __restrict__ parts, int h_q, int h_kv, int d, SeqMeta m,
     const int8_t* __restrict__ signs, const int32_t* __restrict__ cols, int r,
     double* __restrict__ Qs, double* __restrict__ Ks, double* __restrict__ Qbar,
     double* __restrict__ Kbar) {
   __shared__ double x[2 * 256];
   const int row = blockIdx.x;
   const int t = threadIdx.x;
-  const double* p = parts + (long long)row * np * 2 * d + min(t, d - 1);
-  // every load goes out before the first sum (indices clamped, no condition)
-  double vq[kMaxParts], vk[kMaxParts];
+  const double* p = parts + (long long)row * kPoolWaves * 2 * d + min(t, d - 1);
+  // every load goes out before the first sum
+  double vq[kPoolWaves], vk[kPoolWaves];
 #pragma unroll
-  for (int i = 0; i < kMaxParts; ++i) {
-    vq[i] = p[(long long)min(i, np - 1) * 2 * d];
-    vk[i] = p[(long long)min(i, np - 1) * 2 * d + d];
+  for (int w = 0; w < kPoolWaves; ++w) {
+    vq[w] = p[w * 2 * d];
+    vk[w] = p[w * 2 * d + d];
   }
   double sq = 0.0, sk = 0.0;
 #pragma unroll
-  for (int i = 0; i < kMaxParts; ++i)
-    if (i < np) {
-      sq += vq[i];
-      sk += vk[i];
-    }
+  for (int w = 0; w < kPoolWaves; ++w) {
+    sq += vq[w];
+    sk += vk[w];
+  }
   const int s = seq_of_block(m, row);
   const int t0 = m.tok_start[s] + (row - m.blk_start[s]) * m.B;
   const int cnt = min(m.tok_start[s + 1], t0 + m.B) - t0;
@@ -308,47 +376,56 @@ __global__ __launch_bounds__(256) void scores_kernel(const double* __restrict__ 
   }
 }
 
-// Workgroups per block row. One workgroup streams about 50 GB/s, so from 128
-// rows on they reach what the memory gives (6.2 TB/s) and below that a call
-// took as long as its one row; split into about 256 workgroups, 32 heads + 8
-// of d = 128 with B = 128 take (with the block scores) 35.8 -> 15.6 us at 1000
-// tokens, 39.1 -> 20.0 at 4000, 40.9 -> 30.6 at 8000 and 41.2 -> 39.0 at 12000;
-// at 20000 (157 rows) it would be 42.9 -> 51.4. The launch that adds the parts
-// costs 3 us, which a row has to be worth: 80 KB rows went from 13.8 to 16.5.
-static int sketch_parts(int h_q, int h_kv, int d, int B, int64_t nb) {
-  const int64_t bytes = (int64_t)(h_q + h_kv) * B * d * 2;    // of a row in bf16
-  if (nb >= 128 || bytes < 256 * 1024) return 1;
-  const int64_t p = (256 + nb - 1) / nb;
-  return (int)(p > kMaxParts ? kMaxParts : p);
+// Whether few block rows are summed by a workgroup per wavefront. One workgroup
+// for a row streams about 50 GB/s, bound by the conversions and fp64 sums of its
+// eight wavefronts: below 128 rows a call takes as long as its one row, split it
+// takes two thirds and less. From 64 rows on the 4-byte loads per lane cost more
+// than the idle CUs, the later the larger the row (rows of bf16 / fp32; one
+// workgroup / split, us, with the block scores and the launch that adds the
+// parts):
+//   1.3 MB / 2.6 MB  8 rows 33.7 / 20.0, 50.8 / 27.0; 32: 40.2 / 22.2, 57.4 / 30.2;
+//                    94: 41.8 / 38.3, 63.1 / 53.3; 102: 41.9 / 45.2, 64.4 / 59.8
+//   0.66 / 1.3       62: 27.2 / 23.9, 36.2 / 29.7; 78: 27.3 / 28.7, 37.2 / 31.6;
+//                    94: 27.7 / 28.9, 37.8 / 34.5
+//   0.33 / 0.66      31: 24.0 / 17.1, 23.6 / 18.0; 62: 22.7 / 20.9, 24.2 / 23.3;
+//                    78: 22.4 / 24.0, 24.7 / 24.6
+// and 80 KB rows lose at any number (15.6 / 20.4 at 62).
+static bool sketch_split(int h_q, int h_kv, int d, int B, int64_t nb, int esz) {
+  const int64_t bytes = (int64_t)(h_q + h_kv) * B * d * esz;  // of a row
+  if (bytes < 128 * 1024 * esz) return false;
+  return nb <= 64 || (nb <= 96 && bytes >= 1024 * 1024) || (nb < 128 && bytes >= 2048 * 1024);
 }
 
 int64_t sketch_workspace_bytes(int h_q, int h_kv, int d, int B, int64_t nb) {
-  const int np = sketch_parts(h_q, h_kv, d, B, nb);
-  return np > 1 ? nb * np * 2 * d * (int64_t)sizeof(double) : 0;
+  // whichever type the call has
+  const bool split = sketch_split(h_q, h_kv, d, B, nb, 2) || sketch_split(h_q, h_kv, d, B, nb, 4);
+  return split ? nb * kPoolWaves * 2 * d * (int64_t)sizeof(double) : 0;
 }
 
 hipError_t launch_sketch(int dtype, const void* Q, const void* K, int h_q, int h_kv, int d,
                          const SeqMeta& meta, int64_t nb, long long N, const int8_t* signs,
                          const int32_t* cols, int r, double* Qs, double* Ks, double* A,
                          double* A_scale, double* Qbar, double* Kbar, void* ws, hipStream_t st) {
-  const int np = ws != nullptr ? sketch_parts(h_q, h_kv, d, meta.B, nb) : 1;
+  const dim3 grid((unsigned)nb);
+#define SW_POOL(T)                                                                                  \
+  do {                                                                                              \
+    auto q = reinterpret_cast<const T*>(Q);                                                         \
+    auto k = reinterpret_cast<const T*>(K);                                                         \
+    if (split)                                                                                      \
+      hipLaunchKernelGGL(pool_split_kernel<T>, dim3((unsigned)nb, kPoolWaves), dim3(512 / sizeof(T)), 0, \
+                         st, q, k, h_q, h_kv, d, meta, N, A_scale, parts);                          \
+    else                                                                                            \
+      hipLaunchKernelGGL(pool_sketch_kernel<T>, grid, dim3(kPoolThreads), 0, st, q, k, h_q, h_kv, d, \
+                         meta, N, signs, cols, r, Qs, Ks, Qbar, Kbar, A_scale);                     \
+  } while (0)
+  const bool split = ws != nullptr && sketch_split(h_q, h_kv, d, meta.B, nb, dtype == SW_BF16 ? 2 : 4);
   double* parts = static_cast<double*>(ws);
-  const dim3 grid((unsigned)nb, (unsigned)np);
-#define SW_POOL(T, SPLIT)                                                                         \
-  hipLaunchKernelGGL((pool_sketch_kernel<T, SPLIT>), grid, dim3(kPoolThreads), 0, st,             \
-                     reinterpret_cast<const T*>(Q), reinterpret_cast<const T*>(K), h_q, h_kv, d,  \
-                     meta, N, signs, cols, r, Qs, Ks, Qbar, Kbar, A_scale, parts)
-  if (dtype == SW_BF16) {
-    if (np > 1) SW_POOL(uint16_t, true);
-    else SW_POOL(uint16_t, false);
-  } else {
-    if (np > 1) SW_POOL(float, true);
-    else SW_POOL(float, false);
-  }
+  if (dtype == SW_BF16) SW_POOL(uint16_t);
+  else SW_POOL(float);
 #undef SW_POOL
-  if (np > 1)
-    hipLaunchKernelGGL(sketch_parts_kernel, dim3((unsigned)nb), dim3(256), 0, st, parts, np, h_q,
-                       h_kv, d, meta, signs, cols, r, Qs, Ks, Qbar, Kbar);
+  if (split)
+    hipLaunchKernelGGL(sketch_parts_kernel, grid, dim3(256), 0, st, parts, h_q, h_kv, d, meta, signs,
+                       cols, r, Qs, Ks, Qbar, Kbar);
   // tile prefix per sequence
   SeqMeta m2 = meta;
   int total = 0;

@@ -63,7 +63,7 @@ __host__ __device__ inline int cache_at(int b_max, int m, int j) {
 constexpr int kDecodeMaxSplits = 32;
 
 // Bytes with which launch_sketch splits few block rows over more workgroups
-// (0: it would not); without them (ws NULL) it does not split.
+// (0: it would not, whatever the type); without them (ws NULL) it does not split.
 int64_t sketch_workspace_bytes(int h_q, int h_kv, int d, int B, int64_t nb);
 
 hipError_t launch_sketch(int dtype, const void* Q, const void* K, int h_q, int h_kv, int d,

@@ -266,7 +266,9 @@ def test_outputs_are_deterministic():
 @pytest.mark.parametrize("dtype,h_q,h_kv,d,B,seqlens", [
     ("bf16", 32, 8, 128, 128, [700]),                  # 6 rows: 16 parts each
     ("bf16", 32, 8, 128, 128, [1, 130, 1029]),         # rows of 1, 2 and 5 tokens
-    ("bf16", 28, 4, 128, 128, [127 * 128]),            # the most rows that are split
+    ("bf16", 28, 4, 128, 128, [127 * 128]),            # the most rows with a workspace
+    ("bf16", 28, 4, 128, 128, [96 * 128]),             # the most that are split, each type
+    ("f32", 28, 4, 128, 128, [127 * 128]),
     ("f32", 32, 8, 64, 64, [2100]),
     ("bf16", 3, 1, 256, 1024, [2500])])
 def test_sketch_split_over_workgroups(dtype, h_q, h_kv, d, B, seqlens):
@@ -332,3 +334,41 @@ def test_walk_product_on_both_tile_sizes(blocks, s, relu):
         mx = np.abs(want).max(axis=1, keepdims=True)
         want = want / np.where(mx > 0, mx, 1.0)
         np.testing.assert_allclose(got, np.tril(want), rtol=0, atol=1e-12)
+
+
+@pytest.mark.parametrize("dtype,h_q,h_kv,d,B", [
+    ("bf16", 32, 8, 128, 128), ("f32", 32, 8, 128, 128), ("f32", 20, 4, 64, 128), ("bf16", 40, 8, 64, 128),
+    ("f32", 6, 2, 256, 128), ("bf16", 9, 3, 256, 128), ("f32", 32, 32, 16, 256), ("bf16", 64, 8, 16, 512)])
+def test_a_sequence_has_the_same_sketch_bits_in_any_batch(dtype, h_q, h_kv, d, B):
+    """A prompt's sketch is bit-identical alone (its rows split over workgroups),
+    alone without a workspace, and in a batch with too many rows to split.
+    Values of mixed magnitude, so that another order of the fp64 sums would show
+    in either type; a partial last block."""
+    r = min(64, d)
+    _, _, ts, tc = U.srht_dev(d, r, 6)
+    g = torch.Generator().manual_seed(18)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    lens = [5 * B + 77, 130 * B, 3]
+    N = sum(lens)
+    Q, K = ((torch.randn((h, N, d), generator=g) *
+             torch.exp2(torch.randint(-40, 1, (h, N, 1), generator=g).float())).to(td) for h in (h_q, h_kv))
+    cu = [0] + list(np.cumsum(lens).astype(int))
+    nb = 6
+    assert sw.sketch_workspace_bytes(h_q, h_kv, d, [0, lens[0]], B) > 0
+    assert sw.sketch_workspace_bytes(h_q, h_kv, d, cu, B) == 0
+    batch = sw.sketch_scores(U.to_dev(Q), U.to_dev(K), cu, B, ts, tc, want_means=True)
+    dQ, dK = U.to_dev(Q[:, :lens[0]]), U.to_dev(K[:, :lens[0]])
+    alone = sw.sketch_scores(dQ, dK, [0, lens[0]], B, ts, tc, want_means=True)
+    lib = sw.load()
+    ccu, n = sw._cu([0, lens[0]])
+    none = {k: torch.empty_like(v) for k, v in alone.items()}
+    rc = lib.sw_sketch_scores(sw._dtype_code(dQ), dQ.data_ptr(), dK.data_ptr(), h_q, h_kv, d, n, ccu, B,
+                              ts.data_ptr(), tc.data_ptr(), r, none["Qs"].data_ptr(), none["Ks"].data_ptr(),
+                              none["A"].data_ptr(), none["A_scale"].data_ptr(), none["Qbar"].data_ptr(),
+                              none["Kbar"].data_ptr(), None, 0, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, lib.sw_last_error()
+    torch.cuda.synchronize()
+    for k in alone:
+        assert torch.equal(alone[k], none[k]), k
+        part = batch[k][:{"A": nb * nb, "A_scale": 1}.get(k, nb)]
+        assert torch.equal(alone[k], part), k
