@@ -30,7 +30,8 @@
  * - Q is [h_q][N][d], K and V are [h_kv][N][d] (head-major, row-major,
  *   contiguous); h_q is a multiple of h_kv and query head u reads KV head
  *   u / (h_q / h_kv).
- * - Every output is deterministic: the same inputs give the same bits.
+ * - Every output is deterministic: the same inputs give the same bits. A
+ *   sequence's prefill outputs have the same bits alone and beside others.
  */
 #ifndef SKETCHWALK_H
 #define SKETCHWALK_H

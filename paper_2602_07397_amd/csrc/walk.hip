@@ -10,7 +10,8 @@
 //                       diagonal of C are not written outside the diagonal
 //                       tiles (the products never read them).
 //  walk_gemm32_kernel   the same over 32x32 tiles and eight wavefronts, for
-//                       long sequences
+//                       long sequences; walk_gemm_mixed_kernel for calls with
+//                       both
 //  walk_softmax_kernel  causal row softmax of t*A (the transition matrix of
 //                       the appendix lemma on the walk's stationary structure).
 //  walk_norm_kernel     divides each row by its largest magnitude and writes
@@ -20,7 +21,7 @@
 // Alg. 1 step 6, the same power after clipping negative scores to zero, or
 // the identity (the operand already holds weights). The matrix-power variant
 // (the within-layer multi-hop walk of Sec. 1 and Fig. 2) is built from
-// walk_gemm_kernel by binary exponentiation.
+// these products by binary exponentiation.
 #include "sw_common.h"
 #include "sw_internal.h"
 
@@ -110,17 +111,15 @@ __global__ __launch_bounds__(256) void walk_first_kernel(const double* __restric
 
 // Bounded by the launch and one chain of loads up to about 256 blocks, then by
 // the L2 reads (each operand entry is read for 16 rows or columns).
+// wave is the wavefront's number among the tile's four; store: false for four
+// that only keep the barrier.
 template <int F, bool S8>
-__global__ __launch_bounds__(256) void walk_gemm16_kernel(const double* __restrict__ A,
-                                                        const double* __restrict__ A_scale,
-                                                        int s_exp, SeqMeta m, int total_tiles,
-                                                        const double* __restrict__ Rp,
-                                                        double* __restrict__ R) {
-  __shared__ double red[4][64][4];
-  const int wave = threadIdx.x >> 6;
+__device__ __forceinline__ void gemm16_tile(const double* __restrict__ A,
+                                            const double* __restrict__ A_scale, int s_exp,
+                                            const SeqMeta& m, int tile, const double* __restrict__ Rp,
+                                            double* __restrict__ R, int wave, double (*red)[64][4],
+                                            bool store) {
   const int l = threadIdx.x & 63;
-  const int tile = blockIdx.x;
-  if (tile >= total_tiles) return;
   int s = 0;
   while (s + 1 < m.n_seqs && m.aux_start[s + 1] <= tile) ++s;
   const int b = m.blk_start[s + 1] - m.blk_start[s];
@@ -189,12 +188,22 @@ __global__ __launch_bounds__(256) void walk_gemm16_kernel(const double* __restri
 #pragma unroll
   for (int v = 0; v < 4; ++v) red[wave][l][v] = acc[v];
   __syncthreads();
-  if (wave != 0) return;
+  if (wave != 0 || !store) return;
   for (int v = 0; v < 4; ++v) {
     const double sum = ((red[0][l][v] + red[1][l][v]) + red[2][l][v]) + red[3][l][v];
     const int ri = ti * 16 + (l >> 4) + 4 * v, cj = tj * 16 + (l & 15);
     if (ri < b && cj < b) Rs[(long long)ri * b + cj] = (cj <= ri) ? sum : 0.0;
   }
+}
+
+template <int F, bool S8>
+__global__ __launch_bounds__(256) void walk_gemm16_kernel(const double* __restrict__ A,
+                                                        const double* __restrict__ A_scale,
+                                                        int s_exp, SeqMeta m,
+                                                        const double* __restrict__ Rp,
+                                                        double* __restrict__ R) {
+  __shared__ double red[4][64][4];
+  gemm16_tile<F, S8>(A, A_scale, s_exp, m, blockIdx.x, Rp, R, threadIdx.x >> 6, red, true);
 }
 
 // Four 16x16 products per wavefront and step share two A and two B operands, so
@@ -212,14 +221,12 @@ struct __attribute__((packed, aligned(8))) f64pair {   // two neighbours, 8-byte
 };
 
 template <int F, bool S8>
-__global__ __launch_bounds__(kGemmWaves * 64, 4) void walk_gemm32_kernel(
-    const double* __restrict__ A, const double* __restrict__ A_scale, int s_exp, SeqMeta m,
-    int total_tiles, const double* __restrict__ Rp, double* __restrict__ R) {
-  __shared__ double red[kGemmWaves][16][64];
+__device__ __forceinline__ void gemm32_tile(const double* __restrict__ A,
+                                            const double* __restrict__ A_scale, int s_exp,
+                                            const SeqMeta& m, int tile, const double* __restrict__ Rp,
+                                            double* __restrict__ R, double (*red)[16][64]) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l = threadIdx.x & 63;
-  const int tile = blockIdx.x;
-  if (tile >= total_tiles) return;
   int s = 0;
   while (s + 1 < m.n_seqs && m.aux_start[s + 1] <= tile) ++s;
   const int b = m.blk_start[s + 1] - m.blk_start[s];
@@ -245,8 +252,7 @@ __global__ __launch_bounds__(kGemmWaves * 64, 4) void walk_gemm32_kernel(
   // order), so the four groups read 64 consecutive bytes of an A row at a time
   // (with 8 consecutive entries per lane an instruction touched 64 pieces of
   // 16 bytes, and the CU's one address unit was the bound). Wavefront w takes
-  // chunks w, w + kGemmWaves, ...; its chunks are double-buffered in registers:
-  // the loads of the next chunk are in flight during the MFMAs of the current.
+  // chunks w, w + kGemmWaves, ...
   const int nc = ti - tj + 1;
   const long long row0 = (long long)min(ra, b - 1) * b, row1 = (long long)min(ra + 16, b - 1) * b;
   struct Chunk {
@@ -340,6 +346,33 @@ __global__ __launch_bounds__(kGemmWaves * 64, 4) void walk_gemm32_kernel(
   }
 }
 
+template <int F, bool S8>
+__global__ __launch_bounds__(kGemmWaves * 64, 4) void walk_gemm32_kernel(
+    const double* __restrict__ A, const double* __restrict__ A_scale, int s_exp, SeqMeta m,
+    const double* __restrict__ Rp, double* __restrict__ R) {
+  __shared__ double red[kGemmWaves][16][64];
+  gemm32_tile<F, S8>(A, A_scale, s_exp, m, blockIdx.x, Rp, R, red);
+}
+
+// Sequences of both kinds in one launch: the total32 tiles of 32 first, then the
+// total16 of 16, two per workgroup (three sequences of 600, 500 and 400 blocks:
+// 32 us with walk and selection, 39 in two launches, 29 all on tiles of 32).
+template <int F, bool S8>
+__global__ __launch_bounds__(kGemmWaves * 64, 4) void walk_gemm_mixed_kernel(
+    const double* __restrict__ A, const double* __restrict__ A_scale, int s_exp, SeqMeta m32,
+    int total32, SeqMeta m16, int total16, const double* __restrict__ Rp, double* __restrict__ R) {
+  __shared__ double red[kGemmWaves][16][64];
+  if ((int)blockIdx.x < total32) {
+    gemm32_tile<F, S8>(A, A_scale, s_exp, m32, blockIdx.x, Rp, R, red);
+    return;
+  }
+  const int wave = threadIdx.x >> 6, half = wave >> 2;
+  const int tile = 2 * ((int)blockIdx.x - total32) + half;
+  auto red16 = reinterpret_cast<double(*)[64][4]>(&red[0][0][0]) + 4 * half;
+  gemm16_tile<F, S8>(A, A_scale, s_exp, m16, min(tile, total16 - 1), Rp, R, wave & 3, red16,
+                     tile < total16);
+}
+
 // Row i of W: exp(t A[i,j] - max) / sum over the causal blocks j <= i; zeros
 // above the diagonal. The exponentials are stored, then scaled by 1/sum by
 // the same thread that wrote them.
@@ -383,19 +416,27 @@ __global__ __launch_bounds__(256) void walk_norm_kernel(SeqMeta m, double* __res
 
 namespace {
 
-// Edge of the output tiles. Measured (walk and selection, 16 / 32): 13.2 / 14.3
-// us at 256 blocks, 18.7 / 19.1 at 512, 39.7 / 35.2 at 1000.
-int gemm_edge(const SeqMeta& meta) { return meta.max_b > 512 ? kGemmTile : 16; }
+// Edge of a sequence's output tiles. Measured (walk and selection, 16 / 32): 13.2
+// / 14.3 us at 256 blocks, 18.7 / 19.1 at 512, 39.7 / 35.2 at 1000. The two take
+// a tile's sums in different orders; by the sequence's own length, its bits do
+// not depend on what else is in the call.
+int gemm_edge(int b) { return b > 512 ? kGemmTile : 16; }
 
-int gemm_tiles(const SeqMeta& meta, SeqMeta* m2) {
+// The tiles of the sequences with edge 16 and of those with edge 32, each in
+// aux_start of its own copy of the layout.
+struct GemmTiles {
+  SeqMeta m16, m32;
+  int total16, total32;
+};
+
+int count_tiles(const SeqMeta& meta, int edge, SeqMeta* m2) {
   *m2 = meta;
-  const int edge = gemm_edge(meta);
   int total = 0;
   for (int s = 0; s < meta.n_seqs; ++s) {
     m2->aux_start[s] = total;
     const int b = meta.blk_start[s + 1] - meta.blk_start[s];
     const int tb = (b + edge - 1) / edge;
-    total += tb * (tb + 1) / 2;
+    if (gemm_edge(b) == edge) total += tb * (tb + 1) / 2;
   }
   m2->aux_start[meta.n_seqs] = total;
   return total;
@@ -404,23 +445,27 @@ int gemm_tiles(const SeqMeta& meta, SeqMeta* m2) {
 // C = X W(Y): X, Y, C lower triangular per sequence; only the lower
 // triangle of C (and the diagonal tiles) is written.
 template <int F, bool S8>
-void gemm_s(const double* X, const double* Y, const double* A_scale, int s_exp, const SeqMeta& m2,
-            int total, double* C, hipStream_t st) {
-  if (gemm_edge(m2) == kGemmTile)
-    hipLaunchKernelGGL((walk_gemm32_kernel<F, S8>), dim3((unsigned)total), dim3(kGemmWaves * 64), 0,
-                       st, Y, A_scale, s_exp, m2, total, X, C);
+void gemm_s(const double* X, const double* Y, const double* A_scale, int s_exp, const GemmTiles& g,
+            double* C, hipStream_t st) {
+  if (g.total16 == 0)
+    hipLaunchKernelGGL((walk_gemm32_kernel<F, S8>), dim3((unsigned)g.total32), dim3(kGemmWaves * 64), 0,
+                       st, Y, A_scale, s_exp, g.m32, X, C);
+  else if (g.total32 == 0)
+    hipLaunchKernelGGL((walk_gemm16_kernel<F, S8>), dim3((unsigned)g.total16), dim3(256), 0, st, Y,
+                       A_scale, s_exp, g.m16, X, C);
   else
-    hipLaunchKernelGGL((walk_gemm16_kernel<F, S8>), dim3((unsigned)total), dim3(256), 0, st, Y,
-                       A_scale, s_exp, m2, total, X, C);
+    hipLaunchKernelGGL((walk_gemm_mixed_kernel<F, S8>), dim3((unsigned)(g.total32 + (g.total16 + 1) / 2)),
+                       dim3(kGemmWaves * 64), 0, st, Y, A_scale, s_exp, g.m32, g.total32, g.m16, g.total16,
+                       X, C);
 }
 
 template <int F>
-void gemm(const double* X, const double* Y, const double* A_scale, int s_exp, const SeqMeta& m2,
-          int total, double* C, hipStream_t st) {
+void gemm(const double* X, const double* Y, const double* A_scale, int s_exp, const GemmTiles& g,
+          double* C, hipStream_t st) {
   if (s_exp == 8 && F != kWIdent)
-    gemm_s<F, F != kWIdent>(X, Y, A_scale, s_exp, m2, total, C, st);
+    gemm_s<F, F != kWIdent>(X, Y, A_scale, s_exp, g, C, st);
   else
-    gemm_s<F, false>(X, Y, A_scale, s_exp, m2, total, C, st);
+    gemm_s<F, false>(X, Y, A_scale, s_exp, g, C, st);
 }
 
 }  // namespace
@@ -435,8 +480,9 @@ hipError_t launch_walk(int variant, const double* A, const double* A_scale, int 
                        double logit_scale, const SeqMeta& meta, int64_t nb, const double* R_prev,
                        double* R_out, double* ws, hipStream_t st) {
   const dim3 rows((unsigned)nb), blk(256);
-  SeqMeta m2;
-  const int total = gemm_tiles(meta, &m2);
+  GemmTiles g;
+  g.total16 = count_tiles(meta, 16, &g.m16);
+  g.total32 = count_tiles(meta, kGemmTile, &g.m32);
   if (variant == SW_WALK_MATPOW && s_exp == 1) variant = SW_WALK_POWER;  // X^1 = X
   switch (variant) {
     case SW_WALK_POWER:
@@ -451,14 +497,14 @@ hipError_t launch_walk(int variant, const double* A, const double* A_scale, int 
         return hipGetLastError();
       }
       if (variant == SW_WALK_POWER)
-        gemm<kWPow>(R_prev, A, A_scale, s_exp, m2, total, R_out, st);
+        gemm<kWPow>(R_prev, A, A_scale, s_exp, g, R_out, st);
       else
-        gemm<kWRelu>(R_prev, A, A_scale, s_exp, m2, total, R_out, st);
+        gemm<kWRelu>(R_prev, A, A_scale, s_exp, g, R_out, st);
       break;
     case SW_WALK_SOFTMAX: {
       double* W = R_prev == nullptr ? R_out : ws;
       hipLaunchKernelGGL(walk_softmax_kernel, rows, blk, 0, st, A, logit_scale, meta, W);
-      if (R_prev != nullptr) gemm<kWIdent>(R_prev, W, nullptr, 1, m2, total, R_out, st);
+      if (R_prev != nullptr) gemm<kWIdent>(R_prev, W, nullptr, 1, g, R_out, st);
       break;
     }
     case SW_WALK_MATPOW: {
@@ -481,14 +527,14 @@ hipError_t launch_walk(int variant, const double* A, const double* A_scale, int 
           const bool last = ++k == nprod;
           double* dst = (last && R_prev == nullptr) ? R_out : buf[1 - ci];
           if (step == 0)
-            gemm<kWIdent>(cur, cur, nullptr, 1, m2, total, dst, st);
+            gemm<kWIdent>(cur, cur, nullptr, 1, g, dst, st);
           else
-            gemm<kWPow>(cur, A, A_scale, 1, m2, total, dst, st);
+            gemm<kWPow>(cur, A, A_scale, 1, g, dst, st);
           cur = dst;
           ci = 1 - ci;
         }
       }
-      if (R_prev != nullptr) gemm<kWIdent>(R_prev, cur, nullptr, 1, m2, total, R_out, st);
+      if (R_prev != nullptr) gemm<kWIdent>(R_prev, cur, nullptr, 1, g, R_out, st);
       break;
     }
     default:

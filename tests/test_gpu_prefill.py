@@ -372,3 +372,24 @@ def test_a_sequence_has_the_same_sketch_bits_in_any_batch(dtype, h_q, h_kv, d, B
         assert torch.equal(alone[k], none[k]), k
         part = batch[k][:{"A": nb * nb, "A_scale": 1}.get(k, nb)]
         assert torch.equal(alone[k], part), k
+
+
+@pytest.mark.parametrize("variant,s", [(sw.WALK_POWER, 8), (sw.WALK_RELU, 3), (sw.WALK_SOFTMAX, 8),
+                                       (sw.WALK_MATPOW, 3)])
+def test_a_sequence_has_the_same_walk_bits_in_any_batch(variant, s):
+    """Sequences on both sides of the 512 blocks where the product's tiles
+    change, each alone and all in one call (which runs both tile sizes)."""
+    B, blocks = 16, [40, 530, 512, 513, 1]
+    rng = np.random.default_rng(60 + variant)
+    A = [np.tril(rng.normal(size=(b, b))) for b in blocks]
+    P = [np.tril(rng.normal(size=(b, b))) for b in blocks]
+    c = np.array([np.abs(a).max() for a in A])
+    flat = [U.to_dev(np.concatenate([x.ravel() for x in m])) for m in (A, P)]
+    cu = [0] + list(np.cumsum([B * b for b in blocks]).astype(int))
+    R = sw.walk_update_variant(variant, flat[0], U.to_dev(c), s, cu, B, R_prev=flat[1], logit_scale=0.7)
+    at = 0
+    for i, b in enumerate(blocks):
+        one = sw.walk_update_variant(variant, U.to_dev(A[i].ravel()), U.to_dev(c[i:i + 1]), s, [0, B * b], B,
+                                     R_prev=U.to_dev(P[i].ravel()), logit_scale=0.7)
+        assert torch.equal(one, R[at:at + b * b]), b
+        at += b * b
