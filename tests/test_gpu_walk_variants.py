@@ -5,6 +5,7 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
 import synth
@@ -147,3 +148,38 @@ def test_decode_softmax_and_matpow_are_unsupported():
     for v in (sw.WALK_SOFTMAX, sw.WALK_MATPOW):
         with pytest.raises(sw.SketchWalkError, match="code 2"):
             sw.walk_update_decode_variant(v, state, 1, 64, 16, 4, 16, pos, 8)
+
+
+@pytest.mark.parametrize("blocks", [[513], [545, 17, 1], [512, 40], [33]])
+@pytest.mark.parametrize("variant,s", [(sw.WALK_SOFTMAX, 8), (sw.WALK_MATPOW, 2), (sw.WALK_MATPOW, 3),
+                                       (sw.WALK_MATPOW, 8)])
+@pytest.mark.parametrize("first", [True, False])
+def test_softmax_and_matrix_power_on_both_tile_sizes(blocks, variant, s, first):
+    """The chained products of the matrix power and the softmax transition on
+    each side of 512 blocks, alone and mixed, into a workspace full of NaN: a
+    read of an entry that no product wrote would show."""
+    B = 16
+    rng = np.random.default_rng(400 + blocks[0] + s)
+    cu = synth.cu_seqlens([b * B for b in blocks])
+    A = [np.tril(rng.normal(size=(b, b))) for b in blocks]
+    P = [None if first else np.tril(rng.normal(size=(b, b))) for b in blocks]
+    P = [None if p is None else p / np.abs(p).max(axis=1, keepdims=True) for p in P]
+    c = np.array([O.score_scale(a) for a in A])
+    t = 0.7
+    need = int(sw.load().sw_walk_workspace_bytes(variant, len(blocks), sw._cu(cu)[0], B))
+    ws = torch.full((max(need // 8, 1),), float("nan"), dtype=torch.float64, device=U.DEV)
+    nm = sum(b * b for b in blocks)
+    R = torch.full((nm,), float("nan"), dtype=torch.float64, device=U.DEV)
+    dA, dc = U.to_dev(np.concatenate([a.ravel() for a in A])), U.to_dev(c)
+    dP = None if first else U.to_dev(np.concatenate([p.ravel() for p in P]))
+    rc = sw.load().sw_walk_update_variant(
+        variant, dA.data_ptr(), dc.data_ptr(), s, t, len(blocks), sw._cu(cu)[0], B,
+        None if first else dP.data_ptr(), R.data_ptr(), ws.data_ptr(), need,
+        torch.cuda.current_stream().cuda_stream)
+    assert rc == 0, sw.load().sw_last_error()
+    for got, a, p, cc in zip(U.split_mats(R.cpu().numpy(), cu, B), A, P, c):
+        ref = O.walk_step(p, O.walk_weights_variant(ORACLE_VARIANT[variant], a, cc, s, t))
+        assert np.all(np.triu(got, 1) == 0.0)
+        err = np.max(np.abs(got - ref), axis=1)
+        tol = _matpow_row_tol(a, cc, s, p) if variant == sw.WALK_MATPOW else 1e-12
+        assert np.all(err <= tol), (err.max(), np.max(err / tol))
