@@ -864,9 +864,10 @@ def run_walk_variants(args, dev) -> dict:
                 sw.walk_update_variant(v, sks[1]["A"], sks[1]["A_scale"], w.s, cu, B, R0, R1,
                                        logit_scale=t, workspace=ws)
 
-            step()
+            reps = 200
+            for _ in range(10 * reps):   # the clocks are down after the inputs
+                step()
             torch.cuda.synchronize(dev)
-            reps = 50
             e0 = torch.cuda.Event(enable_timing=True)
             e1 = torch.cuda.Event(enable_timing=True)
             e0.record(stream)

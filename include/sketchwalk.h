@@ -199,8 +199,8 @@ int sw_select_topk_blocks(const double* R, int n_seqs, const int32_t* cu_seqlens
  * dtype SW_BF16 or SW_F32; d in {64, 128}; B in {64, 128} (other values
  * return SW_ERR_UNSUPPORTED). O [h_q][N][d] in the input dtype. lse [h_q][N] float32
  * natural-log sum-exp of the scaled logits (optional, may be NULL).
- * idx/cnt as written by sw_select_topk_blocks (block indices ascending,
- * each <= its row's block index; entries outside [0, i] are skipped and
+ * idx/cnt as written by sw_select_topk_blocks (block indices ascending, each
+ * at most once and <= its row's block index; entries outside [0, i] are skipped and
  * cnt is clamped to kmax, so malformed selections cannot read out of
  * bounds).
  * SW_F32: Q, K and V count to their 24 bits from 2^-110 (7.7e-34) in magnitude
@@ -328,6 +328,8 @@ int64_t sw_decode_attn_workspace_bytes(int batch, int h_q, int h_kv, int d);
  * [batch][h_kv][T_max][d]; O [batch][h_q][d] in the input dtype.
  * G = h_q / h_kv in {1, 2, 4, 8}; d in {64, 128}; B a multiple of 16 in
  * [16, 1024] (SW_ERR_INVALID_ARG otherwise); scale <= 0 -> 1/sqrt(d).
+ * SW_BF16 takes the first SW_MAX_BLOCKS entries of a row and block numbers up
+ * to 32767; SW_F32 has no such limits.
  */
 int sw_sparse_attn_decode(int dtype, const void* q, const void* Kc, const void* Vc, int batch,
                           int h_q, int h_kv, int d, int T_max, int B, const int32_t* pos,

@@ -330,11 +330,12 @@ __global__ __launch_bounds__(256) void attn_decode_mfma_kernel(
 //                   ln D / 16 .. + D / 16 - 1 it loaded of the key's value row
 //                   as the A operand of the t-th product, whose row m is dim
 //                   m D / 16 + t. No exchange, no LDS.
-// Bounded by the reads: 6.1 to 6.4 TB/s at 512 blocks of 64 (32 query heads over
-// 8, d = 128, batch 4 and 16; 285 -> 174 and 1118 -> 675 us), where products on
-// the vector unit, a 64-bit division per token and no load in flight during the
-// math gave 3.8. The logits are added as a tree and each group's sums enter the
-// running ones once, so that nothing is less exact than it was (relative error
+// Bounded by the reads: 5.9 and 6.4 TB/s at 512 blocks of 64 (32 query heads over
+// 8, d = 128, batch 4 and 16; 291 -> 183 and 1115 -> 675 us; at 103 blocks and
+// batch 4 5.2, the start and end of one round), the matrix cores 23 % busy.
+// Products on the vector unit, a 64-bit division per token and no load in
+// flight during the math gave 3.8 TB/s. The logits are added as a tree and each
+// group's sums enter the running ones once, so that nothing is less exact than it was (relative error
 // against 64 bits 1.8e-7 on average over four shapes, 1.9e-7 before; one chain
 // of products per logit gave 3.5 times the error at logits of several hundred).
 template <int D>

@@ -850,8 +850,8 @@ __device__ __forceinline__ void walk_column(const char* __restrict__ state, int 
 // launch is latency (6.2 us at 513 blocks and batch 1, about 13 us at 1025
 // blocks and batch 16, where the walk reads 34 MB). With the sketch of all
 // layers in one launch and the attention of several in another, a step takes
-// 412 us instead of 1165 (batch 1, 32768 tokens, 32 layers; four launches per
-// layer before), and 1166 instead of 1318 (batch 16, 65536 tokens, 8 layers).
+// 410 us instead of 1169 (batch 1, 32768 tokens, 32 layers; four launches per
+// layer before), and 1165 instead of 1291 (batch 16, 65536 tokens, 8 layers).
 struct ChainArgs {
   const char* state;       // of layer l
   const int32_t* pos;
