@@ -45,10 +45,10 @@ PEAK_HBM_GBS = 8000.0
 # measured on: a changed source reports null.
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 MEASURED_TRAFFIC = {
-    "attn_prefill.hip": ("47415f5f57de4fb646bc708d878452ee5cdc0aca891f005a5c397df262d704b5",
-                         334359.2 * 1024, 262144.0 * 1024),
-    "attn_decode.hip": ("550fcd2958fbc46480c1ad2aebcc9a22cc1694d335bb001ee2edca197fb82cac",
-                        419787.5 * 1024, 1088.0 * 1024),
+    "attn_prefill.hip": ("dfe99494c1becd3ff3918f9f1daf01d0228e312492e4ab08db76746346ca15de",
+                         334394.3 * 1024, 262144.0 * 1024),
+    "attn_decode.hip": ("5564fea1b240cb604b52d03e4c5e89a73767066367b689a084f915fd579b4fc2",
+                        419962.8 * 1024, 1088.0 * 1024),
 }
 
 
