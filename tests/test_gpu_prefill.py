@@ -393,3 +393,44 @@ def test_a_sequence_has_the_same_walk_bits_in_any_batch(variant, s):
                                      R_prev=U.to_dev(P[i].ravel()), logit_scale=0.7)
         assert torch.equal(one, R[at:at + b * b]), b
         at += b * b
+
+
+@pytest.mark.parametrize("dtype,h_q,h_kv,d,B,lens", [
+    ("bf16", 28, 4, 128, 128, [2500, 150 * 128, 77]),     # alone below 640 groups, then heads divided
+    ("bf16", 21, 1, 128, 64, [1000, 640 * 64]),           # the same with one head left over
+    ("bf16", 32, 8, 128, 128, [700, 9000]),               # alone below one launch of the chip
+    ("bf16", 8, 8, 64, 64, [1500, 530 * 64]),             # walk tiles of both kinds
+    ("f32", 8, 2, 128, 64, [1300, 5000, 900]),
+    ("f32", 4, 4, 64, 64, [700, 3000])])
+def test_a_prompt_has_the_same_bits_alone_and_in_a_batch(dtype, h_q, h_kv, d, B, lens):
+    """Two layers (sketch, walk, selection, attention with lse) of a prompt by
+    itself and as the first of a batch that takes other launches: every output
+    bit for bit."""
+    r = min(64, d)
+    _, _, ts, tc = U.srht_dev(d, r, 6)
+    g = torch.Generator().manual_seed(19)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    N, n = sum(lens), lens[0]
+    cu = [0] + list(np.cumsum(lens).astype(int))
+    b = -(-n // B)
+    R1 = R2 = None
+    for _ in range(2):
+        Q, K, V = (torch.randn((h, N, d), generator=g).to(td) for h in (h_q, h_kv, h_kv))
+        K[:, ::3] *= 2.0
+        out = []
+        for x, c, R in ((n, [0, n], R1), (N, cu, R2)):
+            q, k, v = (U.to_dev(t[:, :x]) for t in (Q, K, V))
+            o = sw.sketch_scores(q, k, c, B, ts, tc, want_means=True)
+            o["R"] = sw.walk_update(o["A"], o["A_scale"], 8, c, B, R)
+            o["idx"], o["cnt"], kmax = sw.select_topk_blocks(o["R"], c, B, density_pct=30)
+            o["O"], o["lse"] = sw.sparse_attn_prefill(q, k, v, c, B, o["idx"], o["cnt"], kmax, want_lse=True)
+            out.append(o)
+        one, many = out
+        R1, R2 = one["R"], many["R"]
+        for key in ("Qs", "Ks", "Qbar", "Kbar", "cnt"):
+            assert torch.equal(one[key], many[key][:b]), key
+        for key in ("A", "R"):
+            assert torch.equal(one[key], many[key][:b * b]), key
+        assert torch.equal(one["A_scale"], many["A_scale"][:1])
+        assert torch.equal(one["idx"], many["idx"][:b, :one["idx"].shape[1]])
+        assert torch.equal(one["O"], many["O"][:, :n]) and torch.equal(one["lse"], many["lse"][:, :n])
